@@ -192,20 +192,24 @@ __device__ inline void red_cell(const Lay& L, const T* __restrict__ A, const T* 
 
 // Fine level entry: r~_0 = w^T v for every cell, and the zero-guess red
 // sweep x_r = r~_0 / a_0.  If nrm2 is given, the input is an unnormalised
-// Krylov vector: it is divided by sqrt(*nrm2) and written back first.
+// Krylov vector: it is divided by sqrt(*nrm2) and written back first.  If
+// redc is given as well, its red half is *redc times that of v0.
 template <int B, typename T>
 __global__ __launch_bounds__(256) void decouple_red_kernel(int n, int nh, const double* __restrict__ w,
                                                            const double* vin, double* vout,
-                                                           const double* __restrict__ nrm2,
+                                                           const double* __restrict__ nrm2, const double* v0,
+                                                           const double* __restrict__ redc,
                                                            const T* __restrict__ A, T* __restrict__ rp,
                                                            T* __restrict__ x) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   double hn = nrm2 ? sqrt(*nrm2) : 1.0;
+  const bool red0 = redc && t < nh;
+  const double rc = red0 ? *redc : 1.0;
   double s = 0.0;
 #pragma unroll
   for (int r = 0; r < B; ++r) {
-    double v = vin[(size_t)r * n + t];
+    double v = red0 ? rc * v0[(size_t)r * n + t] : vin[(size_t)r * n + t];
     if (nrm2) {
       v = v / hn;
       vout[(size_t)r * n + t] = v;
@@ -225,7 +229,8 @@ __global__ __launch_bounds__(256) void decouple_red_kernel(int n, int nh, const 
 template <int B, typename T, bool ABF, bool FPF>
 __global__ __launch_bounds__(256) void decouple_full_kernel(int n, int nh, const double* __restrict__ w,
                                                             const double* vin, double* vout,
-                                                            const double* __restrict__ nrm2,
+                                                            const double* __restrict__ nrm2, const double* v0,
+                                                            const double* __restrict__ redc,
                                                             const T* __restrict__ A, const T* __restrict__ Dinv,
                                                             T* __restrict__ rp, T* __restrict__ x,
                                                             T* __restrict__ Rt, T* __restrict__ Z1) {
@@ -233,10 +238,12 @@ __global__ __launch_bounds__(256) void decouple_full_kernel(int n, int nh, const
   if (t >= n) return;
   const size_t N = n;
   double hn = nrm2 ? sqrt(*nrm2) : 1.0;
+  const bool red0 = redc && t < nh;
+  const double rc = red0 ? *redc : 1.0;
   double v[B], rt[B];
 #pragma unroll
   for (int r = 0; r < B; ++r) {
-    v[r] = vin[(size_t)r * N + t];
+    v[r] = red0 ? rc * v0[(size_t)r * N + t] : vin[(size_t)r * N + t];
     if (nrm2) {
       v[r] = v[r] / hn;
       vout[(size_t)r * N + t] = v[r];
@@ -1143,7 +1150,8 @@ void stage2(cpr_ctx* ctx, const VT* vr, const T* z1, double* z) {
 }
 
 template <int B, typename T, bool ABF, bool FPF>
-void apply_variant(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z) {
+void apply_variant(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z, const double* v0,
+                   const double* redc) {
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   MGLevel& L0 = ctx->levels[0];
@@ -1155,8 +1163,8 @@ void apply_variant(cpr_ctx* ctx, const double* vin, double* v, const double* nrm
   const T* R0 = Pre<T>::R0(ctx);
   const T* Dinv = Pre<T>::Dinv(ctx);
   const double* w = ABF ? ctx->Wabf : ctx->w;
-  decouple_full_kernel<B, T, ABF, FPF><<<div_up(L.n, SB), SB, 0, s>>>(L.n, L.nh, w, vin, v, nrm2, Pre<T>::A(L0),
-                                                                        Dinv, rp, x0, Rt, Z1);
+  decouple_full_kernel<B, T, ABF, FPF><<<div_up(L.n, SB), SB, 0, s>>>(L.n, L.nh, w, vin, v, nrm2, v0, redc,
+                                                                        Pre<T>::A(L0), Dinv, rp, x0, Rt, Z1);
   if (FPF) {
     int nh = div_up(L.nh, SB);
     TIMED(CPR_KCLASS_ILU, (fpf_black_kernel<B, T><<<nh, SB, 0, s>>>(L, J, R0, Dinv, Rt, Z1)));
@@ -1169,17 +1177,18 @@ void apply_variant(cpr_ctx* ctx, const double* vin, double* v, const double* nrm
 }
 
 template <int B, typename T>
-void apply_impl(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z) {
+void apply_impl(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z, const double* v0,
+                const double* redc) {
   const bool abf = ctx->opt.decoupling == CPR_DECOUPLE_ABF;
   const bool fpf = ctx->opt.composition == CPR_COMPOSE_FPF;
-  if (abf && fpf) return apply_variant<B, T, true, true>(ctx, vin, v, nrm2, z);
-  if (abf) return apply_variant<B, T, true, false>(ctx, vin, v, nrm2, z);
-  if (fpf) return apply_variant<B, T, false, true>(ctx, vin, v, nrm2, z);
+  if (abf && fpf) return apply_variant<B, T, true, true>(ctx, vin, v, nrm2, z, v0, redc);
+  if (abf) return apply_variant<B, T, true, false>(ctx, vin, v, nrm2, z, v0, redc);
+  if (fpf) return apply_variant<B, T, false, true>(ctx, vin, v, nrm2, z, v0, redc);
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   MGLevel& L0 = ctx->levels[0];
-  decouple_red_kernel<B, T><<<div_up(L.n, SB), SB, 0, s>>>(L.n, L.nh, ctx->w, vin, v, nrm2, Pre<T>::A(L0),
-                                                            Pre<T>::r(L0), Pre<T>::x(L0));
+  decouple_red_kernel<B, T><<<div_up(L.n, SB), SB, 0, s>>>(L.n, L.nh, ctx->w, vin, v, nrm2, v0, redc,
+                                                            Pre<T>::A(L0), Pre<T>::r(L0), Pre<T>::x(L0));
   vcycle<T>(ctx);
   if (learned_on(ctx) && ctx->opt.nn_level == 0) learned_stage(ctx);
   // rows >= 1 of the quasi-IMPES decoupled residual are those of v
@@ -1241,24 +1250,37 @@ void precond_pressure_stage(cpr_ctx* ctx, const double* v) {
   MGLevel& L0 = ctx->levels[0];
   if (ctx->b == 1)
     decouple_red_kernel<1, double><<<div_up(L.n, SB), SB, 0, ctx->stream>>>(L.n, L.nh, ctx->w, v, nullptr, nullptr,
+                                                                               nullptr, nullptr,
                                                                                L0.A, L0.r, L0.x);
   else if (ctx->b == 2)
     decouple_red_kernel<2, double><<<div_up(L.n, SB), SB, 0, ctx->stream>>>(L.n, L.nh, ctx->w, v, nullptr, nullptr,
+                                                                               nullptr, nullptr,
                                                                                L0.A, L0.r, L0.x);
   else
     decouple_red_kernel<3, double><<<div_up(L.n, SB), SB, 0, ctx->stream>>>(L.n, L.nh, ctx->w, v, nullptr, nullptr,
+                                                                               nullptr, nullptr,
                                                                                L0.A, L0.r, L0.x);
   vcycle<double>(ctx);
 }
 
-void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z) {
+void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z, const double* v0,
+                   const double* redc) {
   const bool mixed = precond_fp32(ctx);
   if (ctx->b == 1) {
-    if (mixed) apply_impl<1, float>(ctx, vin, v, nrm2, z); else apply_impl<1, double>(ctx, vin, v, nrm2, z);
+    if (mixed)
+      apply_impl<1, float>(ctx, vin, v, nrm2, z, v0, redc);
+    else
+      apply_impl<1, double>(ctx, vin, v, nrm2, z, v0, redc);
   } else if (ctx->b == 2) {
-    if (mixed) apply_impl<2, float>(ctx, vin, v, nrm2, z); else apply_impl<2, double>(ctx, vin, v, nrm2, z);
+    if (mixed)
+      apply_impl<2, float>(ctx, vin, v, nrm2, z, v0, redc);
+    else
+      apply_impl<2, double>(ctx, vin, v, nrm2, z, v0, redc);
   } else {
-    if (mixed) apply_impl<3, float>(ctx, vin, v, nrm2, z); else apply_impl<3, double>(ctx, vin, v, nrm2, z);
+    if (mixed)
+      apply_impl<3, float>(ctx, vin, v, nrm2, z, v0, redc);
+    else
+      apply_impl<3, double>(ctx, vin, v, nrm2, z, v0, redc);
   }
   border_precond(ctx, vin, v, nrm2, z);   // rate wells' BHP rows, after the cell correction
 }

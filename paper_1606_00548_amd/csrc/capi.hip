@@ -703,7 +703,8 @@ int cpr_nn_features(cpr_ctx_t* ctx, const double* rprime, float* feat, double* s
 int cpr_export_krylov(cpr_ctx_t* ctx, int j, double* v) {
   if (check_ctx(ctx)) return CPR_EINVAL;
   if (!v || j < 0 || j > ctx->mcap || !ctx->V) return set_err(ctx, CPR_EINVAL, "bad basis index");
-  CPR_TRY(vec_cs_to_nat(ctx, ctx->V + (size_t)j * vec_len(ctx), v));
+  krylov_vector(ctx, j, ctx->vout);
+  CPR_TRY(vec_cs_to_nat(ctx, ctx->vout, v));
   return launch_check(ctx, "cpr_export_krylov");
 }
 

@@ -344,6 +344,9 @@ struct cpr_ctx {
   double* hhost = nullptr;     // pinned host mirror
   double* hhost_dev = nullptr; // its device address (kernels write the Hessenberg column there)
   int nblk = 0;
+  // black-row Krylov cycle (krylov.hip): basis vectors of the last FGMRES
+  // cycle whose red halves are kept as scalars (0: stored whole)
+  int kry_half = 0;
 
   // kernel-duration sampling (one kernel class at a time)
   // learned pressure correction
@@ -448,6 +451,11 @@ void launch_spmv(int b, const Lay& L, const double* A, const double* x, double* 
 // y = A x (or rhs - A x) for the whole system: the block stencil and, with
 // rate-controlled wells, their border (eq. (16)).
 void system_spmv(cpr_ctx* ctx, const double* x, double* y, const double* rhs);
+// y = A z for z = M^-1 v of a context whose preconditioner solves the red
+// rows exactly (red_rows_exact): black rows from the stencil, red rows
+// copied from v, or left unwritten when v is null.
+void launch_spmv_black(int b, const Lay& L, const double* A, const double* z, double* y, const double* v,
+                       hipStream_t s);
 // Well part of a preconditioner application: z_w = (v_w - C z_cells) / D,
 // normalising v_w = vin_w / sqrt(*nrm2) first when nrm2 is given.
 void border_precond(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z);
@@ -461,8 +469,11 @@ int setup_cpr(cpr_ctx* ctx);
 // apply.hip
 // z = M^-1 v.  If nrm2 (device) is given, vin holds an unnormalised Krylov
 // vector: v = vin / sqrt(*nrm2) is formed and stored on the way (vin may
-// equal v).  Otherwise v must equal vin.
-void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z);
+// equal v).  Otherwise v must equal vin.  With redc (device scalar, nrm2
+// given too) only the black half of vin is read; the red half of v is
+// *redc / sqrt(*nrm2) times that of v0.
+void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z,
+                   const double* v0 = nullptr, const double* redc = nullptr);
 
 void precond_pressure_stage(cpr_ctx* ctx, const double* v);
 
@@ -494,7 +505,21 @@ inline bool precond_fp32(const cpr_ctx* c) { return c->opt.precision == CPR_PREC
 // solve to plain FP64 CPR.
 inline bool learned_on(const cpr_ctx* c) { return c->opt.learned && !c->fp64_now; }
 
+// Whether (A M^-1 v)_red = v_red for the preconditioner in use.  Red cells
+// couple only to black ones, so the red-black block ILU(0) has no fill in
+// its red rows and they solve A~ z = r~ exactly, whatever the pressure stage
+// and the decoupling did before (the decoupling W is invertible); measured
+// against the stencil product the two differ by its own rounding, eps |A| |z|.
+// Not so with the FP32 preconditioner (FP32 rounding), with tiles as colours
+// (fill inside a tile) and with rate-controlled wells (their columns are
+// outside the ILU).
+inline bool red_rows_exact(const cpr_ctx* c) {
+  return !precond_fp32(c) && c->opt.ilu_order == CPR_ILU_RED_BLACK && c->nrate == 0;
+}
+
 int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st);
+// Basis vector j of the last FGMRES cycle, whole, into dst (colour-split).
+void krylov_vector(cpr_ctx* ctx, int j, double* dst);
 int bicgstab_solve(cpr_ctx* ctx, cpr_stats_t* st);
 void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, const double* dx, hipStream_t s);
 // Bubble-point floor of the black-oil update: the first PVT pressure node.

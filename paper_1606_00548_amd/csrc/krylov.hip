@@ -25,7 +25,17 @@
 //   coef:   beta = sqrt(e - |a|^2), g = (d - a.c) / beta (one block)
 //   update: v_j = (uh_j - V_j a) / beta over slot j; u = w - V_j c - g v_j
 //           over slot j+1, with ||u||^2
-// (V_j: the j final vectors before slot j).  The host adds nu_j a to column
+// (V_j: the j final vectors before slot j).
+//
+// Black-row cycles (red_rows_exact): (A M^-1 v)_red = v_red, so the red half
+// of every basis vector is a multiple of that of v_0, and only the multiple
+// is kept: the SpMV computes the black rows, the passes above run over the
+// black halves of the slots, and the coefficient kernel adds the red halves'
+// share of each inner product, (product of the two multiples) * |v_0,red|^2.
+// The multiples follow the vectors' own recurrences.  The basis is the one
+// of whole vectors in exact arithmetic, at half of their traffic.
+//
+// The host adds nu_j a to column
 // j-1 of the Hessenberg matrix, sets its entry (j, j-1) to nu_j beta,
 // writes column j (c, g, nu_{j+1} = ||u||) and recomputes the Givens QR.
 #include <cmath>
@@ -199,12 +209,19 @@ __global__ __launch_bounds__(KB) void orth_fused_kernel(long len, int nv, const 
   }
 }
 
-// Delayed CGS2, dot pass of step j (j <= NV final vectors before slot j):
-// part rows 0..j-1 = V_k . uh, rows j..2j-1 = V_k . w, row 2j = uh . w,
+// Where element e of a pass over the vectors lies: pass over whole vectors
+// (nh = 0), or over their black halves (nh = cells per colour, at most three
+// planes of 2 nh).
+__device__ inline long slot_at(long e, long nh) {
+  return nh ? e + nh * (1 + (e >= nh ? 1 : 0) + (e >= 2 * nh ? 1 : 0)) : e;
+}
+
+// Delayed CGS2, dot pass of step j (j <= NV final vectors before slot j)
+// over len elements (slot_at): part rows 0..j-1 = V_k . uh, rows j..2j-1 = V_k . w, row 2j = uh . w,
 // row 2j+1 = uh . uh, each the sum over this block's slice.
 template <int NV>
-__global__ __launch_bounds__(KB) void dcgs_dots_kernel(long len, int j, const double* __restrict__ V, size_t stride,
-                                                       const double* __restrict__ uh, const double* __restrict__ w,
+__global__ __launch_bounds__(KB) void dcgs_dots_kernel(long len, long nh, int j, const double* __restrict__ V,
+                                                       size_t stride, const double* __restrict__ uh, const double* __restrict__ w,
                                                        double* __restrict__ part, int nblk) {
   __shared__ double sh[(2 * NV + 2) * (KB / 64)];
   long per = (len + nblk - 1) / nblk;
@@ -213,7 +230,8 @@ __global__ __launch_bounds__(KB) void dcgs_dots_kernel(long len, int j, const do
   double aa[NV], cc[NV], dd = 0.0, ee = 0.0;
 #pragma unroll
   for (int k = 0; k < NV; ++k) aa[k] = cc[k] = 0.0;
-  for (long e = beg + threadIdx.x; e < end; e += KB) {
+  for (long q = beg + threadIdx.x; q < end; q += KB) {
+    const long e = slot_at(q, nh);
     // every basis load issued before the arithmetic (vectors past j read as 0)
     double vv[NV];
 #pragma unroll
@@ -258,24 +276,37 @@ enum { D_DOTS = 384, D_COEF = 512, D_NRM = 640, D_HOST = 512, D_SLOT = 256 };
 enum { C_A = 0, C_C = 32, C_INVB = 64, C_G = 65 };                       // in D_COEF
 enum { S_A = 0, S_C = 32, S_BETA = 64, S_G = 65, S_NRM = 66, S_FLAG = 67 };   // in a host slot
 
-// The scalars of step j from its reduced dots (one thread, fixed order):
-// beta = sqrt(e - |a|^2) (1 at step 0, which has no vector to
-// reorthogonalise) and g = (d - a.c) / beta; flag = 1 when beta^2 <= 0.
-__global__ void dcgs_coef_kernel(int j, const double* __restrict__ dots, double* __restrict__ coef,
-                                 double* __restrict__ host) {
-  for (int i = threadIdx.x; i < j; i += blockDim.x) {
-    coef[C_A + i] = dots[i];
-    coef[C_C + i] = dots[j + i];
-    host[S_A + i] = dots[i];
-    host[S_C + i] = dots[j + i];
+// Scalars of a black-row cycle (hdev + D_RED): the red multiples of the
+// final vectors, that of the unnormalised u, and u's share of ||u||^2.
+enum { D_RED = 704, R_V = 0, R_U = 64, R_ADD = 65 };
+
+// The scalars of step j from its reduced dots (one wavefront, lane i = basis
+// vector i < j <= 32; sums by a fixed butterfly): beta = sqrt(e - |a|^2) (1
+// at step 0, which has no vector to reorthogonalise) and g = (d - a.c) /
+// beta; flag = 1 when beta^2 <= 0.  red (black-row cycles): the dots lack the
+// red halves' share, multiple * multiple * s0 with s0 = |v_0,red|^2; uh's
+// multiple is that of the last u over its norm sqrt(*nrm2).
+__global__ __launch_bounds__(64) void dcgs_coef_kernel(int j, const double* __restrict__ dots,
+                                                       double* __restrict__ coef, double* __restrict__ host,
+                                                       double* __restrict__ red, double s0,
+                                                       const double* __restrict__ nrm2) {
+  const int i = threadIdx.x;
+  const double uh = red ? (j == 0 ? 1.0 : red[R_U] / sqrt(*nrm2)) : 0.0;
+  const double rv = red && i < j ? red[R_V + i] : 0.0;
+  const double share = red ? rv * uh * s0 : 0.0;
+  const double a = i < j ? dots[i] + share : 0.0;
+  const double c = i < j ? dots[j + i] + share : 0.0;
+  if (i < j) {
+    coef[C_A + i] = a;
+    coef[C_C + i] = c;
+    host[S_A + i] = a;
+    host[S_C + i] = c;
   }
-  if (threadIdx.x != 0) return;
-  double aa = 0.0, ac = 0.0;
-  for (int i = 0; i < j; ++i) {
-    aa += dots[i] * dots[i];
-    ac += dots[i] * dots[j + i];
-  }
-  const double d = dots[2 * j], e = dots[2 * j + 1];
+  const double aa = wave_sum(a * a), ac = wave_sum(a * c);
+  const double ra = wave_sum(a * rv), rcv = wave_sum(c * rv);
+  if (i != 0) return;
+  const double own = red ? uh * uh * s0 : 0.0;
+  const double d = dots[2 * j] + own, e = dots[2 * j + 1] + own;
   const double b2 = j == 0 ? 1.0 : e - aa;
   const bool bad = !(b2 > 0.0);
   const double beta = bad ? 0.0 : sqrt(b2);
@@ -285,15 +316,23 @@ __global__ void dcgs_coef_kernel(int j, const double* __restrict__ dots, double*
   host[S_BETA] = beta;
   host[S_G] = g;
   host[S_FLAG] = bad ? 1.0 : 0.0;
+  if (red) {
+    const double vj = bad ? 0.0 : (uh - ra) / beta;   // multiple of v_j = (uh - V a) / beta
+    const double u = uh - rcv - g * vj;               // of u = w - V c - g v_j (w's is uh's)
+    red[R_V + j] = vj;
+    red[R_U] = u;
+    red[R_ADD] = u * u * s0;
+  }
 }
 
 // Delayed CGS2, update pass of step j: v_j = (uh - V a) / beta over uh,
-// u = w - V c - g v_j over w, and part row 0 = this slice of ||u||^2.
+// u = w - V c - g v_j over w, and part row 0 = this slice of ||u||^2, over
+// len elements (slot_at).
 template <int NV>
-__global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, int j, const double* __restrict__ V, size_t stride,
-                                                         double* __restrict__ uh, double* __restrict__ w,
-                                                         const double* __restrict__ coef, double* __restrict__ part,
-                                                         int nblk) {
+__global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int j, const double* __restrict__ V,
+                                                         size_t stride, double* __restrict__ uh,
+                                                         double* __restrict__ w, const double* __restrict__ coef,
+                                                         double* __restrict__ part, int nblk) {
   __shared__ double cs[2 * NV + 2];
   __shared__ double sh[KB / 64];
   for (int i = threadIdx.x; i < NV; i += KB) {
@@ -310,7 +349,8 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, int j, const 
   long beg = (long)blockIdx.x * per;
   long end = beg + per < len ? beg + per : len;
   double acc = 0.0;
-  for (long e = beg + threadIdx.x; e < end; e += KB) {
+  for (long q = beg + threadIdx.x; q < end; q += KB) {
+    const long e = slot_at(q, nh);
     double vv[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) vv[k] = k < j ? ldnt(V + k * stride + e) : 0.0;
@@ -335,6 +375,37 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, int j, const 
     for (int q = 0; q < KB / 64; ++q) t += sh[q];
     part[blockIdx.x] = t;
   }
+}
+
+// part rows 0 and 1: this block's share of the squares of x's black and red
+// cells (b planes of n = 2 nh cells).
+__global__ __launch_bounds__(KB) void colour_norms_kernel(long len, long nh, const double* __restrict__ x,
+                                                          double* __restrict__ part, int nblk) {
+  __shared__ double sh[CHUNK * (KB / 64)];
+  __shared__ double tot[CHUNK];
+  long per = (len + nblk - 1) / nblk;
+  long beg = (long)blockIdx.x * per;
+  long end = beg + per < len ? beg + per : len;
+  double acc[CHUNK];
+#pragma unroll
+  for (int q = 0; q < CHUNK; ++q) acc[q] = 0.0;
+  for (long e = beg + threadIdx.x; e < end; e += KB) {
+    const long c = e - 2 * nh * ((e >= 2 * nh ? 1 : 0) + (e >= 4 * nh ? 1 : 0));
+    const double v = x[e] * x[e];
+    acc[c < nh ? 1 : 0] += v;
+  }
+  block_sum_chunk(acc, 2, sh, tot);
+  if (threadIdx.x < 2) part[(size_t)threadIdx.x * nblk + blockIdx.x] = tot[threadIdx.x];
+}
+
+// dst = the whole basis vector j of a black-row cycle: black half as stored,
+// red half *rv times that of v_0.
+__global__ void whole_vector_kernel(long len, long nh, const double* __restrict__ v0, const double* __restrict__ vj,
+                                    const double* __restrict__ rv, double* __restrict__ dst) {
+  long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= len) return;
+  const long c = e - 2 * nh * ((e >= 2 * nh ? 1 : 0) + (e >= 4 * nh ? 1 : 0));
+  dst[e] = c < nh ? *rv * v0[e] : vj[e];
 }
 
 __global__ void scale_kernel(long len, double a, const double* __restrict__ x, double* __restrict__ y) {
@@ -554,33 +625,58 @@ int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double*
   return CPR_OK;
 }
 
+// ||x||^2 and its red cells' share (host).  Syncs.
+static int reduce_colour_norms(cpr_ctx* ctx, const double* x, double* all, double* red) {
+  hipStream_t s = ctx->stream;
+  const long bn = (long)ctx->b * ctx->lay.n;
+  colour_norms_kernel<<<ctx->nblk, KB, 0, s>>>(bn, ctx->lay.nh, x, ctx->part, ctx->nblk);
+  reduce_kernel<<<2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr);
+  CPR_TRY(hipGetLastError());
+  CPR_TRY(hipMemcpyAsync(ctx->hhost, ctx->hdev, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+  CPR_TRY(hipStreamSynchronize(s));
+  *red = ctx->hhost[1];
+  *all = ctx->hhost[0] + ctx->hhost[1];
+  return CPR_OK;
+}
+
 namespace {
 
-void dcgs_dots(cpr_ctx* ctx, long len, int j, const double* uh, const double* w) {
+// y = A z for z = M^-1 v
+void precond_spmv(cpr_ctx* ctx, const double* z, double* y, const double* v) {
+  if (red_rows_exact(ctx))
+    launch_spmv_black(ctx->b, ctx->lay, ctx->J, z, y, v, ctx->stream);
+  else
+    system_spmv(ctx, z, y, nullptr);
+}
+
+// nh > 0: over the black halves of the vectors only.
+void dcgs_dots(cpr_ctx* ctx, long nh, int j, const double* uh, const double* w) {
   hipStream_t s = ctx->stream;
   const int nblk = ctx->nblk;
-  const size_t stride = (size_t)len;
+  const size_t stride = (size_t)vec_len(ctx);
+  const long len = nh ? ctx->b * nh : vec_len(ctx);
   prof_begin(ctx, CPR_KCLASS_ORTH);
   if (j <= 8)
-    dcgs_dots_kernel<8><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, ctx->part, nblk);
+    dcgs_dots_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, ctx->part, nblk);
   else if (j <= 16)
-    dcgs_dots_kernel<16><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, ctx->part, nblk);
+    dcgs_dots_kernel<16><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, ctx->part, nblk);
   else
-    dcgs_dots_kernel<32><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, ctx->part, nblk);
+    dcgs_dots_kernel<32><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, ctx->part, nblk);
   prof_end(ctx, CPR_KCLASS_ORTH);
 }
 
-void dcgs_update(cpr_ctx* ctx, long len, int j, double* uh, double* w, const double* coef) {
+void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const double* coef) {
   hipStream_t s = ctx->stream;
   const int nblk = ctx->nblk;
-  const size_t stride = (size_t)len;
+  const size_t stride = (size_t)vec_len(ctx);
+  const long len = nh ? ctx->b * nh : vec_len(ctx);
   prof_begin(ctx, CPR_KCLASS_ORTH);
   if (j <= 8)
-    dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
   else if (j <= 16)
-    dcgs_update_kernel<16><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<16><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
   else
-    dcgs_update_kernel<32><<<nblk, KB, 0, s>>>(len, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<32><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
   prof_end(ctx, CPR_KCLASS_ORTH);
 }
 
@@ -632,16 +728,19 @@ static bool early_stall(const cpr_ctx* ctx, int steps, int its, double est, doub
          ctx->opt.stall_ratio > 0 && est > std::pow(ctx->opt.stall_ratio, (double)STALL_EARLY / m) * beta;
 }
 
-int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, int& its, int& k, std::vector<double>& R,
+// s0 >= 0: a black-row cycle, s0 = |v_0,red|^2.
+int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, double s0, int& its, int& k, std::vector<double>& R,
                 std::vector<double>& g) {
   hipStream_t s = ctx->stream;
-  const long len = vec_len(ctx);
-  const size_t stride = (size_t)len;
+  const size_t stride = (size_t)vec_len(ctx);
+  const bool black = s0 >= 0.0;
+  const long nh = black ? ctx->lay.nh : 0;
   const int m = ctx->opt.restart;
   const double rtol = ctx->opt.rtol;
   const int max_iter = ctx->opt.max_iter;
   const int nblk = ctx->nblk;
   double* hd = ctx->hdev;
+  double* red = black ? hd + D_RED : nullptr;
   std::vector<double> Hh((size_t)(m + 1) * m, 0.0);
   auto launch_step = [&](int j) -> int {
     double* uj = ctx->V + (size_t)j * stride;
@@ -651,21 +750,27 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, int& its, int& k, std::
     // slot j becomes uh_j = u_j / nu_j inside the preconditioner's first kernel
     {
       PhaseScope ps(ctx, PH_PRECOND);
-      precond_apply(ctx, uj, uj, j == 0 ? nullptr : hd + D_NRM, zj);
+      if (j == 0)
+        precond_apply(ctx, uj, uj, nullptr, zj);
+      else
+        precond_apply(ctx, uj, uj, hd + D_NRM, zj, black ? ctx->V : nullptr, black ? red + R_U : nullptr);
     }
     {
       PhaseScope ps(ctx, PH_SPMV);
       prof_begin(ctx, CPR_KCLASS_SPMV);
-      system_spmv(ctx, zj, w, nullptr);
+      if (black)
+        launch_spmv_black(ctx->b, ctx->lay, ctx->J, zj, w, nullptr, s);
+      else
+        system_spmv(ctx, zj, w, nullptr);
       prof_end(ctx, CPR_KCLASS_SPMV);
     }
     {
       PhaseScope ps(ctx, PH_ORTH);
-      dcgs_dots(ctx, len, j, uj, w);
+      dcgs_dots(ctx, nh, j, uj, w);
       reduce_kernel<<<2 * j + 2, KB, 0, s>>>(ctx->part, nblk, hd + D_DOTS, nullptr);
-      dcgs_coef_kernel<<<1, 64, 0, s>>>(j, hd + D_DOTS, hd + D_COEF, slot);
-      dcgs_update(ctx, len, j, uj, w, hd + D_COEF);
-      reduce_kernel<<<1, KB, 0, s>>>(ctx->part, nblk, hd + D_NRM, nullptr, slot + S_NRM);
+      dcgs_coef_kernel<<<1, 64, 0, s>>>(j, hd + D_DOTS, hd + D_COEF, slot, red, s0, hd + D_NRM);
+      dcgs_update(ctx, nh, j, uj, w, hd + D_COEF);
+      reduce_kernel<<<1, KB, 0, s>>>(ctx->part, nblk, hd + D_NRM, black ? red + R_ADD : nullptr, slot + S_NRM);
     }
     CPR_TRY(hipGetLastError());
     CPR_TRY(hipEventRecord(ctx->ev_iter[j & 1], s));
@@ -714,7 +819,18 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, int& its, int& k, std::
     if (learned_on(ctx)) learned_discard_last(ctx);
   }
   givens_qr(Hh, m, k, beta, R, g);
+  if (black) ctx->kry_half = k;
   return CPR_OK;
+}
+
+void krylov_vector(cpr_ctx* ctx, int j, double* dst) {
+  const long len = vec_len(ctx);
+  const double* vj = ctx->V + (size_t)j * len;
+  if (j > 0 && j < ctx->kry_half)
+    whole_vector_kernel<<<div_up(len, 256), 256, 0, ctx->stream>>>(len, ctx->lay.nh, ctx->V, vj,
+                                                                   ctx->hdev + D_RED + R_V + j, dst);
+  else
+    (void)hipMemcpyAsync(dst, vj, len * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream);
 }
 
 // ctx->rs holds the right-hand side, ctx->xs receives the solution
@@ -744,6 +860,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
     ~FallbackReset() { c->fp64_now = false; }
   } fallback_reset{ctx};
   ctx->fp64_now = false;
+  ctx->kry_half = 0;
   ph_solve_start(ctx);
 
   const bool from_x0 = ctx->opt.x0 != 0;
@@ -776,8 +893,8 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
   double beta_start = 0.0;   // true residual at the start of the last cycle
   double* hd = ctx->hdev;  // h1 [0,64), h1+h2 [64,128), ||w||^2 [128], h2 [192,256), y [256,320)
   while (true) {
-    double rr;
-    rc = reduce_dot(ctx, r, r, len, &rr);
+    double rr, rr_red = 0.0;
+    rc = dcgs && ctx->nrate == 0 ? reduce_colour_norms(ctx, r, &rr, &rr_red) : reduce_dot(ctx, r, r, len, &rr);
     if (rc) return rc;
     double beta = std::sqrt(rr);
     S.true_rel = beta / bnorm;
@@ -805,7 +922,9 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
     g[0] = beta;
     int k = 0;
     if (dcgs) {
-      if ((rc = dcgs2_cycle(ctx, beta, bnorm, its, k, H, g)) != CPR_OK) {
+      ctx->kry_half = 0;
+      const double s0 = red_rows_exact(ctx) ? rr_red / rr : -1.0;   // |v_0,red|^2, v_0 = r / beta
+      if ((rc = dcgs2_cycle(ctx, beta, bnorm, s0, its, k, H, g)) != CPR_OK) {
         if (st) *st = S;
         return rc;
       }
@@ -827,7 +946,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
         {
           PhaseScope ps(ctx, PH_SPMV);
           prof_begin(ctx, CPR_KCLASS_SPMV);
-          system_spmv(ctx, zj, w, nullptr);
+          precond_spmv(ctx, zj, w, vj);
           prof_end(ctx, CPR_KCLASS_SPMV);
         }
         {
@@ -946,6 +1065,7 @@ int bicgstab_solve(cpr_ctx* ctx, cpr_stats_t* st) {
   cpr_stats_t S = {};
   S.mg_levels = (int)ctx->levels.size();
   S.qimpes_fallback = ctx->qimpes_bad;
+  ctx->kry_half = 0;
   ph_solve_start(ctx);
 
   zero_kernel<<<eb, 256, 0, s>>>(len, x);
@@ -993,7 +1113,7 @@ int bicgstab_solve(cpr_ctx* ctx, cpr_stats_t* st) {
       {
         PhaseScope ps(ctx, PH_SPMV);
         prof_begin(ctx, CPR_KCLASS_SPMV);
-        system_spmv(ctx, ph, v, nullptr);
+        precond_spmv(ctx, ph, v, p);
         prof_end(ctx, CPR_KCLASS_SPMV);
       }
       {
@@ -1009,7 +1129,7 @@ int bicgstab_solve(cpr_ctx* ctx, cpr_stats_t* st) {
       {
         PhaseScope ps(ctx, PH_SPMV);
         prof_begin(ctx, CPR_KCLASS_SPMV);
-        system_spmv(ctx, sh, t, nullptr);
+        precond_spmv(ctx, sh, t, sv);
         prof_end(ctx, CPR_KCLASS_SPMV);
       }
       {
