@@ -13,6 +13,7 @@
 //  * Block ILU(0) of W A in red-then-black order: on the 7-point graph it
 //    keeps every off-diagonal block and changes only the black diagonals,
 //    D'_i = A~_ii - sum_k A~_ik D'_k^-1 A~_ki over the red neighbours k.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.h"
@@ -269,180 +270,244 @@ __global__ void gj_step_kernel(int nc, int p, const double* __restrict__ src, do
   }
 }
 
-constexpr int GJ_LDS_MAX = 128;   // coarsest levels up to this size are inverted in one workgroup
+constexpr int SCHUR_MAX = 512;   // coarsest levels up to this size are inverted through the Schur complement
 
-// Coarsest inverse through the red-black Schur complement (nc <= 128).  A
+// Coarsest inverse through the red-black Schur complement (nc <= 512).  A
 // 7-point operator couples red cells only to black ones, so with the cells
 // ordered red then black A = [Dr B; C Db] with diagonal Dr, Db, and
 //   S = Db - C Dr^-1 B,
 //   A^-1 = [Dr^-1 - X C Dr^-1, X; -S^-1 C Dr^-1, S^-1],  X = -Dr^-1 B S^-1.
-// Only S (at most 64 x 64) goes through Gauss-Jordan with partial pivoting
-// (in LDS, 16 threads per row); B and C have at most six entries per row
-// and column, so the other blocks are short sums.  Inverse written column
-// major (and as FP32).  A zero or non-finite red diagonal or S pivot sets
-// the singular flag.
-constexpr int SCH_MAX = 64;
-constexpr int SCH_LD = SCH_MAX + 1;
+// Only S (at most 256 x 256) goes through Gauss-Jordan with partial
+// pivoting, in one workgroup (schur_invert_kernel); B and C have at most six
+// entries per row and column, so S and the other blocks are short sums, one
+// thread per entry (schur_build_kernel, schur_expand_kernel).  A zero or non-finite red
+// diagonal or S pivot sets the singular flag.
+//
+// Position of coarsest cell t among the cells of its colour: its place in
+// the colour's half, or t / 2 in natural order (nx is odd there, so colours
+// alternate along t within a plane, and over the whole grid or plane by
+// plane with an even number of cells each).
+__device__ inline int colour_pos(const Lay& L, int t) { return L.cs ? (t < L.nh ? t : t - L.nh) : t >> 1; }
+// The black cell at position q.
+__device__ inline int black_cell(const Lay& L, int q) {
+  if (L.cs) return L.nh + q;
+  int i, j, k;
+  lay_coords(L, 2 * q, i, j, k);
+  return 2 * q + 1 - ((i + j + k) & 1);
+}
+__device__ inline int colour_of(const Lay& L, int t) {
+  int i, j, k;
+  lay_coords(L, t, i, j, k);
+  return (i + j + k) & 1;
+}
 
-__global__ __launch_bounds__(1024) void gj_schur_kernel(Lay L, const double* __restrict__ A,
-                                                        double* __restrict__ inv, float* __restrict__ invf,
-                                                        int* __restrict__ flag) {
-  extern __shared__ double sm[];
-  double* S = sm;                        // [SCH_MAX][SCH_LD]
-  double* X = sm + SCH_MAX * SCH_LD;     // [SCH_MAX][SCH_MAX]
-  __shared__ int colr[GJ_LDS_MAX], pos[GJ_LDS_MAX];
-  __shared__ int red[SCH_MAX], blk[SCH_MAX];
-  __shared__ double Dinvr[SCH_MAX], Db[SCH_MAX], fcol[SCH_MAX];
-  __shared__ int Bk[SCH_MAX][6], Ck[SCH_MAX][6];
-  __shared__ double Bv[SCH_MAX][6], Cv[SCH_MAX][6], Tv[SCH_MAX][6];
-  __shared__ int piv[SCH_MAX], idx[SCH_MAX];
-  __shared__ double pvs;
-  __shared__ int prs, nr_s;
-  const int nc = L.n, tid = threadIdx.x;
-  // colours and positions within a colour
-  if (tid < nc) {
-    int i, j, k;
-    lay_coords(L, tid, i, j, k);
-    colr[tid] = (i + j + k) & 1;
-  }
-  __syncthreads();
-  if (tid < nc) {
-    int q = 0;
-    for (int u = 0; u < tid; ++u) q += colr[u] == colr[tid];
-    pos[tid] = q;
-    if (colr[tid] == 0) red[q] = tid; else blk[q] = tid;
-  }
-  if (tid == 0) {
-    int q = 0;
-    for (int u = 0; u < nc; ++u) q += colr[u] == 0;
-    nr_s = q;
-  }
-  __syncthreads();
-  const int nr = nr_s, nb = nc - nr;
-  // red rows: 1/Dr, B (black neighbours), C^T (the black rows' coupling back)
-  if (tid < nr) {
-    const int c = red[tid];
-    const double d = A[c];
-    if (!(fabs(d) > TINY) || !isfinite(d)) atomicExch(flag, 1);
-    Dinvr[tid] = 1.0 / d;
-    int i, j, k;
-    lay_coords(L, c, i, j, k);
-    for (int e = 0; e < 6; ++e) {
-      const int nbc = lay_nbr(L, i, j, k, e + 1);
-      const int opp = (e ^ 1) + 1;
-      Bk[tid][e] = nbc >= 0 ? pos[nbc] : -1;
-      Bv[tid][e] = nbc >= 0 ? A[(size_t)(e + 1) * nc + c] : 0.0;
-      Tv[tid][e] = nbc >= 0 ? A[(size_t)opp * nc + nbc] : 0.0;
-    }
-  } else if (tid >= 512 && tid - 512 < nb) {
-    const int kb = tid - 512, c = blk[kb];
-    Db[kb] = A[c];
-    int i, j, k;
-    lay_coords(L, c, i, j, k);
-    for (int e = 0; e < 6; ++e) {
-      const int nbc = lay_nbr(L, i, j, k, e + 1);
-      Ck[kb][e] = nbc >= 0 ? pos[nbc] : -1;
-      Cv[kb][e] = nbc >= 0 ? A[(size_t)(e + 1) * nc + c] : 0.0;
+// Maximum over a wavefront, to every lane: rows of 16 lanes by shifts, then
+// the rows' last lanes broadcast upwards (DPP moves, a tenth of the latency
+// of the same butterfly through LDS permutes).
+__device__ inline unsigned wave_max(unsigned k) {
+  auto step = [&](unsigned o) { k = o > k ? o : k; };
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x111, 0xf, 0xf, false));   // row_shr:1
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x112, 0xf, 0xf, false));
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x114, 0xf, 0xf, false));
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x118, 0xf, 0xf, false));
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x142, 0xa, 0xf, false));   // row_bcast:15
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)k, 0x143, 0xc, 0xf, false));   // row_bcast:31
+  return (unsigned)__builtin_amdgcn_readlane((int)k, 63);
+}
+
+// S = Db - C Dr^-1 B (row major), one thread per entry: black cells couple
+// through the red cells adjacent to both.
+__global__ __launch_bounds__(256) void schur_build_kernel(Lay L, const double* __restrict__ A, double* __restrict__ S,
+                                                          int* __restrict__ flag) {
+  const int nc = L.n, nb = L.cs ? L.nh : nc / 2;
+  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+  if (g < nc && colour_of(L, g) == 0 && (!(fabs(A[g]) > TINY) || !isfinite(A[g]))) atomicExch(flag, 1);
+  if (g >= nb * nb) return;
+  const int t1 = black_cell(L, g / nb), t2 = black_cell(L, g % nb);
+  int i, j, k, i2, j2, k2;
+  lay_coords(L, t1, i, j, k);
+  lay_coords(L, t2, i2, j2, k2);
+  double v = t1 == t2 ? A[t1] : 0.0;
+  if (abs(i - i2) + abs(j - j2) + abs(k - k2) <= 2) {
+#pragma unroll
+    for (int e = 1; e < 7; ++e) {
+      int di, dj, dk;
+      dir_offset(e, di, dj, dk);
+      const int r = lay_nbr(L, i, j, k, e);
+      // direction from the red cell (i + di, ...) on to t2, if they are adjacent
+      const int ei = i2 - i - di, ej = j2 - j - dj, ek = k2 - k - dk;
+      if (r < 0 || abs(ei) + abs(ej) + abs(ek) != 1) continue;
+      const int e2 = ei ? (ei < 0 ? 1 : 2) : ej ? (ej < 0 ? 3 : 4) : (ek < 0 ? 5 : 6);
+      v -= A[(size_t)e * nc + t1] * (1.0 / A[r]) * A[(size_t)e2 * nc + r];
     }
   }
-  __syncthreads();
-  // S = Db - C Dr^-1 B
-  for (int q = tid; q < nb * nb; q += 1024) {
-    const int k1 = q / nb, k2 = q % nb;
-    double v = k1 == k2 ? Db[k1] : 0.0;
-    for (int e = 0; e < 6; ++e) {
-      const int r = Ck[k1][e];
-      if (r < 0) continue;
-      double brk = 0.0;
-      for (int e2 = 0; e2 < 6; ++e2) brk += Bk[r][e2] == k2 ? Bv[r][e2] : 0.0;
-      v -= Cv[k1][e] * Dinvr[r] * brk;
+  S[g] = v;
+}
+
+// S^-1 (row major, into `out`) by in-place Gauss-Jordan on nb <= NB rows.
+// The pivots are a serial chain, so the matrix stays in one workgroup:
+// thread (ty, tx) of TR x TC owns rows ty + TR a and columns tx + TC b, RR x
+// CC entries of which CR columns' are registers (all but the largest form,
+// whose 512 KB need LDS as well), and a step costs two barriers: every wave
+// finds the pivot among the unused rows by itself from the column written
+// last; the pivot row's owners write it out; all update, and the owners of
+// the next column write that.  Rows are not exchanged: the row of pivot p is
+// remembered, and the exchange form leaves M[q_p][p'] = S^-1[p][q_p'].  The
+// pivot's magnitude is compared in its leading 23 bits (exponent and 12 bits
+// of the mantissa, the row index below them: the lowest row of nearly equal
+// ones), which bounds the multipliers by 1 + 2^-12.
+// A 432-cell coarsest level (192x192x48) takes 403 us with the kernels around
+// it (383 here), where one launch per column of the whole operator took 2680;
+// 128 cells (128x128x32) take 66 us (50 here), 123 as one workgroup with S in
+// LDS and three barriers a step.
+template <int NB, int TR, int TC, int CR>
+__global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const double* __restrict__ S,
+                                                               double* __restrict__ out, int* __restrict__ flag) {
+  constexpr int NT = TR * TC, RR = NB / TR, CC = NB / TC, NS = (NB + 63) / 64;
+  extern __shared__ double sm[];      // [(CC - CR) * RR][NT]
+  __shared__ double col[2][NS * 64], row[NB];
+  __shared__ int prow[NB], pcol[NB];
+  const int tid = threadIdx.x, tx = tid % TC, ty = tid / TC, lane = tid & 63;
+  double m[RR][CR];
+  auto get = [&](int a, int b) -> double { return b < CR ? m[a][b < CR ? b : 0] : sm[((b - CR) * RR + a) * NT + tid]; };
+  auto put = [&](int a, int b, double v) {
+    if (b < CR) m[a][b < CR ? b : 0] = v; else sm[((b - CR) * RR + a) * NT + tid] = v;
+  };
+#pragma unroll
+  for (int a = 0; a < RR; ++a)
+#pragma unroll
+    for (int b = 0; b < CC; ++b) {
+      const int r = ty + TR * a, c = tx + TC * b;
+      put(a, b, r < nb && c < nb ? S[(size_t)r * nb + c] : 0.0);
     }
-    S[k1 * SCH_LD + k2] = v;
-  }
+  if (tx == 0)
+#pragma unroll
+    for (int a = 0; a < RR; ++a) col[0][ty + TR * a] = m[a][0];
+  unsigned used = 0;   // bit i: row lane + 64 i is a pivot already (or none)
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+    if (lane + 64 * i >= nb) used |= 1u << i;
   __syncthreads();
-  // Gauss-Jordan on S in place: thread (row tid / 16, columns tid % 16 + 16 q)
-  const int row = tid >> 4, l16 = tid & 15;
-  const bool own = row < nb;
   for (int p = 0; p < nb; ++p) {
-    if (tid < 64) {
-      double best = -1.0;
-      int bi = p;
-      if (p + tid < nb) { best = fabs(S[(p + tid) * SCH_LD + p]); bi = p + tid; }
-      for (int o = 32; o > 0; o >>= 1) {
-        double ov = __shfl_down(best, o, 64);
-        int oi = __shfl_down(bi, o, 64);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
-      if (tid == 0) {
-        prs = bi;
-        pvs = S[bi * SCH_LD + p];
-        piv[p] = bi;
-        if (!(best > TINY) || !isfinite(best)) atomicExch(flag, 1);
-      }
+    const double* cp = col[p & 1];
+    unsigned key = 0;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int r = lane + 64 * i;
+      const unsigned k = (((unsigned)__double2hiint(cp[r]) & 0x7fffff00u) | (255u - (unsigned)r)) + 1u;
+      if (!((used >> i) & 1u) && k > key) key = k;
+    }
+    const int q = (int)(255u - ((wave_max(key) - 1u) & 255u));
+    const double pv = cp[q];
+    if ((q & 63) == lane) used |= 1u << (q >> 6);
+    if (tid == 0) {
+      prow[p] = q;
+      pcol[q] = p;
+      if (!(fabs(pv) > TINY) || !isfinite(pv)) atomicExch(flag, 1);
+    }
+    const double pinv = 1.0 / pv;
+    const int qa = q / TR;
+    if (ty == q % TR) {
+#pragma unroll
+      for (int a = 0; a < RR; ++a)
+        if (a == qa) {
+#pragma unroll
+          for (int b = 0; b < CC; ++b)
+            row[tx + TC * b] = tx + TC * b == p ? 1.0 : get(a, b);
+        }
     }
     __syncthreads();
-    const int pr = prs;
-    const double pinv = 1.0 / pvs;
-    if (tid < nb) {
-      const int c = tid;
-      double top = S[pr * SCH_LD + c], old = S[p * SCH_LD + c];
-      if (pr != p) S[pr * SCH_LD + c] = old;
-      S[p * SCH_LD + c] = (c == p ? 1.0 : top) * pinv;
-      if (c == p) { fcol[p] = 0.0; fcol[pr] = pr == p ? 0.0 : old; }
-    } else if (tid >= 512 && tid - 512 < nb) {
-      const int q = tid - 512;
-      if (q != p && q != pr) fcol[q] = S[q * SCH_LD + p];
+    double f[RR];
+#pragma unroll
+    for (int a = 0; a < RR; ++a) f[a] = cp[ty + TR * a];
+    double* cn = col[(p + 1) & 1];
+    const int pb = p / TC, px = p % TC, nxb = (p + 1) / TC, nxx = (p + 1) % TC;
+    if (tx == px) {   // column p starts from zero: it receives -f / pivot
+#pragma unroll
+      for (int b = 0; b < CC; ++b)
+        if (b == pb)
+#pragma unroll
+          for (int a = 0; a < RR; ++a) put(a, b, 0.0);
     }
-    __syncthreads();
-    if (own && row != p) {
-      const double f = fcol[row];
-      for (int c = l16; c < nb; c += 16) S[row * SCH_LD + c] = (c == p ? 0.0 : S[row * SCH_LD + c]) - f * S[p * SCH_LD + c];
+#pragma unroll
+    for (int b = 0; b < CC; ++b) {
+      const double pr = row[tx + TC * b] * pinv;
+#pragma unroll
+      for (int a = 0; a < RR; ++a) put(a, b, get(a, b) - f[a] * pr);
+    }
+    if (ty == q % TR) {   // the pivot row itself
+#pragma unroll
+      for (int a = 0; a < RR; ++a)
+        if (a == qa)
+#pragma unroll
+          for (int b = 0; b < CC; ++b) put(a, b, row[tx + TC * b] * pinv);
+    }
+    if (tx == nxx) {
+#pragma unroll
+      for (int b = 0; b < CC; ++b)
+        if (b == nxb)
+#pragma unroll
+          for (int a = 0; a < RR; ++a) cn[ty + TR * a] = get(a, b);
     }
     __syncthreads();
   }
-  // row interchanges undone as column interchanges, last first: column j of
-  // S^-1 is column idx[j] of the eliminated matrix
-  if (tid == 0) {
-    for (int c = 0; c < nb; ++c) idx[c] = c;
-    for (int p = nb - 1; p >= 0; --p) {
-      const int q = piv[p];
-      const int t = idx[p]; idx[p] = idx[q]; idx[q] = t;
+#pragma unroll
+  for (int b = 0; b < CC; ++b)
+#pragma unroll
+    for (int a = 0; a < RR; ++a) {
+      const int r = ty + TR * a, c = tx + TC * b;
+      if (r < nb && c < nb)
+        out[(size_t)pcol[r] * nb + prow[c]] = get(a, b);
+    }
+}
+
+// A^-1 (column major, and as FP32) from S^-1, one thread per entry.
+__global__ __launch_bounds__(256) void schur_expand_kernel(Lay L, const double* __restrict__ A,
+                                                           const double* __restrict__ Si, double* __restrict__ inv,
+                                                           float* __restrict__ invf) {
+  const int nc = L.n, nb = L.cs ? L.nh : nc / 2;
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= nc * nc) return;
+  const int ci = q / nc, ri = q % nc;       // column cell, row cell
+  const int pc = colour_pos(L, ci), pr = colour_pos(L, ri);
+  const bool rb = colour_of(L, ri) == 1, cb = colour_of(L, ci) == 1;
+  int rn[6];
+  double rv[6];
+  {
+    int i, j, k;
+    lay_coords(L, ri, i, j, k);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      const int n = lay_nbr(L, i, j, k, e + 1);
+      rn[e] = n >= 0 ? colour_pos(L, n) : -1;
+      rv[e] = n >= 0 ? A[(size_t)(e + 1) * nc + ri] : 0.0;
     }
   }
-  __syncthreads();
-  auto Si = [&](int i, int j) { return S[i * SCH_LD + idx[j]]; };
-  // X = -Dr^-1 B S^-1
-  for (int q = tid; q < nr * nb; q += 1024) {
-    const int r = q / nb, j = q % nb;
+  // (row, black column j) of A^-1
+  auto black_col = [&](int j) {
+    if (rb) return Si[(size_t)pr * nb + j];
     double v = 0.0;
+#pragma unroll
     for (int e = 0; e < 6; ++e)
-      if (Bk[r][e] >= 0) v += Bv[r][e] * Si(Bk[r][e], j);
-    X[r * SCH_MAX + j] = -Dinvr[r] * v;
-  }
-  __syncthreads();
-  // the four blocks of A^-1, column major
-  for (int q = tid; q < nc * nc; q += 1024) {
-    const int ci = q / nc, ri = q % nc;       // column cell, row cell
-    const int pc = pos[ci], pri = pos[ri];
-    double v;
-    if (colr[ri] == 1 && colr[ci] == 1) {
-      v = Si(pri, pc);
-    } else if (colr[ri] == 0 && colr[ci] == 1) {
-      v = X[pri * SCH_MAX + pc];
-    } else if (colr[ri] == 1) {               // black row, red column
-      v = 0.0;
-      for (int e = 0; e < 6; ++e)
-        if (Bk[pc][e] >= 0) v += Si(pri, Bk[pc][e]) * Tv[pc][e];
-      v = -v * Dinvr[pc];
-    } else {                                  // red row, red column
-      v = 0.0;
-      for (int e = 0; e < 6; ++e)
-        if (Bk[pc][e] >= 0) v += X[pri * SCH_MAX + Bk[pc][e]] * Tv[pc][e];
-      v = (pri == pc ? Dinvr[pri] : 0.0) - v * Dinvr[pc];
+      if (rn[e] >= 0) v += rv[e] * Si[(size_t)rn[e] * nb + j];
+    return -(1.0 / A[ri]) * v;
+  };
+  double v;
+  if (cb) {
+    v = black_col(pc);
+  } else {
+    v = 0.0;
+    int i, j, k;
+    lay_coords(L, ci, i, j, k);
+    for (int e = 0; e < 6; ++e) {
+      const int n = lay_nbr(L, i, j, k, e + 1);
+      if (n >= 0) v += black_col(colour_pos(L, n)) * A[(size_t)((e ^ 1) + 1) * nc + n];
     }
-    inv[q] = v;
-    if (invf) invf[q] = (float)v;
+    const double dc = 1.0 / A[ci];
+    v = (ri == ci ? dc : 0.0) - v * dc;
   }
+  inv[q] = v;
+  if (invf) invf[q] = (float)v;
 }
 
 // Copy the right half of [I | M^-1] into column-major storage.
@@ -669,15 +734,24 @@ int setup_cpr(cpr_ctx* ctx) {
   // dense inverse of the coarsest level
   const MGLevel& last = ctx->levels.back();
   int nc = last.lay.n;
-  if (nc <= GJ_LDS_MAX) {
-    const size_t smem = ((size_t)SCH_MAX * SCH_LD + (size_t)SCH_MAX * SCH_MAX) * sizeof(double);
-    static bool attr_set = false;
-    if (!attr_set) {
-      CPR_TRY(hipFuncSetAttribute((const void*)gj_schur_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)smem));
-      attr_set = true;
+  if (nc <= SCHUR_MAX) {
+    const int nb = last.lay.cs ? last.lay.nh : nc / 2;
+    double* sb = ctx->gj_work;
+    double* si = ctx->gj_work + (size_t)nb * nb;
+    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, a>>>(last.lay, last.A, sb, ctx->flag);
+    if (nb <= 64) {
+      schur_invert_kernel<64, 16, 16, 4><<<1, 256, 0, a>>>(nb, sb, si, ctx->flag);
+    } else if (nb <= 128) {
+      schur_invert_kernel<128, 32, 16, 8><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
+    } else if (nb <= 224) {
+      schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
+    } else {
+      constexpr int lds = 4 * 8 * 512 * sizeof(double);   // a quarter of the 256 x 256 matrix
+      CPR_TRY(hipFuncSetAttribute((const void*)schur_invert_kernel<256, 32, 16, 12>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      schur_invert_kernel<256, 32, 16, 12><<<1, 512, lds, a>>>(nb, sb, si, ctx->flag);
     }
-    gj_schur_kernel<<<1, 1024, smem, a>>>(last.lay, last.A, ctx->cinv, ctx->cinvf, ctx->flag);
+    schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, a>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
   } else {
     double* bufA = ctx->gj_work;
     double* bufB = ctx->gj_work + (size_t)nc * 2 * nc;
