@@ -22,9 +22,9 @@
 // residuals), restriction of r - A x by 2x2x2 aggregation, coarse solve,
 // black post-sweep reading the prolongated red values x + alpha e_c on the
 // fly (the prolongated red values themselves are overwritten by the red
-// post-sweep, so they are never stored), red post-sweep.  All levels from
-// the first one with at most FUSE_MAX cells down to the dense coarsest solve
-// run in one single-workgroup kernel, which removes a dozen latency-bound
+// post-sweep, so they are never stored), red post-sweep.  The smallest levels
+// down to the dense coarsest solve run in one single-workgroup kernel where
+// they fit its LDS (cycle_fused_level), which removes a dozen latency-bound
 // launches per cycle.
 #include "internal.h"
 
@@ -32,8 +32,8 @@ namespace {
 
 constexpr int FUSE_MAX = 4096;   // cells of the first level handled by the fused kernel
 constexpr int DENSE_FUSED_MAX = 1024;
-constexpr int DENSE_PF = 16;
-constexpr int STAGE_UNROLL = 8;  // loads per thread in flight while the fused kernel stages its levels     // coarsest-inverse entries per thread loaded at the fused kernel's start
+constexpr int DENSE_PF = 17;     // coarsest-inverse entries per thread (of 1024) loaded at the fused kernel's start
+constexpr int STAGE_UNROLL = 8;  // loads per thread in flight while the fused kernel stages its levels
 constexpr int MAXLV = 16;
 // Threads per workgroup of the per-cell kernels (sweeps, restriction,
 // decoupling): one wave per workgroup streams their planes faster than four.
@@ -127,29 +127,6 @@ __device__ inline void black_pre_cell(const Lay& L, const T* __restrict__ A, con
   T xb = (r[t] - s) / A[t];
   x[t] = xb;
   res[q] = r[t] - (A[t] * xb + s);
-}
-
-// coarse cell tc: sum of the fine residuals of its aggregate (P^T r), fine
-// cells in natural order; black residuals were recorded by the black sweep
-template <typename T, bool NT = true>
-__device__ inline void restrict_cell(const Lay& F, const Lay& C, const T* __restrict__ A,
-                                     const T* __restrict__ r, const T* __restrict__ x,
-                                     const T* __restrict__ res, T* __restrict__ rc, int tc) {
-  int ci, cj, ck;
-  lay_coords(C, tc, ci, cj, ck);
-  T acc = 0;
-  for (int fk = 2 * ck; fk <= 2 * ck + 1 && fk < F.nz; ++fk)
-    for (int fj = 2 * cj; fj <= 2 * cj + 1 && fj < F.ny; ++fj)
-      for (int fi = 2 * ci; fi <= 2 * ci + 1 && fi < F.nx; ++fi) {
-        int f = lay_index(F, fi, fj, fk);
-        if (f < F.nh) {
-          T y = A[f] * x[f] + offdiag_sum<T, NT>(F, A, x, f);
-          acc += r[f] - y;
-        } else {
-          acc += res[f - F.nh];
-        }
-      }
-  rc[tc] = acc;
 }
 
 // black cell q after the coarse correction: neighbours are red cells whose
@@ -307,17 +284,20 @@ __global__ __launch_bounds__(256) void black_pre_kernel(Lay L, const T* __restri
 // takes its row's red cell (residual r - A x formed here) and its black
 // cell (residual recorded by the black sweep) in the same order, so the
 // lanes do not diverge on the colour; the two terms are added as a sum of
-// two, whose value does not depend on their order.
+// two, whose value does not depend on their order.  With seq the eight
+// residuals are summed one after the other in natural order instead, as the
+// single-workgroup kernel does it (a level takes either route by its size
+// and type; its values do not change with it).
 // If xc is given, the coarse level's zero-guess red sweep is done here too:
 // a red coarse cell stores x = r / a_0 as soon as its r is known.
 template <typename T>
 __global__ __launch_bounds__(256) void restrict4_kernel(Lay F, Lay C, const T* __restrict__ A,
                                                         const T* __restrict__ r, const T* __restrict__ x,
                                                         const T* __restrict__ res, T* __restrict__ rc,
-                                                        const T* __restrict__ Ac, T* __restrict__ xc) {
+                                                        const T* __restrict__ Ac, T* __restrict__ xc, int seq) {
   int g = blockIdx.x * blockDim.x + threadIdx.x;
   int cn = g >> 2, sub = g & 3;
-  T acc = 0;
+  T acc = 0, lo = 0, hi = 0;
   int tc = -1;
   if (cn < C.n) {
     const int ci = cn % C.nx, cjk = cn / C.nx;
@@ -335,10 +315,21 @@ __global__ __launch_bounds__(256) void restrict4_kernel(Lay F, Lay C, const T* _
       }
       if (fb < F.nx) vb = res[lay_index(F, fb, fj, fk) - F.nh];
       acc = vr + vb;
+      lo = odd ? vb : vr;
+      hi = odd ? vr : vb;
     }
   }
-  acc += __shfl_down(acc, 2, 4);
-  acc += __shfl_down(acc, 1, 4);
+  if (seq) {
+    acc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc += __shfl(lo, q, 4);
+      acc += __shfl(hi, q, 4);
+    }
+  } else {
+    acc += __shfl_down(acc, 2, 4);
+    acc += __shfl_down(acc, 1, 4);
+  }
   if (tc >= 0 && sub == 0) {
     rc[tc] = acc;
     if (xc && tc < C.nh) red_zero_cell(Ac, rc, xc, tc);
@@ -360,16 +351,31 @@ __global__ __launch_bounds__(256) void red_kernel(Lay L, const T* __restrict__ A
   if (q < L.nh) red_cell(L, A, r, x, q);
 }
 
-// Coarsest level alone when it is too large for the fused kernel:
-// x = A^-1 r with the dense FP64 inverse (column major).
+// Coarsest level alone when the fused kernel does not take it: x = A^-1 r
+// with the dense FP64 inverse (column major).  A workgroup takes GV_ROWS
+// rows, so that a column's read is a whole 128-byte line, and splits the
+// columns over its GV_PARTS rows of threads: the inverse (0.9 MB for 336
+// cells) is read by every CU it can occupy, where one workgroup was bound by
+// its own path to the L2 (5 us against about 20 of the fused kernel's 52).
+constexpr int GV_ROWS = 16, GV_PARTS = 16;
 template <typename T>
-__global__ void coarse_gemv_kernel(int nc, const double* __restrict__ inv, const T* __restrict__ r,
-                                   T* __restrict__ x) {
-  int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= nc) return;
+__global__ __launch_bounds__(GV_ROWS * GV_PARTS) void coarse_gemv_kernel(int nc, const double* __restrict__ inv,
+                                                                        const T* __restrict__ r, T* __restrict__ x) {
+  __shared__ double sh[GV_PARTS][GV_ROWS];
+  const int lr = threadIdx.x % GV_ROWS, part = threadIdx.x / GV_ROWS;
+  const int row = blockIdx.x * GV_ROWS + lr;
   double s = 0.0;
-  for (int c = 0; c < nc; ++c) s += inv[(size_t)c * nc + row] * (double)r[c];
-  x[row] = (T)s;
+  if (row < nc) {
+#pragma unroll 8
+    for (int c = part; c < nc; c += GV_PARTS) s += inv[(size_t)c * nc + row] * (double)r[c];
+  }
+  sh[part][lr] = s;
+  __syncthreads();
+  if (part == 0 && row < nc) {
+    double t = 0.0;
+    for (int q = 0; q < GV_PARTS; ++q) t += sh[q][lr];
+    x[row] = (T)t;
+  }
 }
 
 // ------------------------------------------------------------ fused small levels
@@ -381,51 +387,48 @@ struct CoarseArgs {
   const T* A[MAXLV];
   T* x[MAXLV];
   T* r[MAXLV];
-  T* res[MAXLV];
-  // element offsets of each level's arrays in the LDS copy (staged form)
+  // element offsets of each level's arrays in the LDS copy
   int sA[MAXLV], sx[MAXLV], sr[MAXLV], sres[MAXLV];
   const double* inv;
   T alpha;
   int pre, post;             // Gauss-Seidel sweeps before / after the coarse correction
 };
 
-// Bytes of LDS the staged form may take for its copy of the levels (the
-// kernel adds 8 KB of its own): on gfx950 a workgroup may use up to 160 KB.
-constexpr int COARSE_LDS_MAX = 96 * 1024;
+// Bytes of LDS the fused kernel's copy of the levels may take (the kernel
+// adds 8 KB of its own): on gfx950 a workgroup may use up to 160 KB.
+constexpr int COARSE_LDS_MAX = 144 * 1024;
 
-// Staged form (LDS = true): the levels' stencils and the first level's
-// right-hand side are copied into LDS once, every sweep, restriction and
-// prolongation then reads and writes LDS, and the levels' x (and the
-// restricted r) are copied back at the end; the coarsest inverse is read
-// from global memory.  Every sweep depends on the one before, so with the
-// arrays in global memory each costs an L2 round trip.  The arithmetic and
-// its order are the same in both forms.
-template <typename T, bool LDS>
+// The levels' stencils and the first level's right-hand side are copied into
+// LDS once, every sweep, restriction and prolongation then reads and writes
+// LDS, and the levels' x (and the restricted r) are copied back at the end;
+// the coarsest inverse is read from global memory.  Every sweep depends on
+// the one before, so with the arrays in global memory each would cost an L2
+// round trip: such levels take the multi-block kernels.
+template <typename T>
 __global__ __launch_bounds__(1024) void coarse_cycle_kernel(CoarseArgs<T> a) {
   extern __shared__ __align__(16) unsigned char stage_raw[];
   __shared__ double part[1024];
   T* sb = reinterpret_cast<T*>(stage_raw);
   const int tid = threadIdx.x, nt = blockDim.x;
-  auto Ap = [&](int l) -> const T* { return LDS ? sb + a.sA[l] : a.A[l]; };
-  auto xp = [&](int l) -> T* { return LDS ? sb + a.sx[l] : a.x[l]; };
-  auto rp = [&](int l) -> T* { return LDS ? sb + a.sr[l] : a.r[l]; };
-  auto resp = [&](int l) -> T* { return LDS ? sb + a.sres[l] : a.res[l]; };
+  auto Ap = [&](int l) -> const T* { return sb + a.sA[l]; };
+  auto xp = [&](int l) -> T* { return sb + a.sx[l]; };
+  auto rp = [&](int l) -> T* { return sb + a.sr[l]; };
+  auto resp = [&](int l) -> T* { return sb + a.sres[l]; };   // residuals of the level's cells
   // The dense coarsest solve x = A^-1 r: thread (row, p) sums columns p,
-  // p + parts, ... of its row.  When every thread has at most DENSE_PF of
-  // them, they are loaded here, so that the loads overlap the sweeps of the
-  // finer levels instead of forming a chain of dependent loads at the end.
-  const int nc = a.lay[a.count - 1].n;
-  const int parts = nt / nc;            // nc <= DENSE_FUSED_MAX <= nt
+  // p + parts, ... of its row, at most DENSE_PF of them.  They are loaded
+  // here, so that the loads overlap the sweeps of the finer levels instead of
+  // forming a chain of dependent loads at the end.
+  const int nc = a.lay[a.count - 1].n;  // <= DENSE_FUSED_NC
+  const int parts = nt / nc;
   const int drow = tid % nc, dp = tid / nc;
   const bool dactive = tid < nc * parts;
-  const bool prefetch = nc * nc <= nt * DENSE_PF;
   double pre[DENSE_PF];
 #pragma unroll
   for (int u = 0; u < DENSE_PF; ++u) {
     const int c = dp + u * parts;
-    pre[u] = prefetch && dactive && c < nc ? a.inv[(size_t)c * nc + drow] : 0.0;
+    pre[u] = dactive && c < nc ? a.inv[(size_t)c * nc + drow] : 0.0;
   }
-  if constexpr (LDS) {
+  {
     // STAGE_UNROLL independent loads per thread in flight at a time
     auto stage = [&](const T* g, T* d, int len) {
       for (int base = 0; base < len; base += STAGE_UNROLL * nt) {
@@ -452,16 +455,31 @@ __global__ __launch_bounds__(1024) void coarse_cycle_kernel(CoarseArgs<T> a) {
     T *x = xp(l), *r = rp(l), *res = resp(l);
     for (int q = tid; q < F.nh; q += nt) red_zero_cell(A, r, x, q);
     __syncthreads();
-    for (int q = tid; q < F.nh; q += nt) black_pre_cell<T, false>(F, A, r, x, res, q);
+    for (int q = tid; q < F.nh; q += nt) black_pre_cell<T, false>(F, A, r, x, res + F.nh, q);
     __syncthreads();
     for (int k = 1; k < a.pre; ++k) {
       for (int q = tid; q < F.nh; q += nt) red_cell<T, false>(F, A, r, x, q);
       __syncthreads();
-      for (int q = tid; q < F.nh; q += nt) black_pre_cell<T, false>(F, A, r, x, res, q);
+      for (int q = tid; q < F.nh; q += nt) black_pre_cell<T, false>(F, A, r, x, res + F.nh, q);
       __syncthreads();
     }
+    // restriction: the red residuals (the black sweep recorded the others),
+    // one thread each, then every aggregate's sum in natural order
     T* rc = rp(l + 1);
-    for (int tc = tid; tc < C.n; tc += nt) restrict_cell<T, false>(F, C, A, r, x, res, rc, tc);
+    for (int q = tid; q < F.nh; q += nt) {
+      const T y = A[q] * x[q] + offdiag_sum<T, false>(F, A, x, q);
+      res[q] = r[q] - y;
+    }
+    __syncthreads();
+    for (int tc = tid; tc < C.n; tc += nt) {
+      int ci, cj, ck;
+      lay_coords(C, tc, ci, cj, ck);
+      T acc = 0;
+      for (int fk = 2 * ck; fk <= 2 * ck + 1 && fk < F.nz; ++fk)
+        for (int fj = 2 * cj; fj <= 2 * cj + 1 && fj < F.ny; ++fj)
+          for (int fi = 2 * ci; fi <= 2 * ci + 1 && fi < F.nx; ++fi) acc += res[lay_index(F, fi, fj, fk)];
+      rc[tc] = acc;
+    }
     __syncthreads();
   }
   {
@@ -469,14 +487,10 @@ __global__ __launch_bounds__(1024) void coarse_cycle_kernel(CoarseArgs<T> a) {
     const T* rr = rp(L);
     if (dactive) {
       double s = 0.0;
-      if (prefetch) {
 #pragma unroll
-        for (int u = 0; u < DENSE_PF; ++u) {
-          const int c = dp + u * parts;
-          if (c < nc) s += pre[u] * (double)rr[c];
-        }
-      } else {
-        for (int c = dp; c < nc; c += parts) s += a.inv[(size_t)c * nc + drow] * (double)rr[c];
+      for (int u = 0; u < DENSE_PF; ++u) {
+        const int c = dp + u * parts;
+        if (c < nc) s += pre[u] * (double)rr[c];
       }
       part[tid] = s;
     }
@@ -505,13 +519,11 @@ __global__ __launch_bounds__(1024) void coarse_cycle_kernel(CoarseArgs<T> a) {
       __syncthreads();
     }
   }
-  if constexpr (LDS) {
-    for (int l = 0; l < a.count; ++l) {
-      const int n = a.lay[l].n;
-      for (int i = tid; i < n; i += nt) a.x[l][i] = sb[a.sx[l] + i];
-      if (l > 0)
-        for (int i = tid; i < n; i += nt) a.r[l][i] = sb[a.sr[l] + i];
-    }
+  for (int l = 0; l < a.count; ++l) {
+    const int n = a.lay[l].n;
+    for (int i = tid; i < n; i += nt) a.x[l][i] = sb[a.sx[l] + i];
+    if (l > 0)
+      for (int i = tid; i < n; i += nt) a.r[l][i] = sb[a.sr[l] + i];
   }
 }
 
@@ -526,7 +538,7 @@ size_t coarse_stage_layout(CoarseArgs<T>& a) {
       a.sA[q] = (int)off;
       off += 7 * n;
       a.sres[q] = (int)off;
-      off += n / 2 + 1;
+      off += n;
     }
     a.sr[q] = (int)off;
     off += n;
@@ -538,19 +550,13 @@ size_t coarse_stage_layout(CoarseArgs<T>& a) {
 }
 
 template <typename T>
-void launch_coarse_cycle(CoarseArgs<T>& a, hipStream_t s) {
-  // the staged form needs more than the default 64 KB of dynamic LDS
-  static const bool big_lds = [] {
-    const bool ok = hipFuncSetAttribute((const void*)coarse_cycle_kernel<T, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, COARSE_LDS_MAX) == hipSuccess;
-    if (!ok) (void)hipGetLastError();   // leave no error for the launch checks
-    return ok;
-  }();
-  const size_t bytes = coarse_stage_layout(a);
-  if (big_lds && bytes <= (size_t)COARSE_LDS_MAX)
-    coarse_cycle_kernel<T, true><<<1, 1024, bytes, s>>>(a);
-  else
-    coarse_cycle_kernel<T, false><<<1, 1024, 0, s>>>(a);
+hipError_t launch_coarse_cycle(CoarseArgs<T>& a, hipStream_t s) {
+  // more than the default 64 KB of dynamic LDS
+  static const hipError_t big_lds = hipFuncSetAttribute(
+      (const void*)coarse_cycle_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, COARSE_LDS_MAX);
+  if (big_lds != hipSuccess) return big_lds;
+  coarse_cycle_kernel<T><<<1, 1024, coarse_stage_layout(a), s>>>(a);
+  return hipSuccess;
 }
 
 // ------------------------------------------------------------ stage 2 + block ILU(0)
@@ -1045,7 +1051,8 @@ __global__ __launch_bounds__(256) void fpf_resid_kernel(Lay L, const T* __restri
     prof_end(ctx, cls);    \
   } while (0)
 
-// First level handled by the single-workgroup kernel (nl: none).
+// First of the levels small enough for a single workgroup (nl: none).  The
+// learned stage runs above them (options.nn_level).
 int fused_level(const cpr_ctx* ctx) {
   const int nl = (int)ctx->levels.size();
   const int nc = ctx->levels.back().lay.n;
@@ -1060,11 +1067,52 @@ int fused_level(const cpr_ctx* ctx) {
 }
 
 template <typename T>
+CoarseArgs<T> coarse_args(cpr_ctx* ctx, int first) {
+  CoarseArgs<T> a;
+  a.count = (int)ctx->levels.size() - first;
+  for (int q = 0; q < a.count; ++q) {
+    MGLevel& L = ctx->levels[first + q];
+    a.lay[q] = L.lay;
+    a.A[q] = Pre<T>::A(L);
+    a.x[q] = Pre<T>::x(L);
+    a.r[q] = Pre<T>::r(L);
+  }
+  a.inv = ctx->cinv;
+  a.alpha = (T)ctx->opt.mg_alpha;
+  a.pre = ctx->opt.mg_pre;
+  a.post = ctx->opt.mg_post;
+  return a;
+}
+
+// First level the cycle hands to the single-workgroup kernel (nl: none, and
+// the coarsest solve is a kernel of its own).  The kernel saves the launches
+// of its levels, but is one workgroup: it takes levels that its LDS holds
+// (up to about 1,790 cells in FP64, 3,570 in FP32) over a coarsest inverse of
+// at most DENSE_FUSED_NC rows, which its threads can hold in registers from
+// the start; reading a larger one costs it more than the launches.  One
+// application, V(1,1) FP64, one workgroup against multi-block kernels: 64
+// against 72 us with 1,024 over 128 cells (64x64x16), 78 against 73 with
+// 1,600 over 200 (80x80x16), and with the levels in global memory 343 against
+// 290 with 2,464 over 336 (60x220x85), 156 against 92 with 3,456 over 432
+// (96x96x24).
+constexpr int DENSE_FUSED_NC = 128;
+template <typename T>
+int cycle_fused_level(cpr_ctx* ctx) {
+  const int nl = (int)ctx->levels.size();
+  if (ctx->levels.back().lay.n > DENSE_FUSED_NC) return nl;
+  for (int l = fused_level(ctx); l + 1 < nl; ++l) {
+    CoarseArgs<T> a = coarse_args<T>(ctx, l);
+    if (coarse_stage_layout(a) <= (size_t)COARSE_LDS_MAX) return l;
+  }
+  return nl;
+}
+
+template <typename T>
 void vcycle(cpr_ctx* ctx) {
   hipStream_t s = ctx->stream;
   const int nl = (int)ctx->levels.size();
   const int nc = ctx->levels.back().lay.n;
-  const int fuse = fused_level(ctx);
+  const int small = fused_level(ctx), fuse = cycle_fused_level<T>(ctx);
   const T alpha = (T)ctx->opt.mg_alpha;
   const int down = fuse < nl ? fuse : nl - 1;   // levels smoothed by multi-block kernels
   for (int l = 0; l < down; ++l) {
@@ -1083,27 +1131,16 @@ void vcycle(cpr_ctx* ctx) {
     const bool next_multi = l + 1 < down;
     restrict4_kernel<T><<<div_up(4L * C.lay.n, SB), SB, 0, s>>>(
         L.lay, C.lay, Pre<T>::A(L), Pre<T>::r(L), Pre<T>::x(L), Pre<T>::res(L), Pre<T>::r(C),
-        next_multi ? Pre<T>::A(C) : nullptr, next_multi ? Pre<T>::x(C) : nullptr);
+        next_multi ? Pre<T>::A(C) : nullptr, next_multi ? Pre<T>::x(C) : nullptr, l >= small);
   }
   if (fuse < nl) {
-    CoarseArgs<T> a;
-    a.count = nl - fuse;
-    for (int q = 0; q < a.count; ++q) {
-      MGLevel& L = ctx->levels[fuse + q];
-      a.lay[q] = L.lay;
-      a.A[q] = Pre<T>::A(L);
-      a.x[q] = Pre<T>::x(L);
-      a.r[q] = Pre<T>::r(L);
-      a.res[q] = Pre<T>::res(L);
-    }
-    a.inv = ctx->cinv;
-    a.alpha = alpha;
-    a.pre = ctx->opt.mg_pre;
-    a.post = ctx->opt.mg_post;
-    launch_coarse_cycle<T>(a, s);
+    CoarseArgs<T> a = coarse_args<T>(ctx, fuse);
+    const hipError_t e = launch_coarse_cycle<T>(a, s);
+    if (e != hipSuccess) set_hip_err(ctx, e, "coarse_cycle_kernel");
   } else {
     MGLevel& L = ctx->levels.back();
-    coarse_gemv_kernel<T><<<div_up(nc, 128), 128, 0, s>>>(nc, ctx->cinv, Pre<T>::r(L), Pre<T>::x(L));
+    coarse_gemv_kernel<T><<<div_up(nc, GV_ROWS), GV_ROWS * GV_PARTS, 0, s>>>(nc, ctx->cinv, Pre<T>::r(L),
+                                                                             Pre<T>::x(L));
   }
   for (int l = down - 1; l >= 0; --l) {
     MGLevel& L = ctx->levels[l];
