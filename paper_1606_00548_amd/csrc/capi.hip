@@ -718,6 +718,10 @@ int cpr_newton_update(cpr_ctx_t* ctx, double* x, const double* dx) {
 int cpr_spmv(cpr_ctx_t* ctx, const double* x, double* y) {
   if (check_ctx(ctx)) return CPR_EINVAL;
   if (!x || !y) return set_err(ctx, CPR_EINVAL, "null argument");
+  if (spmv_nat_ok(ctx, x, y)) {
+    launch_spmv_nat(ctx->b, ctx->lay, ctx->J, x, y, ctx->stream);
+    return launch_check(ctx, "cpr_spmv");
+  }
   CPR_TRY(vec_nat_to_cs(ctx, x, ctx->vin));
   system_spmv(ctx, ctx->vin, ctx->vout, nullptr);
   CPR_TRY(vec_cs_to_nat(ctx, ctx->vout, y));

@@ -451,6 +451,15 @@ void launch_spmv(int b, const Lay& L, const double* A, const double* x, double* 
 // y = A x (or rhs - A x) for the whole system: the block stencil and, with
 // rate-controlled wells, their border (eq. (16)).
 void system_spmv(cpr_ctx* ctx, const double* x, double* y, const double* rhs);
+// y = A x in natural order, without rate-controlled wells; x and y must not
+// overlap.
+void launch_spmv_nat(int b, const Lay& L, const double* A, const double* x, double* y, hipStream_t s);
+// Whether the product can take it: no rate wells (their border is stored for
+// colour-split vectors) and x, y apart.
+inline bool spmv_nat_ok(const cpr_ctx* c, const double* x, const double* y) {
+  const size_t len = (size_t)c->b * c->lay.n;
+  return c->nrate == 0 && (x + len <= y || y + len <= x);
+}
 // y = A z for z = M^-1 v of a context whose preconditioner solves the red
 // rows exactly (red_rows_exact): black rows from the stencil, red rows
 // copied from v, or left unwritten when v is null.
