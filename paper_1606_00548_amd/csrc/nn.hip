@@ -18,14 +18,13 @@
 // channels in K-steps of 16; activations are converted to BF16 as they are
 // loaded.  The data gradient is the same kernel with mirrored taps and
 // transposed channel blocks; the weight gradient is a GEMM over voxels
-// (M = input channels, N = output channels) whose per-chunk partial sums
+// (M = input channels, N = output channels) whose per-workgroup partial sums
 // are reduced in a fixed order, so training is deterministic.
 #include <cmath>
 #include <cstring>
 
 #include "internal.h"
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -35,10 +34,10 @@ constexpr int NCONV = 7;
 constexpr int CIN[NCONV] = {3, 16, 32, 64, 64, 64, 32};
 constexpr int COUT[NCONV] = {16, 32, 64, 64, 64, 32, 16};
 constexpr int CIN_PAD[NCONV] = {16, 16, 32, 64, 64, 64, 32};
-constexpr int WG_CHUNK = 2048;   // voxels per weight-gradient block
+constexpr int WG_MAX = 512;      // workgroups of one weight gradient
 
-// FP32 -> BF16, round to nearest even (one value; the staging of the
-// convolutions converts pairs with pack_bf16x2)
+// FP32 -> BF16, round to nearest even (one value; staging converts pairs
+// with pack_bf16x2)
 __device__ inline short f2bf(float f) {
   unsigned u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
@@ -412,101 +411,199 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs p) {
   }
 }
 
-// Weight gradient partials: part[chunk][t][ci][co] = sum over the chunk's
-// voxels v of X~[v + off_t][ci] dZ[v][co]; one block per (chunk, tap).
-template <int CI, int CO, bool UP>
-__global__ __launch_bounds__(256) void wgrad_kernel(Geo g, const float* __restrict__ X,
-                                                    const float* __restrict__ dZ, float* __restrict__ part) {
-  __shared__ float red[4][CI * CO];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int t = blockIdx.y;
-  const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-  const long total = (long)g.batch * g.V;
-  const long c0 = (long)blockIdx.x * WG_CHUNK;
-  const int cnx = g.nx >> 1, cny = g.ny >> 1, cV = (g.nx >> 1) * (g.ny >> 1) * (g.nz >> 1);
-  f32x4 acc[CI / 16][CO / 16];
+// Weight gradient: dW[t][ci][co] = sum over voxels v of X~[v + off_t][ci]
+// dZ[v][co], a GEMM with K = voxels on v_mfma_f32_16x16x32_bf16 (A: row ci =
+// lane % 16, B: column co = lane % 16, both k = 8 (lane / 16) + e).  A
+// workgroup takes CIB input and 16 output channels and every nwg-th tile of
+// 16 x 4 x 4 voxels; it stages the tile's dZ and X~ with a one-voxel halo in
+// LDS as BF16, transposed to [channel][voxel] (pairs of x-neighbours packed
+// as they are read), so that a lane's eight k values, eight voxels along x,
+// are one 16-byte read, and each value is read from memory about 2.5 times
+// instead of 27.  Its three waves take the three dz; per K-step of two rows
+// a wave reads dZ once and X~ once per dy, and the dx = -1, +1 operands are
+// funnel shifts of the dx = 0 one and a neighbour on either side.  The 27 /
+// 3 * CIB / 16 accumulators stay in registers over all of the workgroup's
+// tiles; its partial sums are added up in workgroup order by
+// wgrad_reduce_kernel.  The bias gradient sums dZ in FP32 as it is staged.
+// The K loop is bound by LDS reads and MFMA issue alike (per K-step, CIB =
+// 32: 80 LDS against 288 MFMA cycles a wave, three waves a workgroup on four
+// SIMDs).  Four samples of 64x64x32: 50 us for 32 to 16 channels and 24 for 3
+// to 16, against 530 each with one workgroup per 2,048 voxels and tap reading
+// both operands from memory.
+//
+// LDS rows of X~: 24 values for x0 - 8 .. x0 + 15 plus the first two of the
+// next row for x0 + 16, x0 + 17; 36 rows (6 y, 6 z).  Channel strides of 436
+// and 132 words keep the 16-byte reads of 16 channels on distinct banks.
+constexpr int WX = 436, WZ = 132;   // words per channel
+
+struct WgradArgs {
+  Geo g;
+  const float* X;      // [batch][voxel][cs] (half-resolution grid when UP)
+  const float* dZ;     // [batch][voxel][co]
+  int cs, ci, co;      // channels of X in memory, of the gradient (padded), of dZ
+  int nwg;             // workgroups per (input, output) channel block
+  float* part;         // [nwg][27 * ci * co + co]
+};
+
+template <int CIB, int CSRC, bool UP>
+__global__ __launch_bounds__(192) void wgrad_kernel(WgradArgs p) {
+  constexpr int MB = CIB / 16, CQ = CSRC < 4 ? 1 : CIB / 4;   // channel quads staged
+  __shared__ __align__(16) unsigned xs[CIB * WX];
+  __shared__ __align__(16) unsigned zs[16 * WZ];
+  const Geo& g = p.g;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
+  const int ncog = p.co / 16;
+  const int ci0 = (blockIdx.y / ncog) * CIB, co0 = (blockIdx.y % ncog) * 16;
+  const int ntx = (g.nx + 15) / 16, nty = (g.ny + 3) / 4, ntz = (g.nz + 3) / 4;
+  const int ntile = ntx * nty * ntz * g.batch;
+  const int sx = UP ? g.nx >> 1 : g.nx, sy = UP ? g.ny >> 1 : g.ny, sz = UP ? g.nz >> 1 : g.nz;
+  if (CSRC < 4)   // channels past the source's stay zero
+    for (int q = tid; q < CIB * WX; q += 192) xs[q] = 0u;
+  f32x4 acc[3][3][MB];
 #pragma unroll
-  for (int m = 0; m < CI / 16; ++m)
+  for (int a = 0; a < 3; ++a)
 #pragma unroll
-    for (int n = 0; n < CO / 16; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = lane >> 4, i16 = lane & 15;
-  for (long vs = c0 + wave * 16; vs < c0 + WG_CHUNK && vs < total; vs += 64) {
-    bf16x4 a[CI / 16], bb[CO / 16];
+    for (int b = 0; b < 3; ++b)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const long gv = vs + 4 * kq + e;
-      const bool valid = gv < total;
-      const int b = valid ? (int)(gv / g.V) : 0;
-      const int v = valid ? (int)(gv - (long)b * g.V) : 0;
-      const int x = v % g.nx, yz = v / g.nx, y = yz % g.ny, z = yz / g.ny;
-      const int xx = x + dx, yy = y + dy, zz = z + dz;
-      const bool inb = valid && xx >= 0 && xx < g.nx && yy >= 0 && yy < g.ny && zz >= 0 && zz < g.nz;
-      long src;
-      if (UP)
-        src = (long)b * cV + (xx >> 1) + (long)cnx * ((yy >> 1) + (long)cny * (zz >> 1));
-      else
-        src = (long)b * g.V + xx + (long)g.nx * (yy + (long)g.ny * zz);
+      for (int m = 0; m < MB; ++m) acc[a][b][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float4 bsum = make_float4(0.f, 0.f, 0.f, 0.f);   // this thread's channel quad of dZ
+  for (int tile = blockIdx.x; tile < ntile; tile += p.nwg) {
+    const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = (tile / (ntx * nty)) % ntz, b = tile / (ntx * nty * ntz);
+    const int x0 = tx * 16, y0 = ty * 4, z0 = tz * 4;
+    const float* Xb = p.X + (long)b * sx * sy * sz * p.cs + ci0;
+    const float* Zb = p.dZ + (long)b * g.V * p.co + co0;
+    __syncthreads();   // the previous tile's reads are done
+    constexpr int NX = 36 * 10 * CQ, U = 5;
+    for (int q0 = 0; q0 < NX; q0 += U * 192) {
+      float4 lo[U], hi[U];
 #pragma unroll
-      for (int m = 0; m < CI / 16; ++m) a[m][e] = f2bf(inb ? X[src * CI + m * 16 + i16] : 0.f);
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + u * 192 + tid;
+        lo[u] = hi[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (q >= NX) continue;
+        const int c4 = (q % CQ) * 4, pr = q / CQ, row = pr / 10;
+        const int x = x0 + 2 * (pr % 10) - 2, y = y0 + row % 6 - 1, z = z0 + row / 6 - 1;
+        if (y < 0 || y >= g.ny || z < 0 || z >= g.nz) continue;
+        auto load = [&](int xx) {
+          const float* src =
+              UP ? Xb + ((long)(xx >> 1) + (long)sx * ((y >> 1) + (long)sy * (z >> 1))) * p.cs + c4
+                 : Xb + ((long)xx + (long)sx * (y + (long)sy * z)) * p.cs + c4;
+          if (CSRC < 4) return make_float4(src[0], src[1], src[2], 0.f);
+          return *(const float4*)src;
+        };
+        if (x >= 0 && x < g.nx) lo[u] = load(x);
+        if (x + 1 >= 0 && x + 1 < g.nx) hi[u] = UP ? lo[u] : load(x + 1);   // x is even
+      }
 #pragma unroll
-      for (int n = 0; n < CO / 16; ++n) bb[n][e] = f2bf(valid ? dZ[gv * CO + n * 16 + i16] : 0.f);
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + u * 192 + tid;
+        if (q >= NX) continue;
+        const int c4 = (q % CQ) * 4, pr = q / CQ;
+        unsigned* d = xs + c4 * WX + (pr / 10) * 12 + pr % 10 + 3;
+        d[0] = pack_bf16x2(lo[u].x, hi[u].x);
+        d[WX] = pack_bf16x2(lo[u].y, hi[u].y);
+        d[2 * WX] = pack_bf16x2(lo[u].z, hi[u].z);
+        if (CSRC >= 4) d[3 * WX] = pack_bf16x2(lo[u].w, hi[u].w);
+      }
     }
 #pragma unroll
-    for (int m = 0; m < CI / 16; ++m)
+    for (int u = 0; u < 3; ++u) {   // 16 rows of 8 pairs, 4 channel quads
+      const int q = u * 192 + tid;
+      if (q >= 512) continue;
+      const int c4 = (q & 3) * 4, pr = q >> 2, row = pr >> 3;
+      const int x = x0 + 2 * (pr & 7), y = y0 + (row & 3), z = z0 + (row >> 2);
+      float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+      if (y < g.ny && z < g.nz) {
+        const float* src = Zb + ((long)x + (long)g.nx * (y + (long)g.ny * z)) * p.co + c4;
+        if (x < g.nx) lo = *(const float4*)src;
+        if (x + 1 < g.nx) hi = *(const float4*)(src + p.co);
+      }
+      bsum.x += lo.x + hi.x;
+      bsum.y += lo.y + hi.y;
+      bsum.z += lo.z + hi.z;
+      bsum.w += lo.w + hi.w;
+      unsigned* d = zs + c4 * WZ + row * 8 + (pr & 7);
+      d[0] = pack_bf16x2(lo.x, hi.x);
+      d[WZ] = pack_bf16x2(lo.y, hi.y);
+      d[2 * WZ] = pack_bf16x2(lo.z, hi.z);
+      d[3 * WZ] = pack_bf16x2(lo.w, hi.w);
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int ks = 0; ks < 8; ++ks) {
+      const int z = ks >> 1, y = (ks & 1) * 2 + (kq >> 1), xh = kq & 1;
+      const bf16x8 bz = __builtin_bit_cast(bf16x8, *(const uint4*)(zs + i16 * WZ + (z * 4 + y) * 8 + xh * 4));
 #pragma unroll
-      for (int n = 0; n < CO / 16; ++n)
-        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[m], bb[n], acc[m][n], 0, 0, 0);
+      for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+          const unsigned* r = xs + (m * 16 + i16) * WX + ((z + wave) * 6 + y + dy) * 12 + 4 + xh * 4;
+          const uint4 c = *(const uint4*)r;
+          const unsigned l = r[-1], t = r[4];
+          const unsigned s1 = __builtin_amdgcn_alignbit(c.y, c.x, 16), s2 = __builtin_amdgcn_alignbit(c.z, c.y, 16),
+                         s3 = __builtin_amdgcn_alignbit(c.w, c.z, 16);
+          const uint4 am = make_uint4(__builtin_amdgcn_alignbit(c.x, l, 16), s1, s2, s3);
+          const uint4 ap = make_uint4(s1, s2, s3, __builtin_amdgcn_alignbit(t, c.w, 16));
+          acc[dy][0][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, am), bz, acc[dy][0][m], 0, 0, 0);
+          acc[dy][1][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c), bz, acc[dy][1][m], 0, 0, 0);
+          acc[dy][2][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ap), bz, acc[dy][2][m], 0, 0, 0);
+        }
+    }
   }
-  // C tile element (ci = m*16 + 4*kq + e, co = n*16 + i16)
+  // C element (row 4 * kq + e, column i16): input channel, output channel
+  const size_t per = (size_t)27 * p.ci * p.co;
+  float* out = p.part + (size_t)blockIdx.x * (per + p.co);
 #pragma unroll
-  for (int m = 0; m < CI / 16; ++m)
+  for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-    for (int n = 0; n < CO / 16; ++n)
+    for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[wave][(m * 16 + 4 * kq + e) * CO + n * 16 + i16] = acc[m][n][e];
-  __syncthreads();
-  float* out = part + ((size_t)blockIdx.x * 27 + t) * CI * CO;
-  for (int q = threadIdx.x; q < CI * CO; q += 256) out[q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
-}
-
-// dW[t][ci][co] (only the real input channels) = sum over chunks, in order.
-__global__ void wgrad_reduce_kernel(int nchunk, int ci_pad, int ci_real, int co, const float* __restrict__ part,
-                                    float* __restrict__ dW) {
-  int q = blockIdx.x * blockDim.x + threadIdx.x;
-  int per = 27 * ci_real * co;
-  if (q >= per) return;
-  int t = q / (ci_real * co), r = q % (ci_real * co);
-  int ci = r / co, c = r % co;
-  size_t src = ((size_t)t * ci_pad + ci) * co + c;
-  float s = 0.f;
-  for (int k = 0; k < nchunk; ++k) s += part[(size_t)k * 27 * ci_pad * co + src];
-  dW[q] = s;
-}
-
-// Column sums sum_v T[v][c] for the bias gradient: per-block partials.
-__global__ void colsum_partial_kernel(long nvox, int C, const float* __restrict__ T, float* __restrict__ part) {
-  __shared__ float sh[256];
-  const int c = threadIdx.x % C, grp = threadIdx.x / C, ngrp = 256 / C;
-  const long per = (nvox + gridDim.x - 1) / gridDim.x;
-  const long beg = (long)blockIdx.x * per, end = beg + per < nvox ? beg + per : nvox;
-  float s = 0.f;
-  if (grp < ngrp)
-    for (long v = beg + grp; v < end; v += ngrp) s += T[v * C + c];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < C) {
-    float tot = 0.f;
-    for (int q = 0; q < ngrp; ++q) tot += sh[q * C + threadIdx.x];
-    part[(size_t)blockIdx.x * C + threadIdx.x] = tot;
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          out[((size_t)(wave * 9 + dy * 3 + dx) * p.ci + ci0 + m * 16 + 4 * kq + e) * p.co + co0 + i16] =
+              acc[dy][dx][m][e];
+  if (ci0 == 0) {
+    __syncthreads();
+    float* sh = (float*)zs;   // [48][16]
+    *(float4*)(sh + 4 * tid) = bsum;
+    __syncthreads();
+    if (tid < 16) {
+      float t = 0.f;
+      for (int q = 0; q < 48; ++q) t += sh[q * 16 + tid];
+      out[per + co0 + tid] = t;
+    }
   }
 }
 
-__global__ void colsum_final_kernel(int nblk, int C, const float* __restrict__ part, float* __restrict__ out) {
-  int c = threadIdx.x;
-  if (c >= C) return;
+// The gradient of one convolution's parameters (weights of its real input
+// channels, then biases), or any rows of `width` partial sums: out[q] = sum
+// over the n partials of column src(q), 32 columns a block, eight rows of
+// threads taking every eighth partial; fixed order.
+__global__ __launch_bounds__(256) void partial_sum_kernel(int n, size_t width, const float* __restrict__ part,
+                                                          int nout, int ci_pad, int ci_real, int co,
+                                                          float* __restrict__ out) {
+  __shared__ float sh[8][32];
+  const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
+  const int q = blockIdx.x * 32 + lane;
   float s = 0.f;
-  for (int k = 0; k < nblk; ++k) s += part[(size_t)k * C + c];
-  out[c] = s;
+  if (q < nout) {
+    size_t src = q;
+    if (ci_pad) {   // out [27][ci_real][co], co; part [27][ci_pad][co], co
+      const int per = ci_real * co, t = q / per;
+      src = t < 27 ? (size_t)t * ci_pad * co + q % per : (size_t)27 * ci_pad * co + (q - 27 * per);
+    }
+#pragma unroll 8
+    for (int k = row; k < n; k += 8) s += part[(size_t)k * width + src];
+  }
+  sh[row][lane] = s;
+  __syncthreads();
+  if (row == 0 && q < nout) {
+    float t = 0.f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) t += sh[r][lane];
+    out[q] = t;
+  }
 }
 
 // ------------------------------------------------------------ elementwise
@@ -528,52 +625,66 @@ __global__ void pool_kernel(Geo g, int C, const float* __restrict__ X, float* __
   out[q] = s * 0.125f;
 }
 
-// Fine-grid gradient += (coarse gradient of the pooled tensor) / 8.
-__global__ void pool_bwd_kernel(Geo fine, int C, const float* __restrict__ dP, float* __restrict__ dX) {
-  long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  long total = (long)fine.batch * fine.V * C;
-  if (q >= total) return;
-  int c = (int)(q % C);
-  long bv = q / C;
-  int b = (int)(bv / fine.V), v = (int)(bv % fine.V);
-  int x = v % fine.nx, yz = v / fine.nx, y = yz % fine.ny, z = yz / fine.ny;
-  int cnx = fine.nx / 2, cny = fine.ny / 2, cV = fine.V / 8;
-  dX[q] += dP[((long)b * cV + (x >> 1) + (long)cnx * ((y >> 1) + (long)cny * (z >> 1))) * C + c] * 0.125f;
+// The backward elementwise passes take four channels a thread and write the
+// gradient behind the ReLU, dZ = G (a > 0), as they form G, so that no pass
+// reads G back only to mask it.
+__device__ inline float4 relu_mask(float4 g, float4 a) {
+  return make_float4(a.x > 0.f ? g.x : 0.f, a.y > 0.f ? g.y : 0.f, a.z > 0.f ? g.z : 0.f, a.w > 0.f ? g.w : 0.f);
 }
 
-// Coarse gradient of an upsampled tensor: sum of its 8 children (g coarse).
-// accumulate: out += sum, else out = sum.
-__global__ void up_bwd_kernel(Geo g, int C, const float* __restrict__ dU, float* __restrict__ out, int accumulate) {
-  long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  long total = (long)g.batch * g.V * C;
-  if (q >= total) return;
-  int c = (int)(q % C);
-  long bv = q / C;
-  int b = (int)(bv / g.V), v = (int)(bv % g.V);
-  int x = v % g.nx, yz = v / g.nx, y = yz % g.ny, z = yz / g.ny;
-  int fx = 2 * g.nx, fy = 2 * g.ny, fV = 8 * g.V;
-  float s = 0.f;
-  for (int k = 0; k < 2; ++k)
-    for (int j = 0; j < 2; ++j)
-      for (int i = 0; i < 2; ++i)
-        s += dU[((long)b * fV + (2 * x + i) + (long)fx * ((2 * y + j) + (long)fy * (2 * z + k))) * C + c];
-  out[q] = accumulate ? out[q] + s : s;
+// Encoder gradient G = dX + (coarse gradient of the pooled tensor) / 8,
+// masked by the activation a.  dX given, or (level 0) dy wo of the head.
+template <int C, bool HEAD>
+__global__ __launch_bounds__(256) void pool_bwd_kernel(Geo fine, const float* __restrict__ dP,
+                                                       const float* __restrict__ dX, const float* __restrict__ wb,
+                                                       const float* __restrict__ a, float* __restrict__ dZ) {
+  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= (long)fine.batch * fine.V * (C / 4)) return;
+  const int c4 = (int)(q % (C / 4)) * 4;
+  const long bv = q / (C / 4);
+  const int b = (int)(bv / fine.V), v = (int)(bv - (long)b * fine.V);
+  const int x = v % fine.nx, yz = v / fine.nx, y = yz % fine.ny, z = yz / fine.ny;
+  const int cnx = fine.nx / 2, cny = fine.ny / 2, cV = fine.V / 8;
+  const float4 d =
+      *(const float4*)(dP + ((long)b * cV + (x >> 1) + (long)cnx * ((y >> 1) + (long)cny * (z >> 1))) * C + c4);
+  float4 g;
+  if (HEAD) {
+    const float h = dX[bv];
+    g = make_float4(h * wb[c4], h * wb[c4 + 1], h * wb[c4 + 2], h * wb[c4 + 3]);
+  } else {
+    g = *(const float4*)(dX + bv * C + c4);
+  }
+  g.x += d.x * 0.125f;
+  g.y += d.y * 0.125f;
+  g.z += d.z * 0.125f;
+  g.w += d.w * 0.125f;
+  *(float4*)(dZ + bv * C + c4) = relu_mask(g, *(const float4*)(a + bv * C + c4));
 }
 
-// out = g * (a > 0)
-__global__ void relu_mask_kernel(long n, const float* __restrict__ gr, const float* __restrict__ a,
-                                 float* __restrict__ out) {
-  long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) out[q] = a[q] > 0.f ? gr[q] : 0.f;
-}
-
-// Input features [b][v][3] -> padded [b][v][16].
-__global__ void pad_input_kernel(long nvox, const float* __restrict__ x3, float* __restrict__ x16) {
-  long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nvox * 16) return;
-  long v = q / 16;
-  int c = (int)(q % 16);
-  x16[q] = c < 3 ? x3[v * 3 + c] : 0.f;
+// Coarse gradient G of an upsampled tensor: sum of its 8 children (g
+// coarse), stored in out when given and masked by a in dZ.
+template <int C>
+__global__ __launch_bounds__(256) void up_bwd_kernel(Geo g, const float* __restrict__ dU, const float* __restrict__ a,
+                                                     float* __restrict__ out, float* __restrict__ dZ) {
+  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= (long)g.batch * g.V * (C / 4)) return;
+  const int c4 = (int)(q % (C / 4)) * 4;
+  const long bv = q / (C / 4);
+  const int b = (int)(bv / g.V), v = (int)(bv - (long)b * g.V);
+  const int x = v % g.nx, yz = v / g.nx, y = yz % g.ny, z = yz / g.ny;
+  const int fx = 2 * g.nx, fy = 2 * g.ny, fV = 8 * g.V;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float4 d = *(const float4*)(
+        dU + ((long)b * fV + (2 * x + (e & 1)) + (long)fx * ((2 * y + ((e >> 1) & 1)) + (long)fy * (2 * z + (e >> 2)))) * C + c4);
+    s.x += d.x;
+    s.y += d.y;
+    s.z += d.z;
+    s.w += d.w;
+  }
+  if (out) *(float4*)(out + bv * C + c4) = s;
+  *(float4*)(dZ + bv * C + c4) = relu_mask(s, *(const float4*)(a + bv * C + c4));
 }
 
 // Head: y[v] = sum_c d0[v][c] wo[c] + bo.
@@ -587,18 +698,37 @@ __global__ void head_fwd_kernel(long nvox, const float* __restrict__ d0, const f
   y[v] = s + wb[16];
 }
 
-// dd0[v][c] = dy[v] wo[c]; the head-weight products d0*dy for their sums.
-__global__ void head_bwd_kernel(long nvox, const float* __restrict__ d0, const float* __restrict__ dy,
-                                const float* __restrict__ wb, float* __restrict__ dd0, float* __restrict__ prod) {
-  long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nvox * 17) return;
-  long v = q / 17;
-  int c = (int)(q % 17);
-  if (c < 16) {
-    dd0[v * 16 + c] = dy[v] * wb[c];
-    prod[v * 17 + c] = d0[v * 16 + c] * dy[v];
-  } else {
-    prod[v * 17 + 16] = dy[v];
+// Head backward: dZ[v][c] = dy[v] wo[c] (a6 > 0), and per block the partial
+// sums of the head's own gradient, d0[v][c] dy[v] and dy[v].
+constexpr int HEAD_BLOCKS = 512;
+__global__ __launch_bounds__(256) void head_bwd_kernel(long nvox, const float* __restrict__ d0,
+                                                       const float* __restrict__ dy, const float* __restrict__ wb,
+                                                       const float* __restrict__ a6, float* __restrict__ dZ,
+                                                       float* __restrict__ part) {
+  __shared__ float sh[256][5];
+  const int c4 = (threadIdx.x & 3) * 4;
+  const float4 w = make_float4(wb[c4], wb[c4 + 1], wb[c4 + 2], wb[c4 + 3]);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  float sy = 0.f;
+  for (long v = (long)blockIdx.x * 64 + (threadIdx.x >> 2); v < nvox; v += (long)gridDim.x * 64) {
+    const float h = dy[v];
+    const float4 d = *(const float4*)(d0 + v * 16 + c4);
+    *(float4*)(dZ + v * 16 + c4) =
+        relu_mask(make_float4(h * w.x, h * w.y, h * w.z, h * w.w), *(const float4*)(a6 + v * 16 + c4));
+    s.x += d.x * h;
+    s.y += d.y * h;
+    s.z += d.z * h;
+    s.w += d.w * h;
+    sy += h;
+  }
+  float* r = sh[threadIdx.x];
+  r[0] = s.x; r[1] = s.y; r[2] = s.z; r[3] = s.w; r[4] = sy;
+  __syncthreads();
+  if (threadIdx.x < 17) {
+    const int c = threadIdx.x;
+    float t = 0.f;
+    for (int q = 0; q < 64; ++q) t += c < 16 ? sh[4 * q + (c >> 2)][c & 3] : sh[4 * q][4];
+    part[(size_t)blockIdx.x * 17 + c] = t;
   }
 }
 
@@ -748,13 +878,13 @@ struct cpr_nn {
   bf16x8* wf[NCONV] = {};
   bf16x8* wb[NCONV] = {};
   // activations
-  float *x16 = nullptr, *e0 = nullptr, *p1 = nullptr, *e1 = nullptr, *p2 = nullptr, *e2 = nullptr;
+  float *x3 = nullptr, *e0 = nullptr, *p1 = nullptr, *e1 = nullptr, *p2 = nullptr, *e2 = nullptr;
   float *p3 = nullptr, *e3 = nullptr, *a4 = nullptr, *d2 = nullptr, *a5 = nullptr, *d1 = nullptr;
   float *a6 = nullptr, *d0 = nullptr, *y = nullptr;
   // gradients
-  float *dy = nullptr, *g0 = nullptr, *g0b = nullptr, *gu0 = nullptr, *g1 = nullptr, *g1b = nullptr;
-  float *gu1 = nullptr, *g2 = nullptr, *g2b = nullptr, *gu2 = nullptr, *g3 = nullptr, *g3b = nullptr;
-  float *gp = nullptr, *prod = nullptr, *part = nullptr, *lpart = nullptr, *loss = nullptr;
+  float *dy = nullptr, *g0b = nullptr, *gu0 = nullptr, *g1 = nullptr, *g1b = nullptr;
+  float *gu1 = nullptr, *g2 = nullptr, *g2b = nullptr, *gu2 = nullptr, *g3b = nullptr;
+  float *part = nullptr, *lpart = nullptr, *loss = nullptr;
   size_t part_cap = 0;
   int cur_batch = 0;
   long adam_step = 0;
@@ -857,19 +987,28 @@ static void conv(cpr_nn* nn, ConvArgs a) {
   }
 }
 
-template <int CI, int CO, bool UP>
+// Workgroups per channel block of a weight gradient: at most one per tile,
+// WG_MAX over all blocks (two per CU: 64 KB of LDS each; more would only add
+// partial sums, 55 KB apiece, to the reduction).
+static int wgrad_wgs(const Geo& g, int ci_pad, int co) {
+  const int cib = ci_pad < 32 ? ci_pad : 32, blocks = (ci_pad / cib) * (co / 16);
+  const int tiles = div_up(g.nx, 16) * div_up(g.ny, 4) * div_up(g.nz, 4) * g.batch;
+  return std::min(tiles, WG_MAX / blocks);
+}
+
+// Gradient of convolution k's parameters from its input X and dZ.
+template <int CI, int CSRC, int CO, bool UP>
 static void wgrad(cpr_nn* nn, Geo g, const float* X, const float* dZ, int k) {
-  long total = (long)g.batch * g.V;
-  int nchunk = div_up(total, WG_CHUNK);
-  dim3 grid(nchunk, 27);
-  wgrad_kernel<CI, CO, UP><<<grid, 256, 0, nn->stream>>>(g, X, dZ, nn->part);
-  int per = 27 * CIN[k] * CO;
-  wgrad_reduce_kernel<<<div_up(per, 256), 256, 0, nn->stream>>>(nchunk, CI, CIN[k], CO, nn->part,
-                                                               nn->grad + nn->off[k]);
-  // bias gradient
-  int nb = (int)std::min<long>(256, div_up(total, 256));
-  colsum_partial_kernel<<<nb, 256, 0, nn->stream>>>(total, CO, dZ, nn->gp);
-  colsum_final_kernel<<<1, 64, 0, nn->stream>>>(nb, CO, nn->gp, nn->grad + nn->off[k] + 27L * CIN[k] * CO);
+  constexpr int CIB = CI < 32 ? CI : 32;
+  WgradArgs a;
+  a.g = g; a.X = X; a.dZ = dZ;
+  a.cs = CSRC; a.ci = CI; a.co = CO;
+  a.nwg = wgrad_wgs(g, CI, CO);
+  a.part = nn->part;
+  wgrad_kernel<CIB, CSRC, UP><<<dim3(a.nwg, (CI / CIB) * (CO / 16)), 192, 0, nn->stream>>>(a);
+  const int nout = 27 * CSRC * CO + CO;
+  partial_sum_kernel<<<div_up(nout, 32), 256, 0, nn->stream>>>(a.nwg, (size_t)27 * CI * CO + CO, nn->part, nout, CI,
+                                                             CSRC, CO, nn->grad + nn->off[k]);
 }
 
 // x3: input features [B][voxel][3].  train: keep what the backward pass
@@ -916,42 +1055,32 @@ static int nn_backward_impl(cpr_nn* nn) {
       L3 = with_batch(nn->lv[3], B);
   hipStream_t s = nn->stream;
   long n0 = (long)B * L0.V, n1 = (long)B * L1.V, n2 = (long)B * L2.V, n3 = (long)B * L3.V;
-  // head
-  head_bwd_kernel<<<div_up(n0 * 17, 256), 256, 0, s>>>(n0, nn->d0, nn->dy, nn->theta + nn->off[NCONV], nn->g0,
-                                                       nn->prod);
-  {
-    int nb = (int)std::min<long>(256, div_up(n0, 256));
-    colsum_partial_kernel<<<nb, 255, 0, s>>>(n0, 17, nn->prod, nn->gp);
-    colsum_final_kernel<<<1, 64, 0, s>>>(nb, 17, nn->gp, nn->grad + nn->off[NCONV]);
-  }
-  // level 0 decoder: d0 = a6 + e0; dz6 = dd0 * (a6 > 0); g0 keeps de0 = dd0
-  relu_mask_kernel<<<div_up(n0 * 16, 256), 256, 0, s>>>(n0 * 16, nn->g0, nn->a6, nn->g0b);
-  wgrad<32, 16, true>(nn, L0, nn->d1, nn->g0b, 6);
+  const float* head = nn->theta + nn->off[NCONV];
+  auto quads = [](long nvox, int c) { return div_up(nvox * (c / 4), 256); };
+  // head and level 0 decoder: d0 = a6 + e0, so dd0 = dy wo reaches a6 and e0
+  const int hb = (int)std::min<long>(HEAD_BLOCKS, div_up(n0, 64));
+  head_bwd_kernel<<<hb, 256, 0, s>>>(n0, nn->d0, nn->dy, head, nn->a6, nn->g0b, nn->part);
+  partial_sum_kernel<<<1, 256, 0, s>>>(hb, 17, nn->part, 17, 0, 0, 0, nn->grad + nn->off[NCONV]);
+  wgrad<32, 32, 16, true>(nn, L0, nn->d1, nn->g0b, 6);
   conv<16, 16, 32, false, 0>(nn, cargs(L0, nn->g0b, nn->wb[6], nullptr, nullptr, nn->gu0, nullptr));
-  up_bwd_kernel<<<div_up(n1 * 32, 256), 256, 0, s>>>(L1, 32, nn->gu0, nn->g1, 0);      // dd1 = de1
-  relu_mask_kernel<<<div_up(n1 * 32, 256), 256, 0, s>>>(n1 * 32, nn->g1, nn->a5, nn->g1b);
-  wgrad<64, 32, true>(nn, L1, nn->d2, nn->g1b, 5);
+  up_bwd_kernel<32><<<quads(n1, 32), 256, 0, s>>>(L1, nn->gu0, nn->a5, nn->g1, nn->g1b);      // dd1 = de1
+  wgrad<64, 64, 32, true>(nn, L1, nn->d2, nn->g1b, 5);
   conv<32, 32, 64, false, 0>(nn, cargs(L1, nn->g1b, nn->wb[5], nullptr, nullptr, nn->gu1, nullptr));
-  up_bwd_kernel<<<div_up(n2 * 64, 256), 256, 0, s>>>(L2, 64, nn->gu1, nn->g2, 0);      // dd2 = de2
-  relu_mask_kernel<<<div_up(n2 * 64, 256), 256, 0, s>>>(n2 * 64, nn->g2, nn->a4, nn->g2b);
-  wgrad<64, 64, true>(nn, L2, nn->e3, nn->g2b, 4);
+  up_bwd_kernel<64><<<quads(n2, 64), 256, 0, s>>>(L2, nn->gu1, nn->a4, nn->g2, nn->g2b);      // dd2 = de2
+  wgrad<64, 64, 64, true>(nn, L2, nn->e3, nn->g2b, 4);
   conv<64, 64, 64, false, 0>(nn, cargs(L2, nn->g2b, nn->wb[4], nullptr, nullptr, nn->gu2, nullptr));
-  up_bwd_kernel<<<div_up(n3 * 64, 256), 256, 0, s>>>(L3, 64, nn->gu2, nn->g3, 0);      // de3
-  // encoder
-  relu_mask_kernel<<<div_up(n3 * 64, 256), 256, 0, s>>>(n3 * 64, nn->g3, nn->e3, nn->g3b);
-  wgrad<64, 64, false>(nn, L3, nn->p3, nn->g3b, 3);
+  // encoder: de3, then de2, de1, de0 with the pooled tensors' gradients
+  up_bwd_kernel<64><<<quads(n3, 64), 256, 0, s>>>(L3, nn->gu2, nn->e3, nullptr, nn->g3b);
+  wgrad<64, 64, 64, false>(nn, L3, nn->p3, nn->g3b, 3);
   conv<64, 64, 64, false, 0>(nn, cargs(L3, nn->g3b, nn->wb[3], nullptr, nullptr, nn->gu2, nullptr));  // dp3 (L3)
-  pool_bwd_kernel<<<div_up(n2 * 64, 256), 256, 0, s>>>(L2, 64, nn->gu2, nn->g2);          // de2 += pool'(dp3)
-  relu_mask_kernel<<<div_up(n2 * 64, 256), 256, 0, s>>>(n2 * 64, nn->g2, nn->e2, nn->g2b);
-  wgrad<32, 64, false>(nn, L2, nn->p2, nn->g2b, 2);
+  pool_bwd_kernel<64, false><<<quads(n2, 64), 256, 0, s>>>(L2, nn->gu2, nn->g2, nullptr, nn->e2, nn->g2b);
+  wgrad<32, 32, 64, false>(nn, L2, nn->p2, nn->g2b, 2);
   conv<64, 64, 32, false, 0>(nn, cargs(L2, nn->g2b, nn->wb[2], nullptr, nullptr, nn->gu1, nullptr));  // dp2 (L2, 32)
-  pool_bwd_kernel<<<div_up(n1 * 32, 256), 256, 0, s>>>(L1, 32, nn->gu1, nn->g1);          // de1 += pool'(dp2)
-  relu_mask_kernel<<<div_up(n1 * 32, 256), 256, 0, s>>>(n1 * 32, nn->g1, nn->e1, nn->g1b);
-  wgrad<16, 32, false>(nn, L1, nn->p1, nn->g1b, 1);
+  pool_bwd_kernel<32, false><<<quads(n1, 32), 256, 0, s>>>(L1, nn->gu1, nn->g1, nullptr, nn->e1, nn->g1b);
+  wgrad<16, 16, 32, false>(nn, L1, nn->p1, nn->g1b, 1);
   conv<32, 32, 16, false, 0>(nn, cargs(L1, nn->g1b, nn->wb[1], nullptr, nullptr, nn->gu0, nullptr));  // dp1 (L1, 16)
-  pool_bwd_kernel<<<div_up(n0 * 16, 256), 256, 0, s>>>(L0, 16, nn->gu0, nn->g0);          // de0 += pool'(dp1)
-  relu_mask_kernel<<<div_up(n0 * 16, 256), 256, 0, s>>>(n0 * 16, nn->g0, nn->e0, nn->g0b);
-  wgrad<16, 16, false>(nn, L0, nn->x16, nn->g0b, 0);
+  pool_bwd_kernel<16, true><<<quads(n0, 16), 256, 0, s>>>(L0, nn->gu0, nn->dy, head, nn->e0, nn->g0b);
+  wgrad<16, 3, 16, false>(nn, L0, nn->x3, nn->g0b, 0);
   NN_TRY(hipGetLastError());
   return CPR_OK;
 }
@@ -968,35 +1097,33 @@ static int nn_alloc(cpr_nn* nn) {
     NN_TRY(dev_malloc(nn->mem, (void**)&nn->wf[k], fwd_frags(k) * sizeof(bf16x8)));
     NN_TRY(dev_malloc(nn->mem, (void**)&nn->wb[k], bwd_frags(k) * sizeof(bf16x8)));
   }
-  NN_TRY(A(&nn->x16, n[0] * 16)); NN_TRY(A(&nn->e0, n[0] * 16)); NN_TRY(A(&nn->p1, n[1] * 16));
+  NN_TRY(A(&nn->x3, n[0] * 3)); NN_TRY(A(&nn->e0, n[0] * 16)); NN_TRY(A(&nn->p1, n[1] * 16));
   NN_TRY(A(&nn->e1, n[1] * 32)); NN_TRY(A(&nn->p2, n[2] * 32)); NN_TRY(A(&nn->e2, n[2] * 64));
   NN_TRY(A(&nn->p3, n[3] * 64)); NN_TRY(A(&nn->e3, n[3] * 64)); NN_TRY(A(&nn->a4, n[2] * 64));
   NN_TRY(A(&nn->d2, n[2] * 64)); NN_TRY(A(&nn->a5, n[1] * 32)); NN_TRY(A(&nn->d1, n[1] * 32));
   NN_TRY(A(&nn->a6, n[0] * 16)); NN_TRY(A(&nn->d0, n[0] * 16)); NN_TRY(A(&nn->y, n[0]));
-  NN_TRY(A(&nn->dy, n[0])); NN_TRY(A(&nn->g0, n[0] * 16)); NN_TRY(A(&nn->g0b, n[0] * 16));
+  NN_TRY(A(&nn->dy, n[0])); NN_TRY(A(&nn->g0b, n[0] * 16));
   NN_TRY(A(&nn->gu0, n[0] * 32)); NN_TRY(A(&nn->g1, n[1] * 32)); NN_TRY(A(&nn->g1b, n[1] * 32));
   NN_TRY(A(&nn->gu1, n[1] * 64)); NN_TRY(A(&nn->g2, n[2] * 64)); NN_TRY(A(&nn->g2b, n[2] * 64));
-  NN_TRY(A(&nn->gu2, n[2] * 64)); NN_TRY(A(&nn->g3, n[3] * 64)); NN_TRY(A(&nn->g3b, n[3] * 64));
-  NN_TRY(A(&nn->gp, 256L * 64)); NN_TRY(A(&nn->prod, n[0] * 17));
-  size_t pc = 0;
+  NN_TRY(A(&nn->gu2, n[2] * 64)); NN_TRY(A(&nn->g3b, n[3] * 64));
+  size_t pc = HEAD_BLOCKS * 17;   // partial sums of the head's, then of each convolution's gradient
   for (int k = 0; k < NCONV; ++k) {
     int l = (k <= 3) ? k : 6 - k;   // resolution level of conv k's output
-    size_t c = (size_t)div_up(n[l], WG_CHUNK) * 27 * CIN_PAD[k] * COUT[k];
+    size_t c = (size_t)wgrad_wgs(nn->lv[l], CIN_PAD[k], COUT[k]) * (27 * CIN_PAD[k] * COUT[k] + COUT[k]);
     pc = std::max(pc, c);
   }
   nn->part_cap = pc;
   NN_TRY(A(&nn->part, (long)pc));
   NN_TRY(A(&nn->lpart, 3L * B * 64));
   NN_TRY(A(&nn->loss, 1));
-  NN_TRY(hipMemsetAsync(nn->x16, 0, n[0] * 16 * sizeof(float), nn->stream));
   return CPR_OK;
 }
 
 static void nn_free(cpr_nn* nn) {
-  float* fs[] = {nn->theta, nn->m, nn->vv, nn->grad, nn->x16, nn->e0, nn->p1, nn->e1, nn->p2, nn->e2, nn->p3,
-                 nn->e3, nn->a4, nn->d2, nn->a5, nn->d1, nn->a6, nn->d0, nn->y, nn->dy, nn->g0, nn->g0b,
-                 nn->gu0, nn->g1, nn->g1b, nn->gu1, nn->g2, nn->g2b, nn->gu2, nn->g3, nn->g3b, nn->gp,
-                 nn->prod, nn->part, nn->lpart, nn->loss};
+  float* fs[] = {nn->theta, nn->m, nn->vv, nn->grad, nn->x3, nn->e0, nn->p1, nn->e1, nn->p2, nn->e2, nn->p3,
+                 nn->e3, nn->a4, nn->d2, nn->a5, nn->d1, nn->a6, nn->d0, nn->y, nn->dy, nn->g0b,
+                 nn->gu0, nn->g1, nn->g1b, nn->gu1, nn->g2, nn->g2b, nn->gu2, nn->g3b,
+                 nn->part, nn->lpart, nn->loss};
   for (float* p : fs) dev_free(nn->mem, p);
   for (int k = 0; k < NCONV; ++k) {
     dev_free(nn->mem, nn->wf[k]);
@@ -1112,7 +1239,8 @@ int cpr_nn_forward(cpr_nn_t* nn, const float* x, int batch, float* y) {
   if (batch < 1 || batch > nn->max_batch) return nn_err(nn, CPR_EINVAL, "batch out of range");
   if (!nn->frags_valid) return nn_err(nn, CPR_EINVAL, "parameters not set");
   long n0 = (long)batch * nn->lv[0].V;
-  pad_input_kernel<<<div_up(n0 * 16, 256), 256, 0, nn->stream>>>(n0, x, nn->x16);   // for the weight gradient
+  // for the weight gradient, which may run after the caller has changed x
+  NN_TRY(hipMemcpyAsync(nn->x3, x, n0 * 3 * sizeof(float), hipMemcpyDeviceToDevice, nn->stream));
   int rc = nn_forward_impl(nn, x, batch, true);
   if (rc) return rc;
   NN_TRY(hipMemcpyAsync(y, nn->y, n0 * sizeof(float), hipMemcpyDeviceToDevice, nn->stream));
@@ -1168,7 +1296,7 @@ int cpr_nn_train_step(cpr_nn_t* nn, const float* x, const float* t, int batch, f
   hipStream_t s = nn->stream;
   const int V = nn->lv[0].V;
   long n0 = (long)batch * V;
-  pad_input_kernel<<<div_up(n0 * 16, 256), 256, 0, s>>>(n0, x, nn->x16);   // for the weight gradient
+  NN_TRY(hipMemcpyAsync(nn->x3, x, n0 * 3 * sizeof(float), hipMemcpyDeviceToDevice, s));   // for the weight gradient
   int rc = nn_forward_impl(nn, x, batch, true);
   if (rc) return rc;
   const int per = 64;
