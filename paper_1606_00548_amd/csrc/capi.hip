@@ -40,7 +40,7 @@ int dalloc(cpr_ctx* ctx, T** p, size_t count) {
 
 void free_all(cpr_ctx* ctx) {
   release_hierarchy(ctx);
-  void* bufs[] = {ctx->poro, ctx->tp, ctx->perfs_d, ctx->J, ctx->props, ctx->vin, ctx->vin2, ctx->vout,
+  void* bufs[] = {ctx->poro, ctx->tp, ctx->perfs_d, ctx->J, ctx->lt, ctx->vin, ctx->vin2, ctx->vout,
                   ctx->w, ctx->R0, ctx->Dinv, ctx->Jf, ctx->Dinvf, ctx->flag, ctx->V, ctx->Z,
                   ctx->Y, ctx->rp, ctx->xs, ctx->rs, ctx->tmp, ctx->vf, ctx->zf, ctx->Yf, ctx->rpf,
                   ctx->part, ctx->hdev, ctx->lnk, ctx->rprime, ctx->qbuf, ctx->feat, ctx->nnscal,
@@ -109,6 +109,9 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
       for (int q = 0; q < f->n_pvt; ++q) fl.pvt[r][q] = f->pvt[(size_t)r * f->n_pvt + q];
     for (int q = 0; q + 1 < f->n_pvt; ++q)
       if (!(fl.pvt[0][q + 1] > fl.pvt[0][q])) return set_err(ctx, CPR_EINVAL, "PVT pressures must increase");
+    for (int r = 0; r < 6; ++r)
+      for (int q = 0; q + 1 < f->n_pvt; ++q)
+        fl.slope[r][q] = (fl.pvt[r][q + 1] - fl.pvt[r][q]) / (fl.pvt[0][q + 1] - fl.pvt[0][q]);
   }
   ctx->lay = make_lay(g->nx, g->ny, g->nz, true);
   const int b = ctx->b;
@@ -129,7 +132,7 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
   ALLOC(ctx->poro, N);
   ALLOC(ctx->tp, 3 * N);
   ALLOC(ctx->J, tiled_len(N, 7 * b * b));
-  ALLOC(ctx->props, (size_t)props_planes(f->model) * N);
+  ALLOC(ctx->lt, N);
   ALLOC(ctx->vin, NV);
   ALLOC(ctx->vin2, NV);
   ALLOC(ctx->vout, NV);
@@ -434,10 +437,18 @@ int assemble_jacobian(cpr_ctx_t* ctx, const double* x_old, const double* x, doub
   if (!(dt_days > 0) || !std::isfinite(dt_days)) return set_err(ctx, CPR_EINVAL, "dt must be > 0");
   TraceRange tr("assemble_jacobian");
   ph_outer_begin(ctx, PH_ASSEMBLE);
-  CPR_TRY(vec_nat_to_cs(ctx, x_old, ctx->vin2));
-  CPR_TRY(vec_nat_to_cs(ctx, x, ctx->vin));
-  launch_assemble(ctx, ctx->vin2, ctx->vin, dt_days, ctx->vout);
-  CPR_TRY(vec_cs_to_nat(ctx, ctx->vout, rhs_out));
+  const long len = vec_len(ctx);
+  auto apart = [len](const double* a, const double* b) { return a + len <= b || b + len <= a; };
+  if (apart(x_old, rhs_out) && apart(x, rhs_out)) {
+    const int rc = launch_assemble(ctx, x_old, x, dt_days, rhs_out, true);
+    if (rc != CPR_OK) return rc;
+  } else {   // the residual replaces a state: from copies
+    CPR_TRY(vec_nat_to_cs(ctx, x_old, ctx->vin2));
+    CPR_TRY(vec_nat_to_cs(ctx, x, ctx->vin));
+    const int rc = launch_assemble(ctx, ctx->vin2, ctx->vin, dt_days, ctx->vout, false);
+    if (rc != CPR_OK) return rc;
+    CPR_TRY(vec_cs_to_nat(ctx, ctx->vout, rhs_out));
+  }
   ph_outer_end(ctx, PH_ASSEMBLE);
   ctx->assembled = 1;
   ctx->setup_done = 0;

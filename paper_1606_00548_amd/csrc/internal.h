@@ -219,6 +219,7 @@ struct FluidDev {
   double c_w, c_o, c_r, mu_w, mu_o;
   double s_wc, s_or, sg_den;
   double pvt[6][CPR_MAX_PVT];
+  double slope[6][CPR_MAX_PVT];   // of each row's segments
 };
 
 struct Perf {     // one perforated cell of a well
@@ -300,7 +301,7 @@ struct cpr_ctx {
 
   // Jacobian and assembly scratch (colour-split)
   double* J = nullptr;         // [7][b][b] planes of n cells, tiled
-  double* props = nullptr;     // per-cell phase/mobility state for the flux kernel
+  double* lt = nullptr;        // [n] total volumetric mobility of the last assembly (network feature)
   double* vin = nullptr;       // [b][n] input permutation scratch
   double* vin2 = nullptr;      // [b][n]
   double* vout = nullptr;      // [b][n]
@@ -440,10 +441,10 @@ void launch_tiled_to_nat(const Lay& L, int planes, const double* src, double* ds
 // assemble.hip
 void launch_transmissibility(const Lay& L, const cpr_grid_t& g, const double* perm_nat,
                              double* tp, hipStream_t s);
-void launch_assemble(cpr_ctx* ctx, const double* xold_cs, const double* x_cs, double dt_days,
-                     double* rhs_cs);
+// x_old, x and rhs colour-split, or (nat) in natural order; rhs must not
+// overlap the states.
+int launch_assemble(cpr_ctx* ctx, const double* xold, const double* x, double dt_days, double* rhs, bool nat);
 double host_pvt(const FluidDev& f, int row, double p);
-int props_planes(int model);
 
 // spmv.hip
 void launch_spmv(int b, const Lay& L, const double* A, const double* x, double* y,

@@ -36,7 +36,6 @@
 
 int nn_infer(cpr_nn* nn, const float* x3, float* y, const double* xscale);
 float* nn_output(cpr_nn* nn);
-int props_lt_plane(int model);
 
 namespace {
 
@@ -287,7 +286,7 @@ void launch_lnk(const Lay& L, const double* perm_nat, double* lnk, hipStream_t s
 int learned_setup(cpr_ctx* ctx, bool need_nn) {
   if (need_nn && !ctx->nn) return set_err(ctx, CPR_EINVAL, "options.learned set but no network attached");
   if (!ctx->assembled) return set_err(ctx, CPR_EINVAL, "the learned stage needs an assembled state");
-  const double* lt = ctx->props + (size_t)props_lt_plane(ctx->fl.model) * ctx->lay.n;
+  const double* lt = ctx->lt;
   const int lv = ctx->opt.nn_level;
   if (lv == 0) {
     stats_partial_kernel<<<ctx->nblk, LB, 0, ctx->stream>>>(ctx->lay.n, ctx->lnk, lt, ctx->part, ctx->nblk);
@@ -356,7 +355,7 @@ struct StageLevel {
 static StageLevel stage_level(const cpr_ctx* ctx) {
   const int lv = ctx->opt.nn_level;
   if (lv == 0)
-    return {ctx->lay, ctx->levels[0].A, ctx->lnk, ctx->props + (size_t)props_lt_plane(ctx->fl.model) * ctx->lay.n};
+    return {ctx->lay, ctx->levels[0].A, ctx->lnk, ctx->lt};
   return {ctx->levels[lv].lay, ctx->levels[lv].A, ctx->lnk_l, ctx->lt_l};
 }
 

@@ -52,7 +52,7 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
   if (bicg && (rc = ensure_krylov_capacity(ctx, lin.restart > 8 ? lin.restart : 8)) != CPR_OK) return rc;
   for (int cut = 0; cut <= no.max_cuts; ++cut) {
     CPR_TRY(hipMemcpyAsync(x_cs, xold_cs, len * sizeof(double), hipMemcpyDeviceToDevice, s));
-    launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs);
+    if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
     ctx->assembled = 1;
     ctx->setup_done = 0;
     double bb;
@@ -81,7 +81,7 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
       double rr;
       if ((rc = reduce_dot(ctx, r, r, len, &rr)) != CPR_OK) return rc;
       launch_newton_update(b, ctx->lay.n, ctx->nrate, pb_floor(ctx->fl), x_cs, ctx->xs, s);
-      launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs);
+      if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
       ctx->setup_done = 0;
       diff_kernel<<<div_up(len, 256), 256, 0, s>>>(len, ctx->rs, r, ctx->vout);
       double dd;
