@@ -324,7 +324,7 @@ struct cpr_ctx {
   double* cinv = nullptr;      // dense inverse of the coarsest level (column major)
   float* cinvf = nullptr;
   double* gj_work = nullptr;   // Gauss-Jordan workspace
-  int* flag = nullptr;         // device status flag (singular / non-finite)
+  int* flag = nullptr;         // device: singular, quasi-IMPES fallbacks, two last-workgroup counters
   int qimpes_bad = 0;
 
   // Krylov workspace (colour-split)
@@ -535,3 +535,5 @@ void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, con
 // Bubble-point floor of the black-oil update: the first PVT pressure node.
 inline double pb_floor(const FluidDev& f) { return f.model == 3 ? f.pvt[0][0] : 0.0; }
 int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out);
+int reduce_dots(cpr_ctx* ctx, const double* a, const double* b, const double* c, const double* d, long len,
+                double* ab, double* cd);

@@ -56,6 +56,29 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// Values that the last workgroup of a kernel reads from the others.  Stored
+// and loaded at agent scope (past the XCDs' own L2s); a workgroup's thread 0
+// stores its values, waits for them and only then counts itself as arrived
+// (last_block), so the last to arrive sees them all.  No fence is needed for
+// them, and none of the kernel's other stores is read.  The last workgroup
+// leaves the counter at zero for the next kernel.
+__device__ inline void put_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double get_agent(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool last_block(int* counter, int* sh) {
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *sh = old == (int)gridDim.x - 1;
+    if (*sh) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return *sh != 0;
+}
+
 // Block-reduce CHUNK values; thread 0 of the block gets the totals in out.
 __device__ inline void block_sum_chunk(double (&acc)[CHUNK], int cnt, double* sh, double* out) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -280,22 +303,36 @@ enum { S_A = 0, S_C = 32, S_BETA = 64, S_G = 65, S_NRM = 66, S_FLAG = 67 };   //
 // final vectors, that of the unnormalised u, and u's share of ||u||^2.
 enum { D_RED = 704, R_V = 0, R_U = 64, R_ADD = 65 };
 
-// The scalars of step j from its reduced dots (one wavefront, lane i = basis
-// vector i < j <= 32; sums by a fixed butterfly): beta = sqrt(e - |a|^2) (1
-// at step 0, which has no vector to reorthogonalise) and g = (d - a.c) /
-// beta; flag = 1 when beta^2 <= 0.  red (black-row cycles): the dots lack the
-// red halves' share, multiple * multiple * s0 with s0 = |v_0,red|^2; uh's
-// multiple is that of the last u over its norm sqrt(*nrm2).
-__global__ __launch_bounds__(64) void dcgs_coef_kernel(int j, const double* __restrict__ dots,
-                                                       double* __restrict__ coef, double* __restrict__ host,
-                                                       double* __restrict__ red, double s0,
-                                                       const double* __restrict__ nrm2) {
+// The totals of step j's dots (one workgroup per row, fixed order), and by
+// the last workgroup to finish the step's scalars (lane i = basis vector i <
+// j <= 32; sums by a fixed butterfly): beta = sqrt(e - |a|^2) (1 at step 0,
+// which has no vector to reorthogonalise) and g = (d - a.c) / beta; flag = 1
+// when beta^2 <= 0.  red (black-row cycles): the dots lack the red halves'
+// share, multiple * multiple * s0 with s0 = |v_0,red|^2; uh's multiple is
+// that of the last u over its norm sqrt(*nrm2).  One launch for both: the
+// scalars alone were a launch of 3 to 5 us between two others.
+__global__ __launch_bounds__(KB) void dcgs_coef_kernel(int j, const double* __restrict__ part, int nblk,
+                                                       double* dots, double* __restrict__ coef,
+                                                       double* __restrict__ host, double* __restrict__ red, double s0,
+                                                       const double* __restrict__ nrm2, int* counter) {
+  __shared__ double sh[CHUNK * (KB / 64)];
+  __shared__ double tot[CHUNK];
+  __shared__ int last;
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += KB) s += part[(size_t)blockIdx.x * nblk + b];
+  double acc[CHUNK];
+#pragma unroll
+  for (int q = 0; q < CHUNK; ++q) acc[q] = 0.0;
+  acc[0] = s;
+  block_sum_chunk(acc, 1, sh, tot);
+  if (threadIdx.x == 0) put_agent(dots + blockIdx.x, tot[0]);
+  if (!last_block(counter, &last) || threadIdx.x >= 64) return;
   const int i = threadIdx.x;
   const double uh = red ? (j == 0 ? 1.0 : red[R_U] / sqrt(*nrm2)) : 0.0;
   const double rv = red && i < j ? red[R_V + i] : 0.0;
   const double share = red ? rv * uh * s0 : 0.0;
-  const double a = i < j ? dots[i] + share : 0.0;
-  const double c = i < j ? dots[j + i] + share : 0.0;
+  const double a = i < j ? get_agent(dots + i) + share : 0.0;
+  const double c = i < j ? get_agent(dots + j + i) + share : 0.0;
   if (i < j) {
     coef[C_A + i] = a;
     coef[C_C + i] = c;
@@ -306,7 +343,7 @@ __global__ __launch_bounds__(64) void dcgs_coef_kernel(int j, const double* __re
   const double ra = wave_sum(a * rv), rcv = wave_sum(c * rv);
   if (i != 0) return;
   const double own = red ? uh * uh * s0 : 0.0;
-  const double d = dots[2 * j] + own, e = dots[2 * j + 1] + own;
+  const double d = get_agent(dots + 2 * j) + own, e = get_agent(dots + 2 * j + 1) + own;
   const double b2 = j == 0 ? 1.0 : e - aa;
   const bool bad = !(b2 > 0.0);
   const double beta = bad ? 0.0 : sqrt(b2);
@@ -326,15 +363,20 @@ __global__ __launch_bounds__(64) void dcgs_coef_kernel(int j, const double* __re
 }
 
 // Delayed CGS2, update pass of step j: v_j = (uh - V a) / beta over uh,
-// u = w - V c - g v_j over w, and part row 0 = this slice of ||u||^2, over
-// len elements (slot_at).
+// u = w - V c - g v_j over w, over len elements (slot_at), and by the last
+// workgroup to finish ||u||^2 (the slices' sums in a fixed order, plus *add
+// when given) into nrm and pinned host memory.
 template <int NV>
 __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int j, const double* __restrict__ V,
                                                          size_t stride, double* __restrict__ uh,
                                                          double* __restrict__ w, const double* __restrict__ coef,
-                                                         double* __restrict__ part, int nblk) {
+                                                         double* part, int nblk, const double* __restrict__ add,
+                                                         double* __restrict__ nrm, double* __restrict__ host,
+                                                         int* counter) {
   __shared__ double cs[2 * NV + 2];
-  __shared__ double sh[KB / 64];
+  __shared__ double sh[CHUNK * (KB / 64)];
+  __shared__ double tot[CHUNK];
+  __shared__ int last;
   for (int i = threadIdx.x; i < NV; i += KB) {
     cs[i] = i < j ? coef[C_A + i] : 0.0;
     cs[NV + i] = i < j ? coef[C_C + i] : 0.0;
@@ -373,7 +415,18 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int 
   if (threadIdx.x == 0) {
     double t = 0.0;
     for (int q = 0; q < KB / 64; ++q) t += sh[q];
-    part[blockIdx.x] = t;
+    put_agent(part + blockIdx.x, t);
+  }
+  if (!last_block(counter, &last)) return;
+  double total[CHUNK];
+#pragma unroll
+  for (int q = 0; q < CHUNK; ++q) total[q] = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += KB) total[0] += get_agent(part + b);
+  block_sum_chunk(total, 1, sh, tot);
+  if (threadIdx.x == 0) {
+    const double t = tot[0] + (add ? *add : 0.0);
+    *nrm = t;
+    *host = t;
   }
 }
 
@@ -413,16 +466,17 @@ __global__ void scale_kernel(long len, double a, const double* __restrict__ x, d
   if (e < len) y[e] = x[e] / a;
 }
 
-// x += sum_k y[k] Z_k
-__global__ void maxpy_kernel(long len, int nk, const double* __restrict__ Z, size_t stride,
-                             const double* __restrict__ y, double* __restrict__ x) {
-  __shared__ double ys[64];
-  if (threadIdx.x < nk) ys[threadIdx.x] = y[threadIdx.x];
-  __syncthreads();
+// x += sum_k y[k] Z_k, from x = 0 when first (x is then not read); the
+// coefficients come with the launch.
+struct Coefs {
+  double y[64];
+};
+__global__ void maxpy_kernel(long len, int nk, const double* __restrict__ Z, size_t stride, Coefs c, int first,
+                             double* __restrict__ x) {
   long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= len) return;
-  double s = x[e];
-  for (int k = 0; k < nk; ++k) s += ys[k] * Z[k * stride + e];
+  double s = first ? 0.0 : x[e];
+  for (int k = 0; k < nk; ++k) s += c.y[k] * Z[k * stride + e];
   x[e] = s;
 }
 
@@ -611,17 +665,34 @@ void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, con
   newton_update_kernel<<<div_up(n > nrate ? n : nrate, 256), 256, 0, s>>>(b, n, nrate, pb_min, x, dx);
 }
 
-// Dot product of two device vectors of length len into *out (host).  Syncs.
-int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out) {
+// Dot product of two device vectors of length len into host slot `slot` of
+// ctx->hhost (0..7), read after the stream is synchronised.
+static void queue_dot(cpr_ctx* ctx, const double* a, const double* b, long len, int slot) {
   hipStream_t s = ctx->stream;
   // reuse the orthogonalisation kernel with V = a (one vector), w = b
   orth_kernel<<<ctx->nblk, KB, 0, s>>>(len, 1, a, 0, const_cast<double*>(b), nullptr, 1, 0, ctx->part,
                                        ctx->nblk);
-  reduce_kernel<<<1, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr);
+  reduce_kernel<<<1, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev + slot);
+}
+
+// The same into *out; synchronises.
+int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out) {
+  queue_dot(ctx, a, b, len, 0);
   CPR_TRY(hipGetLastError());
-  CPR_TRY(hipMemcpyAsync(ctx->hhost, ctx->hdev, sizeof(double), hipMemcpyDeviceToHost, s));
-  CPR_TRY(hipStreamSynchronize(s));
+  CPR_TRY(hipStreamSynchronize(ctx->stream));
   *out = ctx->hhost[0];
+  return CPR_OK;
+}
+
+// Two dot products with one wait.
+int reduce_dots(cpr_ctx* ctx, const double* a, const double* b, const double* c, const double* d, long len,
+                double* ab, double* cd) {
+  queue_dot(ctx, a, b, len, 0);
+  queue_dot(ctx, c, d, len, 1);
+  CPR_TRY(hipGetLastError());
+  CPR_TRY(hipStreamSynchronize(ctx->stream));
+  *ab = ctx->hhost[0];
+  *cd = ctx->hhost[1];
   return CPR_OK;
 }
 
@@ -630,9 +701,8 @@ static int reduce_colour_norms(cpr_ctx* ctx, const double* x, double* all, doubl
   hipStream_t s = ctx->stream;
   const long bn = (long)ctx->b * ctx->lay.n;
   colour_norms_kernel<<<ctx->nblk, KB, 0, s>>>(bn, ctx->lay.nh, x, ctx->part, ctx->nblk);
-  reduce_kernel<<<2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr);
+  reduce_kernel<<<2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev);
   CPR_TRY(hipGetLastError());
-  CPR_TRY(hipMemcpyAsync(ctx->hhost, ctx->hdev, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
   CPR_TRY(hipStreamSynchronize(s));
   *red = ctx->hhost[1];
   *all = ctx->hhost[0] + ctx->hhost[1];
@@ -665,18 +735,22 @@ void dcgs_dots(cpr_ctx* ctx, long nh, int j, const double* uh, const double* w) 
   prof_end(ctx, CPR_KCLASS_ORTH);
 }
 
-void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const double* coef) {
+void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const double* coef, const double* add,
+                 double* nrm, double* host) {
   hipStream_t s = ctx->stream;
   const int nblk = ctx->nblk;
   const size_t stride = (size_t)vec_len(ctx);
   const long len = nh ? ctx->b * nh : vec_len(ctx);
   prof_begin(ctx, CPR_KCLASS_ORTH);
   if (j <= 8)
-    dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
+                                               host, ctx->flag + 3);
   else if (j <= 16)
-    dcgs_update_kernel<16><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<16><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
+                                               host, ctx->flag + 3);
   else
-    dcgs_update_kernel<32><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk);
+    dcgs_update_kernel<32><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
+                                               host, ctx->flag + 3);
   prof_end(ctx, CPR_KCLASS_ORTH);
 }
 
@@ -767,10 +841,9 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, double s0, int& its, in
     {
       PhaseScope ps(ctx, PH_ORTH);
       dcgs_dots(ctx, nh, j, uj, w);
-      reduce_kernel<<<2 * j + 2, KB, 0, s>>>(ctx->part, nblk, hd + D_DOTS, nullptr);
-      dcgs_coef_kernel<<<1, 64, 0, s>>>(j, hd + D_DOTS, hd + D_COEF, slot, red, s0, hd + D_NRM);
-      dcgs_update(ctx, nh, j, uj, w, hd + D_COEF);
-      reduce_kernel<<<1, KB, 0, s>>>(ctx->part, nblk, hd + D_NRM, black ? red + R_ADD : nullptr, slot + S_NRM);
+      dcgs_coef_kernel<<<2 * j + 2, KB, 0, s>>>(j, ctx->part, nblk, hd + D_DOTS, hd + D_COEF, slot, red, s0, hd + D_NRM,
+                                                ctx->flag + 2);
+      dcgs_update(ctx, nh, j, uj, w, hd + D_COEF, black ? red + R_ADD : nullptr, hd + D_NRM, slot + S_NRM);
     }
     CPR_TRY(hipGetLastError());
     CPR_TRY(hipEventRecord(ctx->ev_iter[j & 1], s));
@@ -863,10 +936,13 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
   ctx->kry_half = 0;
   ph_solve_start(ctx);
 
+  // From zero: x is written by the first cycle's update, and the first
+  // residual is the right-hand side, so one reduction gives both norms.
   const bool from_x0 = ctx->opt.x0 != 0;
-  if (!from_x0) zero_kernel<<<eb, 256, 0, s>>>(len, x);
-  double bb;
-  int rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb);
+  const bool colours = dcgs && ctx->nrate == 0;
+  double bb, bb_red = 0.0;
+  int rc = colours && !from_x0 ? reduce_colour_norms(ctx, ctx->rs, &bb, &bb_red)
+                               : reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb);
   if (rc) return rc;
   double bnorm = std::sqrt(bb);
   S.bnorm = bnorm;
@@ -875,7 +951,8 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
     return set_err(ctx, CPR_ENONFINITE, "non-finite right-hand side");
   }
   if (bnorm == 0.0) {
-    if (from_x0) zero_kernel<<<eb, 256, 0, s>>>(len, x);
+    zero_kernel<<<eb, 256, 0, s>>>(len, x);
+    if (!from_x0) CPR_TRY(hipMemcpyAsync(r, ctx->rs, len * sizeof(double), hipMemcpyDeviceToDevice, s));
     S.converged = 1;
     ph_fill_stats(ctx, &S);
     if (st) *st = S;
@@ -884,26 +961,33 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
   if (from_x0) {
     PhaseScope ps(ctx, PH_SPMV);
     system_spmv(ctx, x, r, ctx->rs);      // r = b - A x0
-  } else {
-    CPR_TRY(hipMemcpyAsync(r, ctx->rs, len * sizeof(double), hipMemcpyDeviceToDevice, s));
   }
   std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), col(m + 1);
   int its = 0;
   int result = CPR_NOT_CONVERGED;
   double beta_start = 0.0;   // true residual at the start of the last cycle
-  double* hd = ctx->hdev;  // h1 [0,64), h1+h2 [64,128), ||w||^2 [128], h2 [192,256), y [256,320)
+  double* hd = ctx->hdev;  // h1 [0,64), h1+h2 [64,128), ||w||^2 [128], h2 [192,256)
   while (true) {
-    double rr, rr_red = 0.0;
-    rc = dcgs && ctx->nrate == 0 ? reduce_colour_norms(ctx, r, &rr, &rr_red) : reduce_dot(ctx, r, r, len, &rr);
-    if (rc) return rc;
+    const bool first = S.cycles == 0 && !from_x0;   // r = b, x = 0
+    double rr = bb, rr_red = bb_red;
+    if (!first) {
+      rc = colours ? reduce_colour_norms(ctx, r, &rr, &rr_red) : reduce_dot(ctx, r, r, len, &rr);
+      if (rc) return rc;
+    }
     double beta = std::sqrt(rr);
     S.true_rel = beta / bnorm;
     if (!std::isfinite(beta)) {
       if (st) *st = S;
       return set_err(ctx, CPR_ENONFINITE, "non-finite residual");
     }
-    if (beta <= rtol * bnorm) { result = CPR_OK; break; }
-    if (its >= max_iter) break;
+    if (beta <= rtol * bnorm || its >= max_iter) {
+      if (beta <= rtol * bnorm) result = CPR_OK;
+      if (first) {
+        zero_kernel<<<eb, 256, 0, s>>>(len, x);
+        CPR_TRY(hipMemcpyAsync(r, ctx->rs, len * sizeof(double), hipMemcpyDeviceToDevice, s));
+      }
+      break;
+    }
     // mixed precision or the learned stage: a restart cycle that left the
     // true residual above stall_ratio times the one it started from (by
     // default: less than halved, where a healthy cycle gains one to two
@@ -916,7 +1000,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
       S.fp64_fallback = S.cycles;
     }
     beta_start = beta;
-    scale_kernel<<<eb, 256, 0, s>>>(len, beta, r, ctx->V);
+    scale_kernel<<<eb, 256, 0, s>>>(len, beta, first ? ctx->rs : r, ctx->V);
     std::fill(H.begin(), H.end(), 0.0);
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
@@ -1026,9 +1110,9 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
       for (int c = i + 1; c < k; ++c) t -= H[(size_t)i * m + c] * y[c];
       y[i] = t / H[(size_t)i * m + i];
     }
-    for (int i = 0; i < k; ++i) ctx->hhost[256 + i] = y[i];
-    CPR_TRY(hipMemcpyAsync(hd + 256, ctx->hhost + 256, k * sizeof(double), hipMemcpyHostToDevice, s));
-    maxpy_kernel<<<eb, 256, 0, s>>>(len, k, ctx->Z, stride, hd + 256, x);
+    Coefs yc;
+    for (int i = 0; i < 64; ++i) yc.y[i] = i < k ? y[i] : 0.0;
+    maxpy_kernel<<<eb, 256, 0, s>>>(len, k, ctx->Z, stride, yc, first, x);
     S.cycles += 1;
     S.est_rel = std::fabs(g[k]) / bnorm;
     PhaseScope ps(ctx, PH_SPMV);

@@ -78,15 +78,19 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
       if (attempt_failure(rc)) break;
       if (rc < 0) return rc;
       const double* r = bicg ? ctx->V : ctx->tmp;   // b - A dx
-      double rr;
-      if ((rc = reduce_dot(ctx, r, r, len, &rr)) != CPR_OK) return rc;
+      // what the forcing term needs: EW2 ||r||, EW1 ||b^l - r||
+      double rr = 0.0, dd = 0.0;
+      if (no.forcing == CPR_FORCING_EW2 && (rc = reduce_dot(ctx, r, r, len, &rr)) != CPR_OK) return rc;
       launch_newton_update(b, ctx->lay.n, ctx->nrate, pb_floor(ctx->fl), x_cs, ctx->xs, s);
       if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
       ctx->setup_done = 0;
-      diff_kernel<<<div_up(len, 256), 256, 0, s>>>(len, ctx->rs, r, ctx->vout);
-      double dd;
-      if ((rc = reduce_dot(ctx, ctx->vout, ctx->vout, len, &dd)) != CPR_OK) return rc;
-      if ((rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb)) != CPR_OK) return rc;
+      if (no.forcing == CPR_FORCING_EW1) {
+        diff_kernel<<<div_up(len, 256), 256, 0, s>>>(len, ctx->rs, r, ctx->vout);
+        rc = reduce_dots(ctx, ctx->vout, ctx->vout, ctx->rs, ctx->rs, len, &dd, &bb);
+      } else {
+        rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb);
+      }
+      if (rc != CPR_OK) return rc;
       bn_prev = bn;
       rn_prev = std::sqrt(rr);
       diff_prev = std::sqrt(dd);

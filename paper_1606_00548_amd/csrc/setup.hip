@@ -700,7 +700,7 @@ int setup_cpr(cpr_ctx* ctx) {
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   const int n = L.n;
-  zero_int_kernel<<<1, 64, 0, s>>>(ctx->flag, 2);
+  zero_int_kernel<<<1, 64, 0, s>>>(ctx->flag, 4);   // and the counters of the Krylov kernels' last workgroups
   // per-cell kernels stream the Jacobian's planes in one-wave workgroups
   int nb = div_up(n, 64);
   const bool abf = ctx->opt.decoupling == CPR_DECOUPLE_ABF;
