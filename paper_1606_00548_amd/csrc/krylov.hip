@@ -363,9 +363,9 @@ __global__ __launch_bounds__(KB) void dcgs_coef_kernel(int j, const double* __re
 }
 
 // Delayed CGS2, update pass of step j: v_j = (uh - V a) / beta over uh,
-// u = w - V c - g v_j over w, over len elements (slot_at), and by the last
-// workgroup to finish ||u||^2 (the slices' sums in a fixed order, plus *add
-// when given) into nrm and pinned host memory.
+// u = w - V c - g v_j over w, over len elements (slot_at), and part row 0 =
+// this slice of ||u||^2.  With a counter the last workgroup to finish sums the
+// slices (fixed order, plus *add when given) into nrm and pinned host memory.
 template <int NV>
 __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int j, const double* __restrict__ V,
                                                          size_t stride, double* __restrict__ uh,
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int 
     for (int q = 0; q < KB / 64; ++q) t += sh[q];
     put_agent(part + blockIdx.x, t);
   }
-  if (!last_block(counter, &last)) return;
+  if (!counter || !last_block(counter, &last)) return;
   double total[CHUNK];
 #pragma unroll
   for (int q = 0; q < CHUNK; ++q) total[q] = 0.0;
@@ -742,15 +742,21 @@ void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const doub
   const size_t stride = (size_t)vec_len(ctx);
   const long len = nh ? ctx->b * nh : vec_len(ctx);
   prof_begin(ctx, CPR_KCLASS_ORTH);
+  // Arriving at one counter costs about 10 ns a workgroup: up to UPDATE_LAST
+  // of them that is less than the reduction's launch (3.5 to 5 us), for 768
+  // (128x128x32) it was 11 us.
+  constexpr int UPDATE_LAST = 128;
+  int* counter = nblk <= UPDATE_LAST ? ctx->flag + 3 : nullptr;
   if (j <= 8)
     dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
-                                               host, ctx->flag + 3);
+                                              host, counter);
   else if (j <= 16)
     dcgs_update_kernel<16><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
-                                               host, ctx->flag + 3);
+                                               host, counter);
   else
     dcgs_update_kernel<32><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
-                                               host, ctx->flag + 3);
+                                               host, counter);
+  if (!counter) reduce_kernel<<<1, KB, 0, s>>>(ctx->part, nblk, nrm, add, host);
   prof_end(ctx, CPR_KCLASS_ORTH);
 }
 
