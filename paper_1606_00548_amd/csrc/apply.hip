@@ -118,15 +118,15 @@ __device__ inline T offdiag_sum(const Lay& L, const T* __restrict__ A, const T* 
   return s;
 }
 
-// black cell q: Gauss-Seidel update and its residual r - A x afterwards
-template <typename T, bool NT = true>
+// black cell q: Gauss-Seidel update and (RES) its residual r - A x afterwards
+template <typename T, bool NT = true, bool RES = true>
 __device__ inline void black_pre_cell(const Lay& L, const T* __restrict__ A, const T* __restrict__ r,
                                       T* __restrict__ x, T* __restrict__ res, int q) {
   int t = L.nh + q;
   T s = offdiag_sum<T, NT>(L, A, x, t);
   T xb = (r[t] - s) / A[t];
   x[t] = xb;
-  res[q] = r[t] - (A[t] * xb + s);
+  if (RES) res[q] = r[t] - (A[t] * xb + s);
 }
 
 // black cell q after the coarse correction: neighbours are red cells whose
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void decouple_red_kernel(int n, int nh, const 
       v = v / hn;
       vout[(size_t)r * n + t] = v;
     }
-    s += w[(size_t)r * n + t] * v;
+    s = r == 0 ? v : s + w[(size_t)r * n + t] * v;   // w_0 = 1 (cpr_setup)
   }
   T rs = (T)s;
   rp[t] = rs;
@@ -235,9 +235,9 @@ __global__ __launch_bounds__(256) void decouple_full_kernel(int n, int nh, const
       rt[r] = s;
     }
   } else {
-    double s = 0.0;
+    double s = v[0];   // w_0 = 1 (cpr_setup)
 #pragma unroll
-    for (int r = 0; r < B; ++r) s += w[(size_t)r * N + t] * v[r];
+    for (int r = 1; r < B; ++r) s += w[(size_t)r * N + t] * v[r];
     rt[0] = s;
 #pragma unroll
     for (int r = 1; r < B; ++r) rt[r] = v[r];
@@ -267,25 +267,24 @@ __global__ __launch_bounds__(256) void decouple_full_kernel(int n, int nh, const
   }
 }
 
-template <typename T>
+template <typename T, bool RES>
 __global__ __launch_bounds__(256) void black_pre_kernel(Lay L, const T* __restrict__ A, const T* __restrict__ r,
                                                         T* __restrict__ x, T* __restrict__ res) {
   int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < L.nh) black_pre_cell(L, A, r, x, res, q);
+  if (q < L.nh) black_pre_cell<T, true, RES>(L, A, r, x, res, q);
 }
 
-// Restriction with four threads per coarse cell: thread (cell, q, s) sums
-// the two fine cells (2ci, 2ci+1) of fine row (2cj+q, 2ck+s); the four
-// partials of a coarse cell sit in adjacent lanes and are combined in a
-// fixed order.  Coarse cells are taken in natural order (ci fastest), so
-// the lanes reading one fine row read consecutive cells of each colour half
-// (in colour-split order consecutive coarse cells are two apart in x, and
-// the fine reads would use every other value of each line).  Every lane
-// takes its row's red cell (residual r - A x formed here) and its black
-// cell (residual recorded by the black sweep) in the same order, so the
-// lanes do not diverge on the colour; the two terms are added as a sum of
-// two, whose value does not depend on their order.  With seq the eight
-// residuals are summed one after the other in natural order instead, as the
+// Restriction: a workgroup takes 64 consecutive coarse cells in natural order
+// (ci fastest) and its wave (q, s) the fine rows (2cj+q, 2ck+s) under them,
+// the two fine cells (2ci, 2ci+1) of its row per lane; the four partials of a
+// coarse cell meet in LDS and are combined in a fixed order.  Consecutive
+// lanes so read consecutive cells of each colour half, a wave's load one run
+// of 64 (with the four rows in adjacent lanes a load covered four runs of 16;
+// FP64 fine level of 384x384x96: 186 -> 118 us).  Every lane takes its row's
+// red cell (residual r - A x formed here) and its black cell (residual
+// recorded by the black sweep) in the same order, so the lanes do not diverge
+// on the colour; the two terms are added as a sum of two, whose value does not
+// depend on their order.  With seq the eight residuals are summed one after the other in natural order instead, as the
 // single-workgroup kernel does it (a level takes either route by its size
 // and type; its values do not change with it).
 // If xc is given, the coarse level's zero-guess red sweep is done here too:
@@ -295,15 +294,17 @@ __global__ __launch_bounds__(256) void restrict4_kernel(Lay F, Lay C, const T* _
                                                         const T* __restrict__ r, const T* __restrict__ x,
                                                         const T* __restrict__ res, T* __restrict__ rc,
                                                         const T* __restrict__ Ac, T* __restrict__ xc, int seq) {
-  int g = blockIdx.x * blockDim.x + threadIdx.x;
-  int cn = g >> 2, sub = g & 3;
-  T acc = 0, lo = 0, hi = 0;
-  int tc = -1;
+  __shared__ T sh[4][2][64];
+  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int cn = blockIdx.x * 64 + lane;
+  T lo = 0, hi = 0;   // residuals of the cells 2ci and 2ci + 1
+  int ci = 0, cj = 0, ck = 0;
   if (cn < C.n) {
-    const int ci = cn % C.nx, cjk = cn / C.nx;
-    const int cj = cjk % C.ny, ck = cjk / C.ny;
-    tc = lay_index(C, ci, cj, ck);
-    int fj = 2 * cj + (sub & 1), fk = 2 * ck + (sub >> 1);
+    const int cjk = cn / C.nx;
+    ci = cn - cjk * C.nx;
+    ck = cjk / C.ny;
+    cj = cjk - ck * C.ny;
+    const int fj = 2 * cj + (sub & 1), fk = 2 * ck + (sub >> 1);
     if (fj < F.ny && fk < F.nz) {
       const int odd = (fj + fk) & 1;
       const int fr = 2 * ci + odd, fb = 2 * ci + 1 - odd;   // red and black cell of the pair
@@ -314,26 +315,30 @@ __global__ __launch_bounds__(256) void restrict4_kernel(Lay F, Lay C, const T* _
         vr = r[f] - y;
       }
       if (fb < F.nx) vb = res[lay_index(F, fb, fj, fk) - F.nh];
-      acc = vr + vb;
       lo = odd ? vb : vr;
       hi = odd ? vr : vb;
     }
   }
+  sh[sub][0][lane] = lo;
+  sh[sub][1][lane] = hi;
+  __syncthreads();
+  if (sub != 0 || cn >= C.n) return;
+  T acc = 0;
   if (seq) {
-    acc = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      acc += __shfl(lo, q, 4);
-      acc += __shfl(hi, q, 4);
+      acc += sh[q][0][lane];
+      acc += sh[q][1][lane];
     }
   } else {
-    acc += __shfl_down(acc, 2, 4);
-    acc += __shfl_down(acc, 1, 4);
+    T p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = sh[q][0][lane] + sh[q][1][lane];
+    acc = (p[0] + p[2]) + (p[1] + p[3]);
   }
-  if (tc >= 0 && sub == 0) {
-    rc[tc] = acc;
-    if (xc && tc < C.nh) red_zero_cell(Ac, rc, xc, tc);
-  }
+  const int tc = lay_index(C, ci, cj, ck);
+  rc[tc] = acc;
+  if (xc && tc < C.nh) red_zero_cell(Ac, rc, xc, tc);
 }
 
 template <typename T>
@@ -561,32 +566,6 @@ hipError_t launch_coarse_cycle(CoarseArgs<T>& a, hipStream_t s) {
 
 // ------------------------------------------------------------ stage 2 + block ILU(0)
 
-// Stage-2 residual r2 = r~ - A~(:, p) dp at cell t.
-template <int B, typename T, typename VT>
-__device__ inline void stage2_resid(const Lay& L, int t, const CsCell& cc, const T* J, const T* R0,
-                                    const VT* __restrict__ v, const T* __restrict__ rp,
-                                    const T* __restrict__ dp, T (&r2)[B]) {
-  const size_t N = L.n;
-  int nbr[7];
-  bool ok[7];
-  cs_nbrs(L, t, cc, nbr, ok);
-  T a[7][B];
-#pragma unroll
-  for (int d = 0; d < 7; ++d)
-#pragma unroll
-    for (int r = 0; r < B; ++r) a[d][r] = at_blk<B, T>(J, R0, N, d, r, 0, t);
-  r2[0] = rp[t];
-#pragma unroll
-  for (int r = 1; r < B; ++r) r2[r] = (T)v[r * N + t];
-#pragma unroll
-  for (int d = 0; d < 7; ++d) {
-    T p = dp[nbr[d]];
-    p = ok[d] ? p : (T)0;
-#pragma unroll
-    for (int r = 0; r < B; ++r) r2[r] -= a[d][r] * p;
-  }
-}
-
 template <int B, typename T>
 __device__ inline void offdiag_apply(const Lay& L, int t, const CsCell& cc, const T* J, const T* R0,
                                      const T* __restrict__ Y, T (&s)[B]) {
@@ -637,19 +616,50 @@ __device__ inline void dinv_apply(const T* __restrict__ Dinv, size_t N, int t, c
 // residual Rt otherwise (VT = T).  With z1 given (F-P-F) the first stage's
 // result is added to z.
 
-// red cells: forward ILU step y_r = D'^-1 r2_r (no lower neighbours)
-template <int B, typename T, typename VT>
+// red cells: forward ILU step y_r = D'^-1 r2_r (no lower neighbours).  With
+// SWEEP the last Gauss-Seidel half-sweep of the pressure cycle comes first:
+// dp = (r~_0 - sum_d a_d dp_nb) / a_0 with the stencil a_d = A~_d(0, 0), the
+// values stage 2 needs itself, so the sweep's own pass (its stencil planes,
+// right-hand side and neighbours: 10 of 50 values a cell in FP64) and launch
+// are saved (FP64, 384x384x96: 98 + 388 us apart, 391 us together).
+template <int B, typename T, typename VT, bool SWEEP>
 __global__ __launch_bounds__(256) void stage2_red_fwd_kernel(Lay L, const T* __restrict__ J,
                                                              const T* __restrict__ R0,
                                                              const T* __restrict__ Dinv,
                                                              const VT* __restrict__ v,
-                                                             const T* __restrict__ rp,
-                                                             const T* __restrict__ dp, T* __restrict__ Y) {
+                                                             const T* __restrict__ rp, T* dp, T* __restrict__ Y) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= L.nh) return;
   CsCell cc = cs_decode(L, t);
-  T r2[B], y[B];
-  stage2_resid<B, T, VT>(L, t, cc, J, R0, v, rp, dp, r2);
+  const size_t N = L.n;
+  int nbr[7];
+  bool ok[7];
+  cs_nbrs(L, t, cc, nbr, ok);
+  T a[7][B];
+#pragma unroll
+  for (int d = 0; d < 7; ++d)
+#pragma unroll
+    for (int r = 0; r < B; ++r) a[d][r] = at_blk<B, T>(J, R0, N, d, r, 0, t);
+  T r2[B], y[B], p[7];
+  r2[0] = rp[t];
+#pragma unroll
+  for (int r = 1; r < B; ++r) r2[r] = (T)v[r * N + t];
+#pragma unroll
+  for (int d = SWEEP ? 1 : 0; d < 7; ++d) {
+    const T q = dp[nbr[d]];
+    p[d] = ok[d] ? q : (T)0;
+  }
+  if (SWEEP) {
+    T s = 0;
+#pragma unroll
+    for (int d = 1; d < 7; ++d) s += a[d][0] * p[d];
+    p[0] = (r2[0] - s) / a[0][0];
+    dp[t] = p[0];
+  }
+#pragma unroll
+  for (int d = 0; d < 7; ++d)
+#pragma unroll
+    for (int r = 0; r < B; ++r) r2[r] -= a[d][r] * p[d];
   dinv_apply<B, T>(Dinv, L.n, t, r2, y);
 #pragma unroll
   for (int r = 0; r < B; ++r) Y[(size_t)r * L.n + t] = y[r];
@@ -1107,8 +1117,19 @@ int cycle_fused_level(cpr_ctx* ctx) {
   return nl;
 }
 
+// The last red sweep of the fine level, left to the first kernel of stage 2:
+// both run over the red cells, the sweep's stencil is the pressure column of
+// the decoupled row 0 that stage 2 reads anyway, and the swept value is only
+// read by this cell's own row (red cells couple to black ones).  Not where
+// the fine level is solved directly or something (the learned stage) reads
+// the finished cycle in between, nor with tiles as colours.
+bool red_sweep_in_stage2(const cpr_ctx* ctx) {
+  return ctx->levels.size() > 1 && ctx->opt.ilu_order == CPR_ILU_RED_BLACK &&
+         !(learned_on(ctx) && ctx->opt.nn_level == 0);
+}
+
 template <typename T>
-void vcycle(cpr_ctx* ctx) {
+void vcycle(cpr_ctx* ctx, bool skip_last_red) {
   hipStream_t s = ctx->stream;
   const int nl = (int)ctx->levels.size();
   const int nc = ctx->levels.back().lay.n;
@@ -1120,16 +1141,23 @@ void vcycle(cpr_ctx* ctx) {
     MGLevel& C = ctx->levels[l + 1];
     int nh = div_up(L.lay.nh, SB);
     // level 0's zero-guess red sweep is fused into the decoupling kernel and
-    // that of the coarser multi-block levels into the restriction above them
-    TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
-                                                                     Pre<T>::x(L), Pre<T>::res(L))));
+    // that of the coarser multi-block levels into the restriction above them;
+    // the last black sweep leaves its residuals for the restriction
+    auto black = [&](bool last) {
+      if (last)
+        TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T, true><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
+                                                                              Pre<T>::x(L), Pre<T>::res(L))));
+      else
+        TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T, false><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
+                                                                               Pre<T>::x(L), Pre<T>::res(L))));
+    };
+    black(ctx->opt.mg_pre == 1);
     for (int k = 1; k < ctx->opt.mg_pre; ++k) {
       TIMED(CPR_KCLASS_SMOOTH, (red_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L), Pre<T>::x(L))));
-      TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
-                                                                       Pre<T>::x(L), Pre<T>::res(L))));
+      black(k + 1 == ctx->opt.mg_pre);
     }
     const bool next_multi = l + 1 < down;
-    restrict4_kernel<T><<<div_up(4L * C.lay.n, SB), SB, 0, s>>>(
+    restrict4_kernel<T><<<div_up(C.lay.n, 64), 256, 0, s>>>(
         L.lay, C.lay, Pre<T>::A(L), Pre<T>::r(L), Pre<T>::x(L), Pre<T>::res(L), Pre<T>::r(C),
         next_multi ? Pre<T>::A(C) : nullptr, next_multi ? Pre<T>::x(C) : nullptr, l >= small);
   }
@@ -1148,10 +1176,11 @@ void vcycle(cpr_ctx* ctx) {
     int nh = div_up(L.lay.nh, SB);
     TIMED(CPR_KCLASS_SMOOTH, (black_post_kernel<T><<<nh, SB, 0, s>>>(L.lay, C.lay, alpha, Pre<T>::A(L),
                                                                       Pre<T>::r(L), Pre<T>::x(C), Pre<T>::x(L))));
-    TIMED(CPR_KCLASS_SMOOTH, (red_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L), Pre<T>::x(L))));
-    for (int k = 1; k < ctx->opt.mg_post; ++k) {
-      TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
-                                                                       Pre<T>::x(L), Pre<T>::res(L))));
+    for (int k = 1; k <= ctx->opt.mg_post; ++k) {
+      if (k > 1)
+        TIMED(CPR_KCLASS_SMOOTH, (black_pre_kernel<T, false><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L),
+                                                                               Pre<T>::x(L), Pre<T>::res(L))));
+      if (l == 0 && k == ctx->opt.mg_post && skip_last_red) break;
       TIMED(CPR_KCLASS_SMOOTH, (red_kernel<T><<<nh, SB, 0, s>>>(L.lay, Pre<T>::A(L), Pre<T>::r(L), Pre<T>::x(L))));
     }
     // the learned correction on this level, before the finer levels'
@@ -1161,12 +1190,12 @@ void vcycle(cpr_ctx* ctx) {
 }
 
 template <int B, typename T, typename VT>
-void stage2(cpr_ctx* ctx, const VT* vr, const T* z1, double* z) {
+void stage2(cpr_ctx* ctx, const VT* vr, const T* z1, double* z, bool sweep) {
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   MGLevel& L0 = ctx->levels[0];
   const T* rp = Pre<T>::r(L0);
-  const T* dp = Pre<T>::x(L0);
+  T* dp = Pre<T>::x(L0);
   const T* J = Pre<T>::J(ctx);
   const T* R0 = Pre<T>::R0(ctx);
   const T* Dinv = Pre<T>::Dinv(ctx);
@@ -1181,7 +1210,10 @@ void stage2(cpr_ctx* ctx, const VT* vr, const T* z1, double* z) {
     return;
   }
   int nh = div_up(L.nh, SB);
-  TIMED(CPR_KCLASS_ILU, (stage2_red_fwd_kernel<B, T, VT><<<nh, SB, 0, s>>>(L, J, R0, Dinv, vr, rp, dp, Y)));
+  if (sweep)
+    TIMED(CPR_KCLASS_ILU, (stage2_red_fwd_kernel<B, T, VT, true><<<nh, SB, 0, s>>>(L, J, R0, Dinv, vr, rp, dp, Y)));
+  else
+    TIMED(CPR_KCLASS_ILU, (stage2_red_fwd_kernel<B, T, VT, false><<<nh, SB, 0, s>>>(L, J, R0, Dinv, vr, rp, dp, Y)));
   TIMED(CPR_KCLASS_ILU, (stage2_black_kernel<B, T, VT><<<nh, SB, 0, s>>>(L, J, R0, Dinv, vr, rp, dp, Y, z1, z)));
   TIMED(CPR_KCLASS_ILU, (stage2_red_bwd_kernel<B, T><<<nh, SB, 0, s>>>(L, J, R0, Dinv, dp, Y, z1, z)));
 }
@@ -1208,9 +1240,10 @@ void apply_variant(cpr_ctx* ctx, const double* vin, double* v, const double* nrm
     TIMED(CPR_KCLASS_ILU, (fpf_red_bwd_kernel<B, T><<<nh, SB, 0, s>>>(L, J, R0, Dinv, Z1, Rt, rp, x0)));
     TIMED(CPR_KCLASS_ILU, (fpf_resid_kernel<B, T><<<nh, SB, 0, s>>>(L, J, R0, Z1, Rt, rp)));
   }
-  vcycle<T>(ctx);
+  const bool sweep = red_sweep_in_stage2(ctx);
+  vcycle<T>(ctx, sweep);
   if (learned_on(ctx) && ctx->opt.nn_level == 0) learned_stage(ctx);
-  stage2<B, T, T>(ctx, Rt, FPF ? Z1 : nullptr, z);
+  stage2<B, T, T>(ctx, Rt, FPF ? Z1 : nullptr, z, sweep);
 }
 
 template <int B, typename T>
@@ -1226,10 +1259,11 @@ void apply_impl(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, 
   MGLevel& L0 = ctx->levels[0];
   decouple_red_kernel<B, T><<<div_up(L.n, SB), SB, 0, s>>>(L.n, L.nh, ctx->w, vin, v, nrm2, v0, redc,
                                                             Pre<T>::A(L0), Pre<T>::r(L0), Pre<T>::x(L0));
-  vcycle<T>(ctx);
+  const bool sweep = red_sweep_in_stage2(ctx);
+  vcycle<T>(ctx, sweep);
   if (learned_on(ctx) && ctx->opt.nn_level == 0) learned_stage(ctx);
   // rows >= 1 of the quasi-IMPES decoupled residual are those of v
-  stage2<B, T, double>(ctx, v, nullptr, z);
+  stage2<B, T, double>(ctx, v, nullptr, z, sweep);
 }
 
 // FP32 copies: decoupled blocks (row 0 from R0), ILU diagonals, MG levels.
@@ -1297,7 +1331,7 @@ void precond_pressure_stage(cpr_ctx* ctx, const double* v) {
     decouple_red_kernel<3, double><<<div_up(L.n, SB), SB, 0, ctx->stream>>>(L.n, L.nh, ctx->w, v, nullptr, nullptr,
                                                                                nullptr, nullptr,
                                                                                L0.A, L0.r, L0.x);
-  vcycle<double>(ctx);
+  vcycle<double>(ctx, false);
 }
 
 void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z, const double* v0,
