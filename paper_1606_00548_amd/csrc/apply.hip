@@ -32,6 +32,7 @@ namespace {
 
 constexpr int FUSE_MAX = 4096;   // cells of the first level handled by the fused kernel
 constexpr int DENSE_FUSED_MAX = 1024;
+constexpr int DENSE_FUSED_NC = 128;   // coarsest cells of the single-workgroup kernel (cycle_fused_level)
 constexpr int DENSE_PF = 17;     // coarsest-inverse entries per thread (of 1024) loaded at the fused kernel's start
 constexpr int STAGE_UNROLL = 8;  // loads per thread in flight while the fused kernel stages its levels
 constexpr int MAXLV = 16;
@@ -554,8 +555,161 @@ size_t coarse_stage_layout(CoarseArgs<T>& a) {
   return off * sizeof(T);
 }
 
+// The same for one smoothed level over the coarsest one (what the default
+// coarsest size leaves; an aggregate has at most eight cells, so the level has
+// at most PAIR_MAX), with everything but x in registers: one thread per cell,
+// red ones in the first half of the workgroup, loads its stencil row,
+// right-hand side and neighbours' places once, all loads in flight together,
+// and a half-sweep is then six LDS reads and a division between two barriers.
+// The arithmetic and its order are those above; the chains of address
+// arithmetic and LDS reads of every sweep are what it saves (1,024 over 128
+// cells, FP64, V(1,1): 15.8 -> 7.7 us).
+constexpr int PAIR_MAX = 8 * DENSE_FUSED_NC;
+template <typename T>
+__global__ __launch_bounds__(1024) void coarse_pair_kernel(CoarseArgs<T> a) {
+  __shared__ T xs[PAIR_MAX + 1], res[PAIR_MAX + 1], rc[DENSE_FUSED_NC], xc[DENSE_FUSED_NC + 1];
+  __shared__ double part[1024];
+  __shared__ unsigned short child[8 * DENSE_FUSED_NC];
+  const Lay &F = a.lay[0], &C = a.lay[1];
+  const int tid = threadIdx.x, nc = C.n;
+  const int side = tid / (PAIR_MAX / 2), slot = tid % (PAIR_MAX / 2);   // wave-uniform side
+  const bool own = slot < F.nh;
+  const bool red = own && side == 0, black = own && side == 1;
+  const int t = side * F.nh + (own ? slot : 0);
+  T A[7];
+#pragma unroll
+  for (int d = 0; d < 7; ++d) A[d] = a.A[0][(size_t)d * F.n + t];
+  const T r = a.r[0][t];
+  const int parts = 1024 / nc, drow = tid % nc, dp = tid / nc;
+  const bool dactive = tid < nc * parts;
+  double pre[DENSE_PF];
+#pragma unroll
+  for (int u = 0; u < DENSE_PF; ++u) {
+    const int c = dp + u * parts;
+    pre[u] = dactive && c < nc ? a.inv[(size_t)c * nc + drow] : 0.0;
+  }
+  // the cell's neighbours and their aggregates as byte offsets of 16 bits, and
+  // in LDS every coarse cell's aggregate; a missing cell is the zero behind
+  // each array
+  unsigned nbr[3], agg[3];
+  {
+    int nb[7], ag[7];
+    bool ok[7];
+    const CsCell cc = cs_decode(F, t);
+    cs_nbrs(F, t, cc, nb, ok);
+#pragma unroll
+    for (int d = 1; d < 7; ++d) {
+      int di, dj, dk;
+      dir_offset(d, di, dj, dk);
+      nb[d] = ok[d] ? nb[d] : PAIR_MAX;
+      ag[d] = ok[d] ? lay_index(C, (cc.i + di) >> 1, (cc.j + dj) >> 1, (cc.k + dk) >> 1) : DENSE_FUSED_NC;
+    }
+    constexpr unsigned W = sizeof(T);
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+      nbr[h] = nb[2 * h + 1] * W | nb[2 * h + 2] * W << 16;
+      agg[h] = ag[2 * h + 1] * W | ag[2 * h + 2] * W << 16;
+    }
+  }
+  if (tid < 8 * nc) {
+    int ci, cj, ck;
+    lay_coords(C, tid >> 3, ci, cj, ck);
+    const int fi = 2 * ci + (tid & 1), fj = 2 * cj + ((tid >> 1) & 1), fk = 2 * ck + ((tid >> 2) & 1);
+    child[tid] = (unsigned short)(fi < F.nx && fj < F.ny && fk < F.nz ? lay_index(F, fi, fj, fk) : PAIR_MAX);
+  }
+  if (tid == 0) xs[PAIR_MAX] = res[PAIR_MAX] = xc[DENSE_FUSED_NC] = (T)0;
+  auto at = [](const T* p, const unsigned(&n)[3], int d) {   // p at offset d of 1 .. 6
+    const unsigned o = (d & 1) ? n[(d - 1) / 2] & 0xffffu : n[(d - 1) / 2] >> 16;
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + o);
+  };
+  auto offdiag = [&] {
+    T v = 0;
+#pragma unroll
+    for (int d = 1; d < 7; ++d) v += A[d] * at(xs, nbr, d);
+    return v;
+  };
+  T x = 0;
+  // half-sweep of the threads of one colour; the last black one before the
+  // restriction leaves its residuals
+  auto sweep = [&](bool mine, bool keep) {
+    if (mine) {
+      const T v = offdiag();
+      x = (r - v) / A[0];
+      xs[t] = x;
+      if (keep) res[t] = r - (A[0] * x + v);
+    }
+    __syncthreads();
+  };
+  if (red) {
+    x = r / A[0];
+    xs[t] = x;
+  }
+  __syncthreads();
+  sweep(black, a.pre == 1);
+  for (int k = 1; k < a.pre; ++k) {
+    sweep(red, false);
+    sweep(black, k + 1 == a.pre);
+  }
+  if (red) {
+    const T y = A[0] * x + offdiag();
+    res[t] = r - y;
+  }
+  __syncthreads();
+  if (tid < nc) {
+    T acc = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += res[child[8 * tid + e]];
+    rc[tid] = acc;
+    a.r[1][tid] = acc;
+  }
+  __syncthreads();
+  if (dactive) {
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < DENSE_PF; ++u) {
+      const int c = dp + u * parts;
+      if (c < nc) v += pre[u] * (double)rc[c];
+    }
+    part[tid] = v;
+  }
+  __syncthreads();
+  if (tid < nc) {
+    double v = 0.0;
+    for (int p = 0; p < parts; ++p) v += part[p * nc + tid];
+    xc[tid] = (T)v;
+    a.x[1][tid] = (T)v;
+  }
+  __syncthreads();
+  if (black) {
+    T v = 0;
+#pragma unroll
+    for (int d = 1; d < 7; ++d) {
+      const T p = at(xs, nbr, d) + a.alpha * at(xc, agg, d);
+      v += A[d] * p;
+    }
+    x = (r - v) / A[0];
+    xs[t] = x;
+  }
+  __syncthreads();
+  sweep(red, false);
+  for (int k = 1; k < a.post; ++k) {
+    sweep(black, false);
+    sweep(red, false);
+  }
+  if (own) a.x[0][t] = x;
+}
+
+template <typename T>
+bool coarse_pair(const CoarseArgs<T>& a) {
+  return a.count == 2 && a.lay[1].n <= DENSE_FUSED_NC && a.lay[0].n <= PAIR_MAX;
+}
+
 template <typename T>
 hipError_t launch_coarse_cycle(CoarseArgs<T>& a, hipStream_t s) {
+  if (coarse_pair(a)) {
+    coarse_pair_kernel<T><<<1, 1024, 0, s>>>(a);
+    return hipSuccess;
+  }
   // more than the default 64 KB of dynamic LDS
   static const hipError_t big_lds = hipFuncSetAttribute(
       (const void*)coarse_cycle_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, COARSE_LDS_MAX);
@@ -1096,23 +1250,22 @@ CoarseArgs<T> coarse_args(cpr_ctx* ctx, int first) {
 
 // First level the cycle hands to the single-workgroup kernel (nl: none, and
 // the coarsest solve is a kernel of its own).  The kernel saves the launches
-// of its levels, but is one workgroup: it takes levels that its LDS holds
-// (up to about 1,790 cells in FP64, 3,570 in FP32) over a coarsest inverse of
-// at most DENSE_FUSED_NC rows, which its threads can hold in registers from
-// the start; reading a larger one costs it more than the launches.  One
-// application, V(1,1) FP64, one workgroup against multi-block kernels: 64
-// against 72 us with 1,024 over 128 cells (64x64x16), 78 against 73 with
-// 1,600 over 200 (80x80x16), and with the levels in global memory 343 against
-// 290 with 2,464 over 336 (60x220x85), 156 against 92 with 3,456 over 432
-// (96x96x24).
-constexpr int DENSE_FUSED_NC = 128;
+// of its levels, but is one workgroup: it takes levels that it can hold (one
+// level in registers, more in LDS up to about 1,790 cells in FP64 and 3,570 in
+// FP32) over a coarsest inverse of at most DENSE_FUSED_NC rows, which its
+// threads can hold in registers from the start; reading a larger one costs it
+// more than the launches.  One application, V(1,1) FP64, one workgroup
+// against multi-block kernels: 64 (by now 56) against 72 us with 1,024 over
+// 128 cells (64x64x16), 78 against 73 with 1,600 over 200 (80x80x16), and with
+// the levels in global memory 343 against 290 with 2,464 over 336 (60x220x85),
+// 156 against 92 with 3,456 over 432 (96x96x24).
 template <typename T>
 int cycle_fused_level(cpr_ctx* ctx) {
   const int nl = (int)ctx->levels.size();
   if (ctx->levels.back().lay.n > DENSE_FUSED_NC) return nl;
   for (int l = fused_level(ctx); l + 1 < nl; ++l) {
     CoarseArgs<T> a = coarse_args<T>(ctx, l);
-    if (coarse_stage_layout(a) <= (size_t)COARSE_LDS_MAX) return l;
+    if (coarse_pair(a) || coarse_stage_layout(a) <= (size_t)COARSE_LDS_MAX) return l;
   }
   return nl;
 }
