@@ -357,9 +357,7 @@ __global__ __launch_bounds__(256) void schur_build_kernel(Lay L, const double* _
 // of the mantissa, the row index below them: the lowest row of nearly equal
 // ones), which bounds the multipliers by 1 + 2^-12.
 // A 432-cell coarsest level (192x192x48) takes 403 us with the kernels around
-// it (383 here), where one launch per column of the whole operator took 2680;
-// 128 cells (128x128x32) take 66 us (50 here), 123 as one workgroup with S in
-// LDS and three barriers a step.
+// it (383 here), where one launch per column of the whole operator took 2680.
 template <int NB, int TR, int TC, int CR>
 __global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const double* __restrict__ S,
                                                                double* __restrict__ out, int* __restrict__ flag) {
@@ -459,6 +457,106 @@ __global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const dou
       if (r < nb && c < nb)
         out[(size_t)pcol[r] * nb + prow[c]] = get(a, b);
     }
+}
+
+// The same for nb <= 64 with a wavefront's lanes as the rows: wave w of four
+// holds columns 16 w .. 16 w + 15, sixteen values a lane, and a step costs one
+// barrier.  The pivot row is broadcast by scalar reads of its lane.  What
+// passes through LDS are the pivot column's values (the multipliers), the
+// pivot's row and reciprocal; the wave that owns column p + 1 finds them as
+// soon as it has updated that column, in one block of code with its other
+// updates, which hide the search and the division.  The wave whose columns
+// are eliminated moves them down one register a step, so that no loop needs a
+// register index and all stay rolled (unrolled over the columns the kernel
+// was bound by instruction fetch: 60 us).  One wave per SIMD is asked of the
+// compiler so that it overlaps the updates.  64 rows: 50 -> 38 us.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void schur_invert64_kernel(
+    int nb, const double* __restrict__ S, double* __restrict__ out, int* __restrict__ flag) {
+  __shared__ double col[2][64], pinv_s[2][64];
+  __shared__ int q_s[2][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double m[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const int cc = wave * 16 + c;
+    m[c] = lane < nb && cc < nb ? S[(size_t)lane * nb + cc] : 0.0;
+  }
+  auto bcast = [](double v, int q) {   // lane q's value to the wave
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q),
+                            __builtin_amdgcn_readlane(__double2loint(v), q));
+  };
+  bool used = lane >= nb, bad = false;
+  int prow = 0, pcol = 0;   // of this lane's column and row
+  // the pivot of column p from its values v (every lane stores it in a place
+  // of its own: stores of one address would go one after the other)
+  auto pivot = [&](int p, double v) {
+    const unsigned key = used ? 0u : (((unsigned)__double2hiint(v) & 0x7fffff00u) | (255u - (unsigned)lane)) + 1u;
+    const int q = __builtin_amdgcn_readfirstlane((int)((255u - ((wave_max(key) - 1u) & 255u)) & 63u));
+    const double pv = bcast(v, q);
+    bad |= !(fabs(pv) > TINY && fabs(pv) < HUGE_VAL);
+    col[p & 1][lane] = v;
+    q_s[p & 1][lane] = q;
+    pinv_s[p & 1][lane] = 1.0 / pv;
+  };
+  double f, pinv;
+  int q;
+  bool is_q;
+  auto begin = [&](int p) {
+    f = col[p & 1][lane];
+    pinv = pinv_s[p & 1][lane];
+    q = __builtin_amdgcn_readfirstlane(q_s[p & 1][lane]);
+    is_q = lane == q;
+    used |= is_q;
+    pcol = is_q ? p : pcol;
+    prow = lane == p ? q : prow;
+  };
+  auto update = [&](double v) {
+    const double pr = bcast(v, q) * pinv;
+    return is_q ? pr : v - f * pr;
+  };
+  const int lo = min(16 * wave, nb), hi = min(lo + 16, nb);
+  if (wave == 0) pivot(0, m[0]);
+  __syncthreads();
+  // the columns of the waves before this one, its own, and the others; each
+  // wave passes the barrier once a column
+  auto pass = [&](int p) {
+    begin(p);
+#pragma unroll
+    for (int c = 0; c < 16; ++c) m[c] = update(m[c]);
+  };
+  for (int p = 0; p + 1 < lo; ++p) {
+    pass(p);
+    __syncthreads();
+  }
+  if (lo > 0) {
+    pass(lo - 1);
+    if (lo < hi) pivot(lo, m[0]);
+    __syncthreads();
+  }
+  auto own = [&](int p, bool more) {
+    begin(p);
+    const double gone = is_q ? pinv : -(f * pinv), next = update(m[1]);
+    if (more) pivot(p + 1, next);
+    m[0] = next;
+#pragma unroll
+    for (int c = 2; c < 16; ++c) m[c - 1] = update(m[c]);
+    m[15] = gone;
+    __syncthreads();
+  };
+  for (int p = lo; p + 1 < hi; ++p) own(p, true);
+  if (lo < hi) own(hi - 1, false);
+  for (int p = hi; p < nb; ++p) {
+    pass(p);
+    __syncthreads();
+  }
+  const int moved = hi - lo;   // register c holds column (c + moved) mod 16
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const int cc = wave * 16 + ((c + moved) & 15);
+    const int to = __builtin_amdgcn_readlane(prow, cc);
+    if (lane < nb && cc < nb) out[(size_t)pcol * nb + to] = m[c];
+  }
+  if (bad) atomicExch(flag, 1);
 }
 
 // A^-1 (column major, and as FP32) from S^-1, one thread per entry.
@@ -623,6 +721,12 @@ __global__ void ilu_tiles_kernel(Lay L, int colour, const double* __restrict__ J
   }
 }
 
+// setup's flags to pinned memory (a copy to pageable memory would be staged
+// by the runtime and waited for there)
+__global__ void report_flags_kernel(const int* __restrict__ flag, int* __restrict__ host) {
+  if (threadIdx.x < 2) host[threadIdx.x] = flag[threadIdx.x];
+}
+
 __global__ void zero_int_kernel(int* p, int n) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < n) p[t] = 0;
@@ -740,7 +844,7 @@ int setup_cpr(cpr_ctx* ctx) {
     double* si = ctx->gj_work + (size_t)nb * nb;
     schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, a>>>(last.lay, last.A, sb, ctx->flag);
     if (nb <= 64) {
-      schur_invert_kernel<64, 16, 16, 4><<<1, 256, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_invert64_kernel<<<1, 256, 0, a>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 128) {
       schur_invert_kernel<128, 32, 16, 8><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 224) {
@@ -791,8 +895,9 @@ int setup_cpr(cpr_ctx* ctx) {
   CPR_TRY(hipStreamWaitEvent(s, ctx->ev_gj, 0));
   rc = launch_check(ctx, "cpr_setup kernels");
   if (rc != CPR_OK) return rc;
-  int hflag[2] = {0, 0};
-  CPR_TRY(hipMemcpyAsync(hflag, ctx->flag, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+  int* hflag = reinterpret_cast<int*>(ctx->hhost + 8);
+  report_flags_kernel<<<1, 64, 0, s>>>(ctx->flag, reinterpret_cast<int*>(ctx->hhost_dev + 8));
+  CPR_TRY(hipGetLastError());
   CPR_TRY(hipStreamSynchronize(s));
   ctx->qimpes_bad = hflag[1];
   if (hflag[0]) return set_err(ctx, CPR_ESINGULAR, "singular ILU diagonal block or coarsest operator");
