@@ -156,50 +156,63 @@ __global__ void abf_kernel(int n, const double* __restrict__ J, double* __restri
   }
 }
 
-// Galerkin coarse operator for piecewise-constant 2x2x2 aggregation: eight
-// lanes per coarse cell, one per fine cell of its aggregate, each sorting
-// its stencil row into the coarse couplings (inside the aggregate: the
-// diagonal); the eight partial rows are summed by a fixed butterfly.  Ghost
-// cells of a padded fine level take no part; a ghost coarse cell gets the
-// identity row.
+// Galerkin coarse operator for piecewise-constant 2x2x2 aggregation.  A
+// workgroup takes 64 consecutive coarse cells in natural order and its wave
+// (q, s) the fine rows (2cj+q, 2ck+s) under them, the two fine cells of its
+// row per lane, so that every load of a wave is one run of 64 of a colour
+// half (with eight lanes per coarse cell in storage order a load covered 16
+// short runs): 26 us for 192x192x48 cells, 3.8 TB/s.  A lane sorts its cells'
+// stencil rows into the coarse couplings (inside the aggregate: the diagonal);
+// the partial rows are summed in a fixed order, pairs along x, then y, then z.  Ghost cells of a padded fine level take no
+// part; a ghost coarse cell gets the identity row.
 __global__ __launch_bounds__(256) void rap_kernel(Lay F, Lay C, const double* __restrict__ Af,
                                                   double* __restrict__ Ac) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  const int tc = g >> 3, sub = g & 7;
-  double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+  __shared__ double sh[4][7][64];
+  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int cn = blockIdx.x * 64 + lane;
+  double p[2][7] = {};
   int ci = 0, cj = 0, ck = 0;
-  if (tc < C.n) {
-    lay_coords(C, tc, ci, cj, ck);
-    const int fi = 2 * ci + (sub & 1), fj = 2 * cj + ((sub >> 1) & 1), fk = 2 * ck + (sub >> 2);
-    if (fi < F.nxr && fj < F.ny && fk < F.nz) {
-      const int f = lay_index(F, fi, fj, fk);
-      acc[0] += Af[f];
+  if (cn < C.n) {
+    const int cjk = cn / C.nx;
+    ci = cn - cjk * C.nx;
+    ck = cjk / C.ny;
+    cj = cjk - ck * C.ny;
+    const int fj = 2 * cj + (sub & 1), fk = 2 * ck + (sub >> 1);
+    if (fj < F.ny && fk < F.nz) {
+      double a[2][7];
 #pragma unroll
-      for (int d = 1; d < 7; ++d) {
-        int di, dj, dk;
-        dir_offset(d, di, dj, dk);
-        const int gi = fi + di, gj = fj + dj, gk = fk + dk;
-        if (gi < 0 || gi >= F.nxr || gj < 0 || gj >= F.ny || gk < 0 || gk >= F.nz) continue;
-        const double a = Af[(size_t)d * F.n + f];
-        if ((gi >> 1) == ci && (gj >> 1) == cj && (gk >> 1) == ck)
-          acc[0] += a;
-        else
-          acc[d] += a;
+      for (int e = 0; e < 2; ++e) {
+        const int f = lay_index(F, min(2 * ci + e, F.nx - 1), fj, fk);
+#pragma unroll
+        for (int d = 0; d < 7; ++d) a[e][d] = Af[(size_t)d * F.n + f];
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int fi = 2 * ci + e;
+        if (fi >= F.nxr) continue;
+        p[e][0] += a[e][0];
+#pragma unroll
+        for (int d = 1; d < 7; ++d) {
+          int di, dj, dk;
+          dir_offset(d, di, dj, dk);
+          const int gi = fi + di, gj = fj + dj, gk = fk + dk;
+          if (gi < 0 || gi >= F.nxr || gj < 0 || gj >= F.ny || gk < 0 || gk >= F.nz) continue;
+          if ((gi >> 1) == ci && (gj >> 1) == cj && (gk >> 1) == ck)
+            p[e][0] += a[e][d];
+          else
+            p[e][d] += a[e][d];
+        }
       }
     }
   }
 #pragma unroll
-  for (int d = 0; d < 7; ++d) {
-    acc[d] += __shfl_xor(acc[d], 1, 8);
-    acc[d] += __shfl_xor(acc[d], 2, 8);
-    acc[d] += __shfl_xor(acc[d], 4, 8);
-  }
-  if (tc < C.n && sub == 0) {
-    if (ci >= C.nxr) {
-      acc[0] = 1.0;
-      for (int d = 1; d < 7; ++d) acc[d] = 0.0;
-    }
-    for (int d = 0; d < 7; ++d) Ac[(size_t)d * C.n + tc] = acc[d];
+  for (int d = 0; d < 7; ++d) sh[sub][d][lane] = p[0][d] + p[1][d];
+  __syncthreads();
+  if (cn >= C.n) return;
+  const int tc = lay_index(C, ci, cj, ck);
+  for (int d = sub; d < 7; d += 4) {
+    const double v = (sh[0][d][lane] + sh[1][d][lane]) + (sh[2][d][lane] + sh[3][d][lane]);
+    Ac[(size_t)d * C.n + tc] = ci < C.nxr ? v : d == 0 ? 1.0 : 0.0;
   }
 }
 
@@ -824,17 +837,20 @@ int setup_cpr(cpr_ctx* ctx) {
   }
   // rows >= 1 of the decoupled blocks: the Jacobian's own (quasi-IMPES) or D^-1 A (ABF)
   const double* Jdec = abf ? ctx->Jt : ctx->J;
-  // Galerkin chain and coarsest inverse on the auxiliary stream, the ILU
-  // factorisation meanwhile on the caller's stream
+  // Galerkin chain and coarsest inverse on the auxiliary stream.  The ILU
+  // factorisation on the caller's stream overlaps the inverse only, a serial
+  // chain in one workgroup: its kernels flood the chip, so that the Galerkin
+  // kernels beside them took as long as it did and the inverse's workgroup got
+  // its place when they had drained (192x192x48: 288 against 26 us and the
+  // inverse done 970 against 450 us after the decoupling).
   hipStream_t a = ctx->aux;
   CPR_TRY(hipEventRecord(ctx->ev_q, s));
   CPR_TRY(hipStreamWaitEvent(a, ctx->ev_q, 0));
   for (size_t l = 0; l + 1 < ctx->levels.size(); ++l) {
     const MGLevel& F = ctx->levels[l];
     MGLevel& C = ctx->levels[l + 1];
-    rap_kernel<<<div_up(8L * C.lay.n, 256), 256, 0, a>>>(F.lay, C.lay, F.A, C.A);
+    rap_kernel<<<div_up(C.lay.n, 64), 256, 0, a>>>(F.lay, C.lay, F.A, C.A);
   }
-  CPR_TRY(hipEventRecord(ctx->ev_rap, a));
   // dense inverse of the coarsest level
   const MGLevel& last = ctx->levels.back();
   int nc = last.lay.n;
@@ -843,6 +859,7 @@ int setup_cpr(cpr_ctx* ctx) {
     double* sb = ctx->gj_work;
     double* si = ctx->gj_work + (size_t)nb * nb;
     schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, a>>>(last.lay, last.A, sb, ctx->flag);
+    CPR_TRY(hipEventRecord(ctx->ev_rap, a));
     if (nb <= 64) {
       schur_invert64_kernel<<<1, 256, 0, a>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 128) {
@@ -857,6 +874,7 @@ int setup_cpr(cpr_ctx* ctx) {
     }
     schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, a>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
   } else {
+    CPR_TRY(hipEventRecord(ctx->ev_rap, a));
     double* bufA = ctx->gj_work;
     double* bufB = ctx->gj_work + (size_t)nc * 2 * nc;
     dense_build_kernel<<<div_up(nc, 256), 256, 0, a>>>(last.lay, last.A, bufA);
@@ -869,6 +887,7 @@ int setup_cpr(cpr_ctx* ctx) {
     gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, a>>>(nc, bufA, ctx->cinv, ctx->cinvf);
   }
   CPR_TRY(hipEventRecord(ctx->ev_gj, a));
+  CPR_TRY(hipStreamWaitEvent(s, ctx->ev_rap, 0));
   // block ILU(0): red diagonals (cells or tiles) first, black ones use them
   const bool tiles = ctx->opt.ilu_order == CPR_ILU_TILES;
   const int nh = tiles ? (int)div_up(tile_threads(L), 64) : div_up(L.nh, 64);
@@ -888,10 +907,7 @@ int setup_cpr(cpr_ctx* ctx) {
       ilu_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
     }
   }
-  if (ctx->opt.precision == CPR_PREC_MIXED) {
-    CPR_TRY(hipStreamWaitEvent(s, ctx->ev_rap, 0));   // FP32 copies of the levels
-    launch_mixed_copies(ctx);
-  }
+  if (ctx->opt.precision == CPR_PREC_MIXED) launch_mixed_copies(ctx);
   CPR_TRY(hipStreamWaitEvent(s, ctx->ev_gj, 0));
   rc = launch_check(ctx, "cpr_setup kernels");
   if (rc != CPR_OK) return rc;
