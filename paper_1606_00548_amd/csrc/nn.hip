@@ -60,17 +60,21 @@ struct Geo {
 // 1x1x1 head is applied to a + skip and only y is stored.  EPI 0: raw acc in
 // outA (data gradient).
 //
-// Implicit GEMM on v_mfma_f32_16x16x32_bf16: M = voxels, N = output
-// channels, K = (tap, input channel) in steps of 32.  A workgroup (4 waves)
-// owns a tile of 16 x 4 x TZ output voxels and CO/NS of the output
-// channels.  At the start it stages, with all loads in flight together,
-// the input it needs (tile plus a one-voxel halo, or the half-resolution
-// cells under it when UP) in LDS as BF16, and the B-fragments of its
-// channels for every K-step; each input value is then read from memory
-// about 2-3 times instead of 27, and the K loop touches LDS only.  With
-// KS = 1 each wave owns one z-plane of the tile (4 M-blocks of 16 voxels
-// along x) and every K-step; with KS = 4 (small grids, to keep enough waves
-// in flight) the tile is one plane and the waves split the K-steps
+// Implicit GEMM on v_mfma_f32_16x16x32_bf16: M = output channels, N = voxels,
+// K = (tap, input channel) in steps of 32, so that a lane of a result holds
+// four consecutive channels of one voxel and biases, skips, activations and
+// pools move as 16-byte values.  A workgroup (4 waves) owns CO/NS of the
+// output channels, whose weight fragments it stages in LDS once, and with
+// KS = 1 several tiles of 16 x 4 x 4 output voxels one after the other (as
+// many workgroups as the chip holds).  Of a tile it stages the input (tile
+// plus a one-voxel halo, or the half-resolution cells under it when UP) in
+// LDS as BF16; the next tile's loads are in flight during the K loop, which
+// touches LDS only (with one tile per workgroup the loads' and the weights'
+// latency stood before every K loop: one sample of 128x128x64, the convolution
+// at full resolution 59 -> 33 us, all seven 170 -> 128 us).
+// Each wave owns one z-plane of the tile (4 N-blocks of 16 voxels along x)
+// and every K-step; with KS = 4 (small grids, to keep enough waves in flight)
+// the workgroup has one tile of one plane and the waves split the K-steps
 // round-robin, their partial tiles summed in LDS in wave order, so results
 // are deterministic either way.  POOL (KS = 1 only): the workgroup also
 // writes the 2x2x2 average of its activations, which its tile holds whole.
@@ -103,59 +107,74 @@ struct ConvArgs {
   const double* xscale;  // CSRC = 3: device scalar multiplying input channel 2 as it is loaded, or null
 };
 
+template <int CI, bool UP, int KS>
+struct ConvTile {
+  static constexpr int TZ = 4 / KS;
+  static constexpr int HX = UP ? TX / 2 + 2 : TX + 2, HY = UP ? TY / 2 + 2 : TY + 2, HZ = UP ? TZ / 2 + 2 : TZ + 2;
+  static constexpr int HV = HX * HY * HZ;
+  // halo voxel stride in bytes: padded by 16 bytes for CI >= 16 so that 16
+  // lanes reading 16 bytes of 16 neighbouring voxels hit distinct banks
+  static constexpr int VB = (CI >= 16 ? CI + 8 : CI) * 2;
+};
+template <int CI, int CO, bool UP, int KS, int NS>
+__host__ __device__ constexpr int conv_lds() {
+  constexpr int main = ConvTile<CI, UP, KS>::HV * ConvTile<CI, UP, KS>::VB + ksteps(CI) * (CO / NS) * 64;
+  constexpr int red = KS > 1 ? KS * 64 * (CO / NS) * 4 : 0;
+  return main > red ? main : red;
+}
+// workgroups a CU holds of a convolution that walks over tiles
+constexpr int CUS = 256, CU_LDS = 160 * 1024;
+template <int CI, int CO, bool UP, int KS, int NS>
+__host__ __device__ constexpr int conv_per_cu() {
+  constexpr int fit = CU_LDS / conv_lds<CI, CO, UP, KS, NS>();
+  return KS > 1 ? 1 : fit < 4 ? fit : 4;
+}
+
 template <int CI, int CSRC, int CO, bool UP, int EPI, int KS, int NS, bool POOL>
-__global__ __launch_bounds__(256) void conv_kernel(ConvArgs p) {
+__global__ __launch_bounds__(256, (conv_per_cu<CI, CO, UP, KS, NS>())) void conv_kernel(ConvArgs p) {
   static_assert(KS == 1 || KS == 4, "K split is 1 or 4");
   static_assert(CI == 4 || CI == 16 || CI % 32 == 0, "channel layout");
   static_assert(CO % (16 * NS) == 0, "channel split");
   static_assert(!POOL || KS == 1, "pooling needs whole 2x2x2 cells in the tile");
-  constexpr int TZ = 4 / KS;
-  constexpr int HX = UP ? TX / 2 + 2 : TX + 2;
-  constexpr int HY = UP ? TY / 2 + 2 : TY + 2;
-  constexpr int HZ = UP ? TZ / 2 + 2 : TZ + 2;
-  constexpr int HV = HX * HY * HZ;
+  using Tile = ConvTile<CI, UP, KS>;
+  constexpr int TZ = Tile::TZ, HX = Tile::HX, HY = Tile::HY, HV = Tile::HV, VB = Tile::VB;
   constexpr int NK = ksteps(CI);
-  constexpr int NT = CO / 16;          // N-blocks of the whole convolution
+  constexpr int NT = CO / 16;          // M-blocks of the whole convolution
   constexpr int COB = CO / NS;         // output channels of this workgroup
   constexpr int NTB = COB / 16;
-  // halo voxel stride in BF16 values: padded by 16 bytes for CI >= 16 so
-  // that 16 lanes reading 16 bytes of 16 neighbouring voxels hit distinct banks
-  constexpr int CST = CI >= 16 ? CI + 8 : CI;
-  constexpr int VB = CST * 2;
   constexpr int HALO_BYTES = HV * VB;
-  constexpr int W_BYTES = NK * NTB * 64 * 16;
-  constexpr int RED_BYTES = KS > 1 ? KS * 64 * COB * 4 : 0;
-  constexpr int POOL_BYTES = POOL ? 64 * COB * 4 : 0;
-  constexpr int MAIN_BYTES = HALO_BYTES + W_BYTES;
-  constexpr int SMEM = MAIN_BYTES > RED_BYTES ? (MAIN_BYTES > POOL_BYTES ? MAIN_BYTES : POOL_BYTES)
-                                              : (RED_BYTES > POOL_BYTES ? RED_BYTES : POOL_BYTES);
-  __shared__ __align__(16) unsigned char smem[SMEM];
+  static_assert(HALO_BYTES % 16 == 0 && (!POOL || 64 * COB * 4 <= HALO_BYTES), "pool sums reuse the halo");
+  __shared__ __align__(16) unsigned char smem[conv_lds<CI, CO, UP, KS, NS>()];
   const bf16x8* wl = (const bf16x8*)(smem + HALO_BYTES);
   const Geo& g = p.g;
 
-  // (tile, channel block) of this workgroup; consecutive blocks go to the
+  // channel block and tiles of this workgroup; consecutive ones go to the
   // same XCD, and the channel blocks of a tile are neighbours
   const int ntx = (g.nx + TX - 1) / TX, nty = (g.ny + TY - 1) / TY, ntz = (g.nz + TZ - 1) / TZ;
-  const int nblocks = ntx * nty * ntz * g.batch * NS;
+  const int ntiles = ntx * nty * ntz * g.batch;
   int blk = blockIdx.x;
-  if ((nblocks & 7) == 0) blk = (blockIdx.x & 7) * (nblocks >> 3) + (blockIdx.x >> 3);
-  const int nb = blk % NS, tile = blk / NS;
-  const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = (tile / (ntx * nty)) % ntz, b = tile / (ntx * nty * ntz);
-  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
+  if ((gridDim.x & 7) == 0) blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int nb = blk % NS, walkers = gridDim.x / NS;
+  const int tile0 = (int)((long)(blk / NS) * ntiles / walkers), tile1 = (int)((long)(blk / NS + 1) * ntiles / walkers);
+  int x0, y0, z0, b;
+  auto locate = [&](int tile) {
+    x0 = tile % ntx * TX;
+    y0 = (tile / ntx) % nty * TY;
+    z0 = (tile / (ntx * nty)) % ntz * TZ;
+    b = tile / (ntx * nty * ntz);
+  };
 
-  // stage the input window as BF16 (zero outside the grid) and this
-  // block's weight fragments, eight loads per thread in flight
   const int sx = UP ? g.nx >> 1 : g.nx, sy = UP ? g.ny >> 1 : g.ny, sz = UP ? g.nz >> 1 : g.nz;
-  const int ox = UP ? (x0 - 1) >> 1 : x0 - 1, oy = UP ? (y0 - 1) >> 1 : y0 - 1, oz = UP ? (z0 - 1) >> 1 : z0 - 1;
-  const float* Xb = p.X + (long)b * sx * sy * sz * CSRC;
   const float xs2 = (CSRC != CI && p.xscale) ? (float)*p.xscale : 1.f;
-  constexpr int NQ = HV * (CI / 4);
-  constexpr int NWF = NK * NTB * 64;
-  for (int q0 = 0; q0 < NQ; q0 += 8 * 256) {
-    float4 v[8];
+  constexpr int NQ = HV * (CI / 4), NU = (NQ + 255) / 256;
+  // the input window of a tile, NU quads of channels per thread (zero outside
+  // the grid)
+  auto fetch = [&](float4(&v)[NU]) {
+    const int ox = UP ? (x0 - 1) >> 1 : x0 - 1, oy = UP ? (y0 - 1) >> 1 : y0 - 1, oz = UP ? (z0 - 1) >> 1 : z0 - 1;
+    const float* Xb = p.X + (long)b * sx * sy * sz * CSRC;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * 256 + threadIdx.x;
+    for (int u = 0; u < NU; ++u) {
+      const int q = u * 256 + threadIdx.x;
       v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (q < NQ) {
         const int hv = q / (CI / 4), c4 = (q % (CI / 4)) * 4;
@@ -166,246 +185,301 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs p) {
           if (CSRC == CI) {
             v[u] = *(const float4*)src;
           } else {
-            v[u].x = src[0]; v[u].y = src[1]; v[u].z = src[2] * xs2;
+            v[u].x = src[0]; v[u].y = src[1]; v[u].z = src[2];
+            v[u].w = 1.f;   // inside the grid (the fourth channel is padding)
           }
         }
       }
     }
+  };
+  auto place = [&](const float4(&v)[NU]) {   // the same as BF16 into LDS
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * 256 + threadIdx.x;
+    for (int u = 0; u < NU; ++u) {
+      const int q = u * 256 + threadIdx.x;
+      const float z = CSRC == CI ? v[u].z : v[u].w != 0.f ? v[u].z * xs2 : 0.f;
+      const float w = CSRC == CI ? v[u].w : 0.f;
       if (q < NQ)
         *(uint2*)(smem + (size_t)(q / (CI / 4)) * VB + (q % (CI / 4)) * 8) =
-            make_uint2(pack_bf16x2(v[u].x, v[u].y), pack_bf16x2(v[u].z, v[u].w));
+            make_uint2(pack_bf16x2(v[u].x, v[u].y), pack_bf16x2(z, w));
     }
-  }
-  for (int q0 = 0; q0 < NWF; q0 += 8 * 256) {
-    bf16x8 w[8];
+  };
+  // a tile's quads (at most 21 a thread) are loaded a tile ahead, those of the
+  // first together with the weights (at most 14 fragments a thread): one
+  // round trip to memory before the first K loop
+  float4 v[NU];
+  locate(tile0);
+  if (tile0 < tile1) fetch(v);
+  {
+    constexpr int NWF = NK * NTB * 64, WU = (NWF + 255) / 256;
+    bf16x8 w[WU];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * 256 + threadIdx.x;
+    for (int u = 0; u < WU; ++u) {
+      const int q = u * 256 + threadIdx.x;
       if (q < NWF) {
         const int ks = q / (NTB * 64), j = (q / 64) % NTB, lane = q % 64;
         w[u] = p.W[((size_t)ks * NT + nb * NTB + j) * 64 + lane];
       }
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * 256 + threadIdx.x;
+    for (int u = 0; u < WU; ++u) {
+      const int q = u * 256 + threadIdx.x;
       if (q < NWF) ((bf16x8*)(smem + HALO_BYTES))[q] = w[u];
     }
   }
-  __syncthreads();
 
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the K split branches on it
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
   const int lz = KS == 1 ? wave : 0;
-  // Byte address in the halo of the input under output voxel (i16, m, lz)
-  // at tap (dx, dy, dz) = per-lane part + a part known at compile time once
-  // the K loop is unrolled (folded into the LDS instructions' offsets).
-  // Same grid: (i16 + 1 + dx) + HX (m + 1 + dy) + HX HY (lz + 1 + dz).
-  // UP (x0, y0 multiples of 16 and 4): ((i16 + dx) >> 1) + 1 along x,
-  // ((m + dy) >> 1) + 1 along y, and ((z0 + lz + dz) >> 1) - ((z0 - 1) >> 1)
-  // along z, which depends on z0 and is uniform over the wave.
-  const int lane_chunk = CI >= 32 ? 16 * kq : (CI == 16 ? 16 * (kq & 1) : 0);
-  int base = 0;            // same grid
-  int upb[3][3] = {};      // UP: [dx + 1][dz + 1]
-  if constexpr (UP) {
-#pragma unroll
-    for (int ddx = 0; ddx < 3; ++ddx)
-#pragma unroll
-      for (int ddz = 0; ddz < 3; ++ddz) {
-        const int zc = ((z0 + lz + ddz - 1) >> 1) - oz;
-        upb[ddx][ddz] = ((((i16 + ddx - 1) >> 1) + 1) + HX * HY * zc) * VB + lane_chunk;
-      }
-  } else {
-    base = ((i16 + 1) + HX + HX * HY * (lz + 1)) * VB + lane_chunk;
-  }
-  // KS = 1 with a skip input: its values for this wave's outputs are loaded
-  // before the K loop so that their latency hides behind the MFMAs
   const long V = g.V;
-  const int c0 = nb * COB;
-  float skv[KS == 1 && EPI == 1 ? 4 : 1][4][NTB];
-  if constexpr (KS == 1 && EPI == 1) {
-    const bool has_skip = p.skip != nullptr;
+  const int c0 = nb * COB + 4 * kq;   // first channel of this lane in M-block 0
+  float4 bias[NTB] = {};
+  if constexpr (EPI == 1) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int x = x0 + 4 * kq + e, y = y0 + m, z = z0 + lz;
-        const bool ok = has_skip && x < g.nx && y < g.ny && z < g.nz;
-        const long o = (long)b * V + x + (long)g.nx * (y + (long)g.ny * z);
-#pragma unroll
-        for (int n = 0; n < NTB; ++n) skv[m][e][n] = ok ? p.skip[o * CO + c0 + n * 16 + i16] : 0.f;
-      }
+    for (int n = 0; n < NTB; ++n)
+      bias[n] = make_float4(p.bias[c0 + n * 16], p.bias[c0 + n * 16 + 1], p.bias[c0 + n * 16 + 2],
+                            p.bias[c0 + n * 16 + 3]);
   }
-  f32x4 acc[4][NTB];
+
+  for (int tile = tile0; tile < tile1; ++tile) {
+    if (tile > tile0) __syncthreads();   // the tile before no longer needs the halo
+    place(v);
+    __syncthreads();
+
+    // Byte address in the halo of the input under output voxel (i16, m, lz)
+    // at tap (dx, dy, dz) = per-lane part + a part known at compile time once
+    // the K loop is unrolled (folded into the LDS instructions' offsets).
+    // Same grid: (i16 + 1 + dx) + HX (m + 1 + dy) + HX HY (lz + 1 + dz).
+    // UP (x0, y0 multiples of 16 and 4): ((i16 + dx) >> 1) + 1 along x,
+    // ((m + dy) >> 1) + 1 along y, and ((z0 + lz + dz) >> 1) - ((z0 - 1) >> 1)
+    // along z, which depends on z0 and is uniform over the wave.
+    const int lane_chunk = CI >= 32 ? 16 * kq : (CI == 16 ? 16 * (kq & 1) : 0);
+    int base = 0;            // same grid
+    int upb[3][3] = {};      // UP: [dx + 1][dz + 1]
+    if constexpr (UP) {
+      const int oz = (z0 - 1) >> 1;
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+      for (int ddx = 0; ddx < 3; ++ddx)
 #pragma unroll
-    for (int n = 0; n < NTB; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // same-grid tap offset (bytes) relative to base, m = 0
-  auto toff = [](int t) { return ((t % 3 - 1) + HX * ((t / 3) % 3 - 1) + HX * HY * (t / 9 - 1)) * VB; };
-  if constexpr (CI >= 32) {
-    // K-steps grouped by (dz, dx, channel chunk): the three dy taps of a
-    // group read the same input rows, so the wave loads each row's A
-    // fragment once (6 rows of the tile plus halo, or 4 half-resolution
-    // rows when UP) and the three B-fragments, then issues 12 MFMA per
-    // N-block.  Groups are split over the waves when KS = 4.
-    constexpr int NCH = CI / 32;
-    constexpr int NR = UP ? 4 : 6;
-#pragma unroll
-    for (int grp = 0; grp < 9 * NCH; ++grp) {
-      if (KS > 1 && (grp % KS) != wave) continue;
-      const int kc = grp % NCH, dx = (grp / NCH) % 3 - 1, dz = grp / (3 * NCH) - 1;
-      bf16x8 bw[3][NTB];
-#pragma unroll
-      for (int ddy = 0; ddy < 3; ++ddy)
-#pragma unroll
-        for (int n = 0; n < NTB; ++n)
-          bw[ddy][n] = wl[((size_t)(((dz + 1) * 9 + ddy * 3 + (dx + 1)) * NCH + kc) * NTB + n) * 64 + lane];
-      bf16x8 ar[NR];
-#pragma unroll
-      for (int yy = 0; yy < NR; ++yy) {
-        int addr;
-        if constexpr (UP)
-          addr = upb[dx + 1][dz + 1] + HX * yy * VB + kc * 64;
-        else
-          addr = base + (dx + HX * HY * dz) * VB + HX * (yy - 1) * VB + kc * 64;
-        ar[yy] = __builtin_bit_cast(bf16x8, *(const uint4*)(smem + addr));
-      }
+        for (int ddz = 0; ddz < 3; ++ddz) {
+          const int zc = ((z0 + lz + ddz - 1) >> 1) - oz;
+          upb[ddx][ddz] = ((((i16 + ddx - 1) >> 1) + 1) + HX * HY * zc) * VB + lane_chunk;
+        }
+    } else {
+      base = ((i16 + 1) + HX + HX * HY * (lz + 1)) * VB + lane_chunk;
+    }
+    // this lane's outputs: voxel (x, y0 + m, z), channels c0 + 16 n ...
+    const int x = x0 + i16, z = z0 + lz, ty = y0;
+    const long o0 = (long)b * V + x + (long)g.nx * (ty + (long)g.ny * z);
+    const bool oxz = x < g.nx && z < g.nz;
+    // KS = 1 with a skip input: its values are loaded before the K loop so
+    // that their latency hides behind the MFMAs
+    float4 skv[KS == 1 && EPI == 1 ? 4 : 1][NTB];
+    if constexpr (KS == 1 && EPI == 1) {
+      const bool has_skip = p.skip != nullptr;
 #pragma unroll
       for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int ddy = 0; ddy < 3; ++ddy) {
-          const int yy = UP ? ((m + ddy - 1) >> 1) + 1 : m + ddy;
+        for (int n = 0; n < NTB; ++n)
+          skv[m][n] = has_skip && oxz && ty + m < g.ny
+                          ? *(const float4*)(p.skip + (o0 + (long)m * g.nx) * CO + c0 + n * 16)
+                          : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    const int tx0 = x0, tz0 = z0, tb = b;
+    if (tile + 1 < tile1) {
+      locate(tile + 1);
+      fetch(v);
+    }
+    f32x4 acc[4][NTB];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int n = 0; n < NTB; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // same-grid tap offset (bytes) relative to base, m = 0
+    auto toff = [](int t) { return ((t % 3 - 1) + HX * ((t / 3) % 3 - 1) + HX * HY * (t / 9 - 1)) * VB; };
+    if constexpr (CI >= 32) {
+      // K-steps grouped by (dz, dx, channel chunk): the three dy taps of a
+      // group read the same input rows, so the wave loads each row's voxel
+      // fragment once (6 rows of the tile plus halo, or 4 half-resolution
+      // rows when UP) and the three weight fragments, then issues 12 MFMA per
+      // M-block.  Groups are split over the waves when KS = 4.
+      constexpr int NCH = CI / 32;
+      constexpr int NR = UP ? 4 : 6;
+      auto group = [&](int kc, int dx, int dz, int row0) {   // row0: address of the first row
+        bf16x8 bw[3][NTB];
+#pragma unroll
+        for (int ddy = 0; ddy < 3; ++ddy)
 #pragma unroll
           for (int n = 0; n < NTB; ++n)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[yy], bw[ddy][n], acc[m][n], 0, 0, 0);
+            bw[ddy][n] = wl[(((dz + 1) * 9 + ddy * 3 + (dx + 1)) * NCH + kc) * NTB * 64 + n * 64 + lane];
+        bf16x8 ar[NR];
+#pragma unroll
+        for (int yy = 0; yy < NR; ++yy)
+          ar[yy] = __builtin_bit_cast(bf16x8, *(const uint4*)(smem + row0 + HX * yy * VB + kc * 64));
+#pragma unroll
+        for (int ddy = 0; ddy < 3; ++ddy)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            const int yy = UP ? ((m + ddy - 1) >> 1) + 1 : m + ddy;
+#pragma unroll
+            for (int n = 0; n < NTB; ++n)
+              acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[ddy][n], ar[yy], acc[m][n], 0, 0, 0);
+          }
+      };
+      if constexpr (KS == 1) {
+#pragma unroll
+        for (int grp = 0; grp < 9 * NCH; ++grp) {
+          const int kc = grp % NCH, dx = (grp / NCH) % 3 - 1, dz = grp / (3 * NCH) - 1;
+          group(kc, dx, dz, UP ? upb[dx + 1][dz + 1] : base + (dx + HX * HY * dz - HX) * VB);
         }
-    }
-  } else {
-#pragma unroll
-  for (int ks = 0; ks < NK; ++ks) {
-    if (KS > 1 && (ks % KS) != wave) continue;
-    bf16x8 bw[NTB];
-#pragma unroll
-    for (int n = 0; n < NTB; ++n) bw[n] = wl[((size_t)ks * NTB + n) * 64 + lane];
-    int sel0 = 0, sel1 = 0;     // per-lane tap offsets of this step
-    if constexpr (CI == 16) {
-      sel0 = (kq >> 1) ? toff(min(2 * ks + 1, 26)) : toff(2 * ks);
-    } else {
-      const int ta[4] = {min(8 * ks, 26), min(8 * ks + 2, 26), min(8 * ks + 4, 26), min(8 * ks + 6, 26)};
-      const int tb[4] = {min(8 * ks + 1, 26), min(8 * ks + 3, 26), min(8 * ks + 5, 26), min(8 * ks + 7, 26)};
-      sel0 = kq == 0 ? toff(ta[0]) : kq == 1 ? toff(ta[1]) : kq == 2 ? toff(ta[2]) : toff(ta[3]);
-      sel1 = kq == 0 ? toff(tb[0]) : kq == 1 ? toff(tb[1]) : kq == 2 ? toff(tb[2]) : toff(tb[3]);
-    }
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      uint4 raw;
-      if constexpr (CI == 16) {
-        raw = *(const uint4*)(smem + base + sel0 + HX * m * VB);
       } else {
-        const uint2 lo = *(const uint2*)(smem + base + sel0 + HX * m * VB);
-        const uint2 hi = *(const uint2*)(smem + base + sel1 + HX * m * VB);
-        raw = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        // rolled: a wave runs every fourth group once, so that unrolled code
+        // would be fetched for each of them
+        for (int grp = wave; grp < 9 * NCH; grp += KS) {
+          const int kc = grp % NCH, dx = (grp / NCH) % 3 - 1, dz = grp / (3 * NCH) - 1;
+          const int up = ((((i16 + dx) >> 1) + 1) + HX * HY * (((tz0 + dz) >> 1) - ((tz0 - 1) >> 1))) * VB + lane_chunk;
+          group(kc, dx, dz, UP ? up : base + (dx + HX * HY * dz - HX) * VB);
+        }
       }
-      const bf16x8 a = __builtin_bit_cast(bf16x8, raw);
+    } else {
 #pragma unroll
-      for (int n = 0; n < NTB; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[n], acc[m][n], 0, 0, 0);
+      for (int ks = 0; ks < NK; ++ks) {
+        if (KS > 1 && (ks % KS) != wave) continue;
+        bf16x8 bw[NTB];
+#pragma unroll
+        for (int n = 0; n < NTB; ++n) bw[n] = wl[((size_t)ks * NTB + n) * 64 + lane];
+        int sel0 = 0, sel1 = 0;     // per-lane tap offsets of this step
+        if constexpr (CI == 16) {
+          sel0 = (kq >> 1) ? toff(min(2 * ks + 1, 26)) : toff(2 * ks);
+        } else {
+          const int ta[4] = {min(8 * ks, 26), min(8 * ks + 2, 26), min(8 * ks + 4, 26), min(8 * ks + 6, 26)};
+          const int tb4[4] = {min(8 * ks + 1, 26), min(8 * ks + 3, 26), min(8 * ks + 5, 26), min(8 * ks + 7, 26)};
+          sel0 = kq == 0 ? toff(ta[0]) : kq == 1 ? toff(ta[1]) : kq == 2 ? toff(ta[2]) : toff(ta[3]);
+          sel1 = kq == 0 ? toff(tb4[0]) : kq == 1 ? toff(tb4[1]) : kq == 2 ? toff(tb4[2]) : toff(tb4[3]);
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          uint4 raw;
+          if constexpr (CI == 16) {
+            raw = *(const uint4*)(smem + base + sel0 + HX * m * VB);
+          } else {
+            const uint2 lo = *(const uint2*)(smem + base + sel0 + HX * m * VB);
+            const uint2 hi = *(const uint2*)(smem + base + sel1 + HX * m * VB);
+            raw = make_uint4(lo.x, lo.y, hi.x, hi.y);
+          }
+          const bf16x8 a = __builtin_bit_cast(bf16x8, raw);
+#pragma unroll
+          for (int n = 0; n < NTB; ++n)
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[n], a, acc[m][n], 0, 0, 0);
+        }
+      }
     }
-  }
-  }
 
-  if constexpr (KS == 1) {
-    // C element (row 4*kq + e, column i16) of M-block m, N-block n is
-    // voxel (x0 + 4*kq + e, y0 + m, z0 + lz), channel c0 + n*16 + i16
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int y = y0 + m, z = z0 + lz;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int x = x0 + 4 * kq + e;
-        const bool ok = x < g.nx && y < g.ny && z < g.nz;
-        const long o = (long)b * V + x + (long)g.nx * (y + (long)g.ny * z);
+      for (int m = 0; m < 4; ++m) {
+        const bool ok = oxz && ty + m < g.ny;
+        const long o = o0 + (long)m * g.nx;
         if constexpr (EPI == 1 && CO == 16) {
           if (p.head) {
             // y = sum_c head[c] (relu(acc + bias) + skip)[c] + head[CO]
-            const float a = fmaxf(acc[m][0][e] + p.bias[i16], 0.f) + skv[m][e][0];
-            float h = a * p.head[i16];
-            h += __shfl_xor(h, 8, 16);
-            h += __shfl_xor(h, 4, 16);
-            h += __shfl_xor(h, 2, 16);
-            h += __shfl_xor(h, 1, 16);
-            if (ok && i16 == 0) p.y[o] = h + p.head[CO];
+            const f32x4 a = acc[m][0];
+            const float4 k = skv[m][0];
+            float h = (fmaxf(a[0] + bias[0].x, 0.f) + k.x) * p.head[c0];
+            h += (fmaxf(a[1] + bias[0].y, 0.f) + k.y) * p.head[c0 + 1];
+            h += (fmaxf(a[2] + bias[0].z, 0.f) + k.z) * p.head[c0 + 2];
+            h += (fmaxf(a[3] + bias[0].w, 0.f) + k.w) * p.head[c0 + 3];
+            h += __shfl_xor(h, 32);
+            h += __shfl_xor(h, 16);
+            if (ok && kq == 0) p.y[o] = h + p.head[CO];
             continue;
           }
         }
 #pragma unroll
         for (int n = 0; n < NTB; ++n) {
-          const int co = c0 + n * 16 + i16;
-          float val = acc[m][n][e];
+          const long oc = o * CO + c0 + n * 16;
+          f32x4& r = acc[m][n];
           if constexpr (EPI == 1) {
-            val = fmaxf(val + p.bias[co], 0.f);
-            acc[m][n][e] = val;
+            r[0] = fmaxf(r[0] + bias[n].x, 0.f);
+            r[1] = fmaxf(r[1] + bias[n].y, 0.f);
+            r[2] = fmaxf(r[2] + bias[n].z, 0.f);
+            r[3] = fmaxf(r[3] + bias[n].w, 0.f);
             if (!ok) continue;
-            if (p.outA) p.outA[o * CO + co] = val;
-            if (p.skip) p.outD[o * CO + co] = val + skv[m][e][n];
+            const float4 k = skv[m][n];
+            if (p.outA) *(float4*)(p.outA + oc) = make_float4(r[0], r[1], r[2], r[3]);
+            if (p.skip) *(float4*)(p.outD + oc) = make_float4(r[0] + k.x, r[1] + k.y, r[2] + k.z, r[3] + k.w);
           } else if (ok) {
-            p.outA[o * CO + co] = val;
+            *(float4*)(p.outA + oc) = make_float4(r[0], r[1], r[2], r[3]);
           }
         }
       }
-    }
-    if constexpr (POOL) {
-      // 2x2 (x, y) sums in registers, the z pairs (waves 2k, 2k+1) via LDS
-      __syncthreads();
-      float* ps = (float*)smem;   // [lz][py][px][COB]
+      if constexpr (POOL) {
+        // 2x2 (x, y) sums of neighbouring lanes and registers, the z pairs
+        // (waves 2k, 2k+1) via LDS
+        __syncthreads();
+        float4* ps = (float4*)smem;   // [lz][py][px][COB / 4]
 #pragma unroll
-      for (int py = 0; py < 2; ++py)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int py = 0; py < 2; ++py)
 #pragma unroll
           for (int n = 0; n < NTB; ++n) {
-            const float sum = (acc[2 * py][n][2 * q] + acc[2 * py][n][2 * q + 1]) +
-                              (acc[2 * py + 1][n][2 * q] + acc[2 * py + 1][n][2 * q + 1]);
-            ps[((lz * 2 + py) * 8 + 2 * kq + q) * COB + n * 16 + i16] = sum;
+            float sum[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float lo = acc[2 * py][n][e], hi = acc[2 * py + 1][n][e];
+              sum[e] = (lo + __shfl_xor(lo, 1)) + (hi + __shfl_xor(hi, 1));
+            }
+            if (!(i16 & 1))
+              ps[((lz * 2 + py) * 8 + (i16 >> 1)) * (COB / 4) + n * 4 + kq] =
+                  make_float4(sum[0], sum[1], sum[2], sum[3]);
           }
-      __syncthreads();
-      const int cnx = g.nx >> 1, cny = g.ny >> 1, cnz = g.nz >> 1;
-      for (int q = threadIdx.x; q < 32 * COB; q += 256) {
-        const int co = q % COB, cell = q / COB;
-        const int px = cell & 7, py = (cell >> 3) & 1, pz = cell >> 4;
-        const int cx = (x0 >> 1) + px, cy = (y0 >> 1) + py, cz = (z0 >> 1) + pz;
-        if (cx >= cnx || cy >= cny || cz >= cnz) continue;
-        const float v = ps[((2 * pz * 2 + py) * 8 + px) * COB + co] + ps[(((2 * pz + 1) * 2 + py) * 8 + px) * COB + co];
-        p.pool[((long)b * cnx * cny * cnz + cx + (long)cnx * (cy + (long)cny * cz)) * CO + c0 + co] = 0.125f * v;
+        __syncthreads();
+        const int cnx = g.nx >> 1, cny = g.ny >> 1, cnz = g.nz >> 1;
+        for (int q = threadIdx.x; q < 8 * COB; q += 256) {
+          const int c4 = q % (COB / 4), cell = q / (COB / 4);
+          const int px = cell & 7, py = (cell >> 3) & 1, pz = cell >> 4;
+          const int cx = (tx0 >> 1) + px, cy = (ty >> 1) + py, cz = (tz0 >> 1) + pz;
+          if (cx >= cnx || cy >= cny || cz >= cnz) continue;
+          const float4 lo = ps[((2 * pz * 2 + py) * 8 + px) * (COB / 4) + c4];
+          const float4 hi = ps[(((2 * pz + 1) * 2 + py) * 8 + px) * (COB / 4) + c4];
+          *(float4*)(p.pool + ((long)tb * cnx * cny * cnz + cx + (long)cnx * (cy + (long)cny * cz)) * CO + nb * COB +
+                     4 * c4) = make_float4(0.125f * (lo.x + hi.x), 0.125f * (lo.y + hi.y), 0.125f * (lo.z + hi.z),
+                                           0.125f * (lo.w + hi.w));
+        }
       }
-    }
-  } else {
-    // partial tiles to LDS, summed in wave order by all threads
-    __syncthreads();
-    float* red = (float*)smem;
+    } else {
+      // partial tiles to LDS, summed in wave order by all threads
+      __syncthreads();
+      float4* red = (float4*)smem;   // [wave][voxel][COB / 4]
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+      for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int n = 0; n < NTB; ++n)
+        for (int n = 0; n < NTB; ++n)
+          red[((size_t)wave * 64 + m * 16 + i16) * (COB / 4) + n * 4 + kq] =
+              make_float4(acc[m][n][0], acc[m][n][1], acc[m][n][2], acc[m][n][3]);
+      __syncthreads();
+      for (int q = threadIdx.x; q < 16 * COB; q += 256) {
+        const int vox = q / (COB / 4), co = nb * COB + q % (COB / 4) * 4;
+        const int vx = tx0 + (vox & 15), vy = ty + (vox >> 4);
+        if (vx >= g.nx || vy >= g.ny) continue;
+        const long o = ((long)tb * V + vx + (long)g.nx * (vy + (long)g.ny * tz0)) * CO + co;
+        float4 r = red[q];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[((size_t)wave * 64 + m * 16 + 4 * kq + e) * COB + n * 16 + i16] = acc[m][n][e];
-    __syncthreads();
-    for (int q = threadIdx.x; q < 64 * COB; q += 256) {
-      const int vox = q / COB, co = c0 + q % COB;
-      const int x = x0 + (vox & 15), y = y0 + (vox >> 4), z = z0;
-      if (x >= g.nx || y >= g.ny || z >= g.nz) continue;
-      const long o = (long)b * V + x + (long)g.nx * (y + (long)g.ny * z);
-      float val = red[q];
-#pragma unroll
-      for (int w = 1; w < KS; ++w) val += red[(size_t)w * 64 * COB + q];
-      if (EPI == 1) {
-        const float a = fmaxf(val + p.bias[co], 0.f);
-        if (p.outA) p.outA[o * CO + co] = a;
-        if (p.skip) p.outD[o * CO + co] = a + p.skip[o * CO + co];
-      } else {
-        p.outA[o * CO + co] = val;
+        for (int w = 1; w < KS; ++w) {
+          const float4 t = red[(size_t)w * 16 * COB + q];
+          r.x += t.x; r.y += t.y; r.z += t.z; r.w += t.w;
+        }
+        if (EPI == 1) {
+          r.x = fmaxf(r.x + p.bias[co], 0.f);
+          r.y = fmaxf(r.y + p.bias[co + 1], 0.f);
+          r.z = fmaxf(r.z + p.bias[co + 2], 0.f);
+          r.w = fmaxf(r.w + p.bias[co + 3], 0.f);
+          if (p.outA) *(float4*)(p.outA + o) = r;
+          if (p.skip) {
+            const float4 k = *(const float4*)(p.skip + o);
+            *(float4*)(p.outD + o) = make_float4(r.x + k.x, r.y + k.y, r.z + k.z, r.w + k.w);
+          }
+        } else {
+          *(float4*)(p.outA + o) = r;
+        }
       }
     }
   }
@@ -942,20 +1016,29 @@ static ConvArgs cargs(Geo g, const float* X, const bf16x8* W, const float* bias,
   return a;
 }
 
+// With KS = 1 a workgroup walks over its share of the tiles, and there are as
+// many as the chip holds (KS = 4: one per tile).
+template <int CI, int CSRC, int CO, bool UP, int EPI, int KS, int NS, bool POOL>
+static void conv_launch(cpr_nn* nn, const ConvArgs& a, long tiles) {
+  constexpr long resident = (long)CUS * conv_per_cu<CI, CO, UP, KS, NS>() / NS;
+  const long walkers = KS == 1 ? std::min(tiles, resident) : tiles;
+  conv_kernel<CI, CSRC, CO, UP, EPI, KS, NS, POOL><<<walkers * NS, 256, 0, nn->stream>>>(a);
+}
+
 template <int CI, int CSRC, int CO, bool UP, int EPI, int KS, bool POOL>
 static void conv_ns(cpr_nn* nn, const ConvArgs& a, long tiles, int ns) {
   if constexpr (wbytes(CI, CO, 1) <= WMAX)
     if (ns == 1) {
-      conv_kernel<CI, CSRC, CO, UP, EPI, KS, 1, POOL><<<tiles, 256, 0, nn->stream>>>(a);
+      conv_launch<CI, CSRC, CO, UP, EPI, KS, 1, POOL>(nn, a, tiles);
       return;
     }
   if constexpr (CO >= 32 && wbytes(CI, CO, 2) <= WMAX)
     if (ns == 2) {
-      conv_kernel<CI, CSRC, CO, UP, EPI, KS, 2, POOL><<<tiles * 2, 256, 0, nn->stream>>>(a);
+      conv_launch<CI, CSRC, CO, UP, EPI, KS, 2, POOL>(nn, a, tiles);
       return;
     }
   if constexpr (CO >= 64)
-    if (ns == 4) conv_kernel<CI, CSRC, CO, UP, EPI, KS, 4, POOL><<<tiles * 4, 256, 0, nn->stream>>>(a);
+    if (ns == 4) conv_launch<CI, CSRC, CO, UP, EPI, KS, 4, POOL>(nn, a, tiles);
 }
 
 // a.pool (POOL only): also write the 2x2x2 average of the activations,
@@ -965,15 +1048,17 @@ static void conv(cpr_nn* nn, ConvArgs a) {
   const Geo& g = a.g;
   const long vox = (long)g.batch * g.V;
   const long txy = (long)div_up(g.nx, TX) * div_up(g.ny, TY);
-  const bool whole = vox >= 65536 && (UP || CI <= 32);
+  constexpr bool fits = UP || CI <= 32;
+  const bool whole = fits && vox >= 65536;
   const long tiles = whole ? txy * div_up(g.nz, 4) * g.batch : txy * g.nz * g.batch;
   int ns = 1;
   while (wbytes(CI, CO, ns) > WMAX) ns *= 2;
   while (CO / (16 * ns) >= 2 && ns < 4 && tiles * ns < 512) ns *= 2;
-  if (whole) {
-    conv_ns<CI, CSRC, CO, UP, EPI, 1, POOL>(nn, a, tiles, ns);
-    return;
-  }
+  if constexpr (fits)
+    if (whole) {
+      conv_ns<CI, CSRC, CO, UP, EPI, 1, POOL>(nn, a, tiles, ns);
+      return;
+    }
   ConvArgs b = a;
   b.head = nullptr;
   b.y = nullptr;
