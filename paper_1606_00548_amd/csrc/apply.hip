@@ -1419,47 +1419,9 @@ void apply_impl(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, 
   stage2<B, T, double>(ctx, v, nullptr, z, sweep);
 }
 
-// FP32 copies: decoupled blocks (row 0 from R0), ILU diagonals, MG levels.
-template <int B>
-__global__ void mixed_copy_kernel(int n, const double* __restrict__ J, const double* __restrict__ R0,
-                                  const double* __restrict__ Dinv, float* __restrict__ Jf,
-                                  float* __restrict__ Dinvf) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const size_t N = n;
-  for (int d = 0; d < 7; ++d)
-    for (int r = 0; r < B; ++r)
-      for (int c = 0; c < B; ++c) {
-        size_t o = tix(7 * B * B, (d * B + r) * B + c, t);
-        Jf[o] = (float)(r == 0 ? R0[tix(7 * B, d * B + c, t)] : J[o]);
-      }
-  for (int e = 0; e < B * B; ++e) Dinvf[tix(B * B, e, t)] = (float)Dinv[tix(B * B, e, t)];
-}
-
-__global__ void to_float_kernel(size_t n, const double* __restrict__ a, float* __restrict__ b) {
-  size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) b[t] = (float)a[t];
-}
-
 }  // namespace
 
 int vcycle_fused_level(const cpr_ctx* ctx) { return fused_level(ctx); }
-
-void launch_mixed_copies(cpr_ctx* ctx) {
-  hipStream_t s = ctx->stream;
-  int n = ctx->lay.n;
-  const double* J = Pre<double>::J(ctx);
-  if (ctx->b == 1)
-    mixed_copy_kernel<1><<<div_up(n, 256), 256, 0, s>>>(n, J, ctx->R0, ctx->Dinv, ctx->Jf, ctx->Dinvf);
-  else if (ctx->b == 2)
-    mixed_copy_kernel<2><<<div_up(n, 256), 256, 0, s>>>(n, J, ctx->R0, ctx->Dinv, ctx->Jf, ctx->Dinvf);
-  else
-    mixed_copy_kernel<3><<<div_up(n, 256), 256, 0, s>>>(n, J, ctx->R0, ctx->Dinv, ctx->Jf, ctx->Dinvf);
-  for (auto& L : ctx->levels) {
-    size_t m = (size_t)7 * L.lay.n;
-    to_float_kernel<<<div_up((long)m, 256), 256, 0, s>>>(m, L.A, L.Af);
-  }
-}
 
 // Pressure stage alone (FP64, the plain cycle even when a learned stage is
 // set up): r~_p = w^T v into level 0's r, dp_mg into its x.

@@ -9,7 +9,6 @@
 #include "internal.h"
 
 void release_hierarchy(cpr_ctx* ctx);
-void launch_mixed_copies(cpr_ctx* ctx);
 
 int set_err(cpr_ctx* ctx, int code, const std::string& msg) {
   if (ctx) ctx->err = msg;

@@ -92,9 +92,10 @@ __device__ bool solve_transposed_e0(const double (&D)[B][B], double (&y)[B]) {
   return ok;
 }
 
-template <int B>
+template <int B, bool MIXED>
 __global__ void qimpes_kernel(int n, const double* __restrict__ J, double* __restrict__ w,
-                              double* __restrict__ R0, double* __restrict__ Ap, int* __restrict__ nbad) {
+                              double* __restrict__ R0, double* __restrict__ Ap, int* __restrict__ nbad,
+                              float* __restrict__ Jf, float* __restrict__ Apf) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const size_t N = n;
@@ -114,9 +115,17 @@ __global__ void qimpes_kernel(int n, const double* __restrict__ J, double* __res
   for (int d = 0; d < 7; ++d) {
     for (int c = 0; c < B; ++c) {
       double s = 0.0;
-      for (int r = 0; r < B; ++r) s += wv[r] * J[tix(7 * B * B, (d * B + r) * B + c, t)];
+      double a[B];
+      for (int r = 0; r < B; ++r) {
+        a[r] = J[tix(7 * B * B, (d * B + r) * B + c, t)];
+        s += wv[r] * a[r];
+      }
       R0[tix(7 * B, d * B + c, t)] = s;
       if (c == 0) Ap[(size_t)d * N + t] = s;
+      if (MIXED) {
+        for (int r = 0; r < B; ++r) Jf[tix(7 * B * B, (d * B + r) * B + c, t)] = (float)(r == 0 ? s : a[r]);
+        if (c == 0) Apf[(size_t)d * N + t] = (float)s;
+      }
     }
   }
 }
@@ -125,10 +134,10 @@ __global__ void qimpes_kernel(int n, const double* __restrict__ J, double* __res
 // block row i; row 0 of every decoupled block goes to R0 (and its (0, 0)
 // entry to the pressure operator), rows >= 1 to Jt.  A singular diagonal
 // block raises the flag.
-template <int B>
+template <int B, bool MIXED>
 __global__ void abf_kernel(int n, const double* __restrict__ J, double* __restrict__ W,
                            double* __restrict__ R0, double* __restrict__ Jt, double* __restrict__ Ap,
-                           int* __restrict__ flag) {
+                           int* __restrict__ flag, float* __restrict__ Jf, float* __restrict__ Apf) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const size_t N = n;
@@ -152,6 +161,10 @@ __global__ void abf_kernel(int n, const double* __restrict__ J, double* __restri
         } else {
           Jt[tix(7 * B * B, (d * B + r) * B + c, t)] = s;
         }
+        if (MIXED) {
+          Jf[tix(7 * B * B, (d * B + r) * B + c, t)] = (float)s;
+          if (r == 0 && c == 0) Apf[(size_t)d * N + t] = (float)s;
+        }
       }
   }
 }
@@ -166,7 +179,7 @@ __global__ void abf_kernel(int n, const double* __restrict__ J, double* __restri
 // the partial rows are summed in a fixed order, pairs along x, then y, then z.  Ghost cells of a padded fine level take no
 // part; a ghost coarse cell gets the identity row.
 __global__ __launch_bounds__(256) void rap_kernel(Lay F, Lay C, const double* __restrict__ Af,
-                                                  double* __restrict__ Ac) {
+                                                  double* __restrict__ Ac, float* __restrict__ Acf) {
   __shared__ double sh[4][7][64];
   const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
   const int cn = blockIdx.x * 64 + lane;
@@ -211,8 +224,10 @@ __global__ __launch_bounds__(256) void rap_kernel(Lay F, Lay C, const double* __
   if (cn >= C.n) return;
   const int tc = lay_index(C, ci, cj, ck);
   for (int d = sub; d < 7; d += 4) {
-    const double v = (sh[0][d][lane] + sh[1][d][lane]) + (sh[2][d][lane] + sh[3][d][lane]);
-    Ac[(size_t)d * C.n + tc] = ci < C.nxr ? v : d == 0 ? 1.0 : 0.0;
+    const double sum = (sh[0][d][lane] + sh[1][d][lane]) + (sh[2][d][lane] + sh[3][d][lane]);
+    const double v = ci < C.nxr ? sum : d == 0 ? 1.0 : 0.0;
+    Ac[(size_t)d * C.n + tc] = v;
+    if (Acf) Acf[(size_t)d * C.n + tc] = (float)v;
   }
 }
 
@@ -641,7 +656,7 @@ __device__ inline double at_blk(const double* __restrict__ J, const double* __re
 
 template <int B>
 __global__ void ilu_kernel(Lay L, int colour, const double* __restrict__ J, const double* __restrict__ R0,
-                           double* __restrict__ Dinv, int* __restrict__ flag) {
+                           double* __restrict__ Dinv, int* __restrict__ flag, float* __restrict__ Dinvf) {
   int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= L.nh) return;
   int t = colour * L.nh + q;
@@ -680,7 +695,10 @@ __global__ void ilu_kernel(Lay L, int colour, const double* __restrict__ J, cons
   double inv[B][B];
   if (!small_inverse<B>(D, inv)) atomicExch(flag, 1);
   for (int r = 0; r < B; ++r)
-    for (int c = 0; c < B; ++c) Dinv[tix(B * B, r * B + c, t)] = inv[r][c];
+    for (int c = 0; c < B; ++c) {
+      Dinv[tix(B * B, r * B + c, t)] = inv[r][c];
+      if (Dinvf) Dinvf[tix(B * B, r * B + c, t)] = (float)inv[r][c];
+    }
 }
 
 // Block ILU(0) diagonals in the tiled red-black order, one thread per tile
@@ -690,7 +708,7 @@ __global__ void ilu_kernel(Lay L, int colour, const double* __restrict__ J, cons
 // tile every neighbour in another tile (all of them red).
 template <int B>
 __global__ void ilu_tiles_kernel(Lay L, int colour, const double* __restrict__ J, const double* __restrict__ R0,
-                                 double* Dinv, int* __restrict__ flag) {
+                                 double* Dinv, int* __restrict__ flag, float* __restrict__ Dinvf) {
   int i, tj, tk;
   if (!tile_of_thread(L, colour, (long)blockIdx.x * blockDim.x + threadIdx.x, i, tj, tk)) return;
   const size_t N = L.n;
@@ -730,7 +748,10 @@ __global__ void ilu_tiles_kernel(Lay L, int colour, const double* __restrict__ J
     double inv[B][B];
     if (!small_inverse<B>(D, inv)) atomicExch(flag, 1);
     for (int r = 0; r < B; ++r)
-      for (int c = 0; c < B; ++c) Dinv[tix(B * B, r * B + c, t)] = inv[r][c];
+      for (int c = 0; c < B; ++c) {
+        Dinv[tix(B * B, r * B + c, t)] = inv[r][c];
+        if (Dinvf) Dinvf[tix(B * B, r * B + c, t)] = (float)inv[r][c];
+      }
   }
 }
 
@@ -809,7 +830,20 @@ static int build_hierarchy(cpr_ctx* ctx) {
 }
 
 // FP32 copies used by the mixed-precision preconditioner.
-void launch_mixed_copies(cpr_ctx* ctx);
+// Decoupling; MIXED: with FP32 copies of the decoupled blocks and the fine
+// level.  The per-cell kernels stream the Jacobian's planes in one-wave
+// workgroups.
+template <int B, bool MIXED>
+static void launch_decoupling(cpr_ctx* ctx) {
+  const int n = ctx->lay.n, nb = div_up(n, 64);
+  const MGLevel& L0 = ctx->levels[0];
+  if (ctx->opt.decoupling == CPR_DECOUPLE_ABF)
+    abf_kernel<B, MIXED><<<nb, 64, 0, ctx->stream>>>(n, ctx->J, ctx->Wabf, ctx->R0, ctx->Jt, L0.A, ctx->flag, ctx->Jf,
+                                                     L0.Af);
+  else
+    qimpes_kernel<B, MIXED><<<nb, 64, 0, ctx->stream>>>(n, ctx->J, ctx->w, ctx->R0, L0.A, ctx->flag + 1, ctx->Jf,
+                                                        L0.Af);
+}
 
 int setup_cpr(cpr_ctx* ctx) {
   int rc = build_hierarchy(ctx);
@@ -818,23 +852,19 @@ int setup_cpr(cpr_ctx* ctx) {
   const Lay& L = ctx->lay;
   const int n = L.n;
   zero_int_kernel<<<1, 64, 0, s>>>(ctx->flag, 4);   // and the counters of the Krylov kernels' last workgroups
-  // per-cell kernels stream the Jacobian's planes in one-wave workgroups
-  int nb = div_up(n, 64);
+  // The FP32 copies of a mixed preconditioner (decoupled blocks, levels, ILU
+  // diagonals) are stored by the kernels that form the values: passes of their
+  // own read them again (256x256x64 black oil: 625 us of the decoupling and
+  // 680 + 95 us of the copies, 870 us together).
+  const bool mixed = ctx->opt.precision == CPR_PREC_MIXED;
+  float* df = mixed ? ctx->Dinvf : nullptr;
   const bool abf = ctx->opt.decoupling == CPR_DECOUPLE_ABF;
-  if (abf) {
-    if (ctx->b == 1)
-      abf_kernel<1><<<nb, 64, 0, s>>>(n, ctx->J, ctx->Wabf, ctx->R0, ctx->Jt, ctx->levels[0].A, ctx->flag);
-    else if (ctx->b == 2)
-      abf_kernel<2><<<nb, 64, 0, s>>>(n, ctx->J, ctx->Wabf, ctx->R0, ctx->Jt, ctx->levels[0].A, ctx->flag);
-    else
-      abf_kernel<3><<<nb, 64, 0, s>>>(n, ctx->J, ctx->Wabf, ctx->R0, ctx->Jt, ctx->levels[0].A, ctx->flag);
-  } else if (ctx->b == 1) {
-    qimpes_kernel<1><<<nb, 64, 0, s>>>(n, ctx->J, ctx->w, ctx->R0, ctx->levels[0].A, ctx->flag + 1);
-  } else if (ctx->b == 2) {
-    qimpes_kernel<2><<<nb, 64, 0, s>>>(n, ctx->J, ctx->w, ctx->R0, ctx->levels[0].A, ctx->flag + 1);
-  } else {
-    qimpes_kernel<3><<<nb, 64, 0, s>>>(n, ctx->J, ctx->w, ctx->R0, ctx->levels[0].A, ctx->flag + 1);
-  }
+  if (ctx->b == 1)
+    mixed ? launch_decoupling<1, true>(ctx) : launch_decoupling<1, false>(ctx);
+  else if (ctx->b == 2)
+    mixed ? launch_decoupling<2, true>(ctx) : launch_decoupling<2, false>(ctx);
+  else
+    mixed ? launch_decoupling<3, true>(ctx) : launch_decoupling<3, false>(ctx);
   // rows >= 1 of the decoupled blocks: the Jacobian's own (quasi-IMPES) or D^-1 A (ABF)
   const double* Jdec = abf ? ctx->Jt : ctx->J;
   // Galerkin chain and coarsest inverse on the auxiliary stream.  The ILU
@@ -849,7 +879,7 @@ int setup_cpr(cpr_ctx* ctx) {
   for (size_t l = 0; l + 1 < ctx->levels.size(); ++l) {
     const MGLevel& F = ctx->levels[l];
     MGLevel& C = ctx->levels[l + 1];
-    rap_kernel<<<div_up(C.lay.n, 64), 256, 0, a>>>(F.lay, C.lay, F.A, C.A);
+    rap_kernel<<<div_up(C.lay.n, 64), 256, 0, a>>>(F.lay, C.lay, F.A, C.A, mixed ? C.Af : nullptr);
   }
   // dense inverse of the coarsest level
   const MGLevel& last = ctx->levels.back();
@@ -894,20 +924,19 @@ int setup_cpr(cpr_ctx* ctx) {
   for (int colour = 0; colour < 2; ++colour) {
     if (tiles) {
       if (ctx->b == 1)
-        ilu_tiles_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+        ilu_tiles_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
       else if (ctx->b == 2)
-        ilu_tiles_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+        ilu_tiles_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
       else
-        ilu_tiles_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+        ilu_tiles_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else if (ctx->b == 1) {
-      ilu_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+      ilu_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else if (ctx->b == 2) {
-      ilu_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+      ilu_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else {
-      ilu_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag);
+      ilu_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     }
   }
-  if (ctx->opt.precision == CPR_PREC_MIXED) launch_mixed_copies(ctx);
   CPR_TRY(hipStreamWaitEvent(s, ctx->ev_gj, 0));
   rc = launch_check(ctx, "cpr_setup kernels");
   if (rc != CPR_OK) return rc;
