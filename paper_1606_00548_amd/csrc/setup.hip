@@ -487,71 +487,118 @@ __global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const dou
     }
 }
 
-// The same for nb <= 64 with a wavefront's lanes as the rows: wave w of four
-// holds columns 16 w .. 16 w + 15, sixteen values a lane, and a step costs one
-// barrier.  The pivot row is broadcast by scalar reads of its lane.  What
-// passes through LDS are the pivot column's values (the multipliers), the
-// pivot's row and reciprocal; the wave that owns column p + 1 finds them as
-// soon as it has updated that column, in one block of code with its other
+// The same with a wavefront's lanes as the rows, for nb <= 64 RR and <= NW CC:
+// lane l of wave w holds rows l + 64 i of columns CC w ..., and a step costs
+// one barrier.  The pivot row is broadcast by scalar reads of its lane, and an
+// entry's update is those two reads (shared by the lane's rows) and one
+// multiply-add: the pivot row is not divided by its pivot until the end (a
+// row's later updates are proportional to its own entries, so its scale
+// factors out), which also makes its multiplier zero instead of a select.
+// What passes through LDS are the pivot column's values (the multipliers) and
+// the pivot's row and reciprocal; the wave that owns column p + 1 finds them
+// as soon as it has updated that column, in one block of code with its other
 // updates, which hide the search and the division.  The wave whose columns
 // are eliminated moves them down one register a step, so that no loop needs a
-// register index and all stay rolled (unrolled over the columns the kernel
-// was bound by instruction fetch: 60 us).  One wave per SIMD is asked of the
-// compiler so that it overlaps the updates.  64 rows: 50 -> 38 us.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void schur_invert64_kernel(
+// register index and all stay rolled (a step unrolled over the columns was
+// bound by instruction fetch).  Sixteen waves, so that the owner's other
+// updates are few: with four of sixteen columns the 64-row form took 36 us,
+// with sixteen of four 31 (50 in the general form); 168 rows 214 us (296).
+// Above 192 rows the entries of sixteen waves do not fit the registers, and
+// eight waves are no faster than the general form.
+template <int RR, int CC, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void schur_lanes_kernel(
     int nb, const double* __restrict__ S, double* __restrict__ out, int* __restrict__ flag) {
-  __shared__ double col[2][64], pinv_s[2][64];
-  __shared__ int q_s[2][64];
+  static_assert(64 * RR <= 256 && NW * CC <= 256, "the pivot's row is kept in eight bits");
+  __shared__ double col[2][RR][64], pinv_s[NW * CC];
+  __shared__ int prow[NW * CC], pcol[64 * RR];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double m[16];
+  double m[CC][RR];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int cc = wave * 16 + c;
-    m[c] = lane < nb && cc < nb ? S[(size_t)lane * nb + cc] : 0.0;
-  }
+  for (int c = 0; c < CC; ++c)
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      const int r = lane + 64 * i, cc = wave * CC + c;
+      m[c][i] = r < nb && cc < nb ? S[(size_t)r * nb + cc] : 0.0;
+    }
   auto bcast = [](double v, int q) {   // lane q's value to the wave
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q),
                             __builtin_amdgcn_readlane(__double2loint(v), q));
   };
-  bool used = lane >= nb, bad = false;
-  int prow = 0, pcol = 0;   // of this lane's column and row
-  // the pivot of column p from its values v (every lane stores it in a place
-  // of its own: stores of one address would go one after the other)
-  auto pivot = [&](int p, double v) {
-    const unsigned key = used ? 0u : (((unsigned)__double2hiint(v) & 0x7fffff00u) | (255u - (unsigned)lane)) + 1u;
-    const int q = __builtin_amdgcn_readfirstlane((int)((255u - ((wave_max(key) - 1u) & 255u)) & 63u));
-    const double pv = bcast(v, q);
+  bool used[RR], bad = false;
+#pragma unroll
+  for (int i = 0; i < RR; ++i) used[i] = lane + 64 * i >= nb;
+  // the pivot of column p from its values v
+  auto pivot = [&](int p, const double(&v)[RR]) {
+    unsigned key = 0;
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      const unsigned row = lane + 64 * i;
+      const unsigned k = (((unsigned)__double2hiint(v[i]) & 0x7fffff00u) | (255u - row)) + 1u;
+      key = used[i] || k < key ? key : k;
+      col[p & 1][i][lane] = v[i];
+    }
+    const int q = (int)(255u - ((wave_max(key) - 1u) & 255u));   // an unused row of nb always
+    double pv = bcast(v[0], q & 63);
+#pragma unroll
+    for (int i = 1; i < RR; ++i) pv = q >> 6 == i ? bcast(v[i], q & 63) : pv;
     bad |= !(fabs(pv) > TINY && fabs(pv) < HUGE_VAL);
-    col[p & 1][lane] = v;
-    q_s[p & 1][lane] = q;
-    pinv_s[p & 1][lane] = 1.0 / pv;
+    const double r = 1.0 / pv;
+    if (lane == 0) {
+      prow[p] = q;
+      pinv_s[p] = r;
+    }
   };
-  double f, pinv;
+  double fp[RR];   // the multipliers over the pivot
+  bool is_q[RR];
   int q;
-  bool is_q;
   auto begin = [&](int p) {
-    f = col[p & 1][lane];
-    pinv = pinv_s[p & 1][lane];
-    q = __builtin_amdgcn_readfirstlane(q_s[p & 1][lane]);
-    is_q = lane == q;
-    used |= is_q;
-    pcol = is_q ? p : pcol;
-    prow = lane == p ? q : prow;
+    q = __builtin_amdgcn_readfirstlane(prow[p]);
+    const double pinv = pinv_s[p];
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      is_q[i] = lane + 64 * i == q;
+      used[i] |= is_q[i];
+      fp[i] = is_q[i] ? 0.0 : col[p & 1][i][lane] * pinv;
+    }
   };
-  auto update = [&](double v) {
-    const double pr = bcast(v, q) * pinv;
-    return is_q ? pr : v - f * pr;
+  double row[CC];   // the pivot row of this wave's columns
+  auto read_row = [&] {
+#pragma unroll
+    for (int i = 0; i < RR; ++i)
+      if (q >> 6 == i) {
+#pragma unroll
+        for (int c = 0; c < CC; ++c) row[c] = bcast(m[c][i], q & 63);
+      }
   };
-  const int lo = min(16 * wave, nb), hi = min(lo + 16, nb);
-  if (wave == 0) pivot(0, m[0]);
-  __syncthreads();
-  // the columns of the waves before this one, its own, and the others; each
-  // wave passes the barrier once a column
   auto pass = [&](int p) {
     begin(p);
+    read_row();
 #pragma unroll
-    for (int c = 0; c < 16; ++c) m[c] = update(m[c]);
+    for (int c = 0; c < CC; ++c)
+#pragma unroll
+      for (int i = 0; i < RR; ++i) m[c][i] -= fp[i] * row[c];
   };
+  auto own = [&](int p, bool more) {
+    begin(p);
+    read_row();
+    double next[RR];
+#pragma unroll
+    for (int i = 0; i < RR; ++i) next[i] = m[1][i] - fp[i] * row[1];
+    if (more) pivot(p + 1, next);
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      m[0][i] = next[i];
+#pragma unroll
+      for (int c = 2; c < CC; ++c) m[c - 1][i] = m[c][i] - fp[i] * row[c];
+      m[CC - 1][i] = is_q[i] ? 1.0 : -fp[i];
+    }
+    __syncthreads();
+  };
+  // the columns of the waves before this one, its own, and the others; each
+  // wave passes the barrier once a column
+  const int lo = min(CC * wave, nb), hi = min(lo + CC, nb);
+  if (wave == 0) pivot(0, m[0]);
+  __syncthreads();
   for (int p = 0; p + 1 < lo; ++p) {
     pass(p);
     __syncthreads();
@@ -561,28 +608,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (lo < hi) pivot(lo, m[0]);
     __syncthreads();
   }
-  auto own = [&](int p, bool more) {
-    begin(p);
-    const double gone = is_q ? pinv : -(f * pinv), next = update(m[1]);
-    if (more) pivot(p + 1, next);
-    m[0] = next;
-#pragma unroll
-    for (int c = 2; c < 16; ++c) m[c - 1] = update(m[c]);
-    m[15] = gone;
-    __syncthreads();
-  };
   for (int p = lo; p + 1 < hi; ++p) own(p, true);
   if (lo < hi) own(hi - 1, false);
   for (int p = hi; p < nb; ++p) {
     pass(p);
     __syncthreads();
   }
-  const int moved = hi - lo;   // register c holds column (c + moved) mod 16
+  for (int p = threadIdx.x; p < nb; p += 64 * NW) pcol[prow[p]] = p;
+  __syncthreads();
+  const int moved = hi - lo;   // register c holds column (c + moved) mod CC
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int cc = wave * 16 + ((c + moved) & 15);
-    const int to = __builtin_amdgcn_readlane(prow, cc);
-    if (lane < nb && cc < nb) out[(size_t)pcol * nb + to] = m[c];
+  for (int i = 0; i < RR; ++i) {
+    const int r = lane + 64 * i;
+    if (r >= nb) continue;
+    const int to = pcol[r];
+    const double scale = pinv_s[to];
+#pragma unroll
+    for (int c = 0; c < CC; ++c) {
+      const int cc = wave * CC + (c + moved < CC ? c + moved : c + moved - CC);
+      if (cc < nb) out[(size_t)to * nb + prow[cc]] = m[c][i] * scale;
+    }
   }
   if (bad) atomicExch(flag, 1);
 }
@@ -891,9 +936,11 @@ int setup_cpr(cpr_ctx* ctx) {
     schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, a>>>(last.lay, last.A, sb, ctx->flag);
     CPR_TRY(hipEventRecord(ctx->ev_rap, a));
     if (nb <= 64) {
-      schur_invert64_kernel<<<1, 256, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 128) {
-      schur_invert_kernel<128, 32, 16, 8><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
+    } else if (nb <= 192) {
+      schur_lanes_kernel<3, 12, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 224) {
       schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
     } else {

@@ -1,8 +1,9 @@
 """The kernels of the smallest levels: the single-workgroup cycle of one
 smoothed level (one thread per cell: the largest level it takes, 1,024 over
 128 cells, odd rows and planes, a natural-order coarsest level, a few cells)
-and the inverse whose waves hold 16 columns each (15, 16, 17, 32, 48, 49 and 63
-black cells).  Tolerances as for every single application: 1e-9 against the
+and the inverse whose lanes are the rows and whose waves hold 4, 8 or 12
+columns each (15, 16, 17, 32, 48, 49, 63, 160, 192 and, in the form above them,
+193, 196 and 216 black cells).  Tolerances as for every single application: 1e-9 against the
 oracle in FP64, 1e-5 with the FP32 preconditioner, and 1e-9 of the system a
 single level solves."""
 import numpy as np
@@ -36,7 +37,8 @@ def test_single_workgroup_cycle_matches_oracle(shape, pre, post):
         assert np.linalg.norm(z - ref) <= tol * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("nx,ny,nz", [(2, 5, 3), (2, 4, 4), (2, 17, 1), (4, 4, 4), (6, 4, 4), (2, 7, 7), (2, 9, 7)])
+@pytest.mark.parametrize("nx,ny,nz", [(2, 5, 3), (2, 4, 4), (2, 17, 1), (4, 4, 4), (6, 4, 4), (2, 7, 7), (2, 9, 7),
+                                      (10, 16, 2), (16, 24, 1), (2, 193, 1), (14, 7, 4), (18, 12, 2)])
 def test_one_application_solves_a_single_level(nx, ny, nz):
     from paper_1606_00548_amd import cprmi
     case = synth.single_phase_uniform(nx, ny, nz, wells=[synth.well(0, 0, nz, "prod", 150.0)])
