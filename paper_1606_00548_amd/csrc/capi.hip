@@ -71,6 +71,16 @@ double peaceman(double kx_md, double ky_md, double dx, double dy, double dz, dou
   return 2.0 * 3.141592653589793 * std::sqrt(kx * ky) * dz / (std::log(ro / rw) + skin);
 }
 
+// Horizontal permeabilities of the perforated cells: one kernel and two copies
+// for all of them (blocking 8-byte copies took 54 ms for 425 perforations).
+__global__ void perf_perm_kernel(int n, const int* __restrict__ cell, const double* __restrict__ perm3, size_t N,
+                                 double* __restrict__ kx, double* __restrict__ ky) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  kx[q] = perm3[cell[q]];
+  ky[q] = perm3[N + cell[q]];
+}
+
 int check_ctx(cpr_ctx* ctx) { return ctx ? CPR_OK : CPR_EINVAL; }
 
 int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, const double* poro,
@@ -191,6 +201,8 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
     ctx->rho_scale[2] = f->rho_g_sc / host_pvt(fl, 4, f->p_ref);
   }
   // perforations (each well's contiguous, in the order given)
+  std::vector<int> perf_cell;              // their cells in natural order
+  std::vector<const cpr_well_t*> perf_well;
   for (int q = 0; q < nwells; ++q) {
     const cpr_well_t& w = wells[q];
     const bool rate = w.control == CPR_CONTROL_RATE;
@@ -213,24 +225,34 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
       return set_err(ctx, CPR_EINVAL, "unknown well kind");
     if (!(w.rw > 0)) return set_err(ctx, CPR_EINVAL, "well radius must be > 0");
     for (int k = w.k0; k <= w.k1; ++k) {
-      size_t nat = (size_t)w.i + (size_t)g->nx * ((size_t)w.j + (size_t)g->ny * k);
-      double kxy[2];
-      CPR_TRY(hipMemcpy(&kxy[0], perm3 + nat, sizeof(double), hipMemcpyDeviceToHost));
-      CPR_TRY(hipMemcpy(&kxy[1], perm3 + N + nat, sizeof(double), hipMemcpyDeviceToHost));
       Perf p;
       p.cell = lay_index(ctx->lay, w.i, w.j, k);
       p.kind = w.kind;
       p.rw = rate ? (int)ctx->rwells.size() - 1 : -1;
-      p.wi = peaceman(kxy[0], kxy[1], g->dx, g->dy, g->dz, w.rw, w.skin);
+      p.wi = 0.0;   // below
       p.bhp = w.bhp;
       double depth = g->top + (k + 0.5) * g->dz;
       p.dzh = g->top - depth;
       for (const Perf& o : ctx->perfs)
         if (o.cell == p.cell) return set_err(ctx, CPR_EINVAL, "two perforations in one cell");
       ctx->perfs.push_back(p);
+      perf_cell.push_back(w.i + g->nx * (w.j + g->ny * k));
+      perf_well.push_back(&w);
     }
   }
   if (!ctx->perfs.empty()) {
+    // at most one perforation a cell: the vectors' buffers hold them
+    const size_t np = perf_cell.size();
+    std::vector<double> kx(np), ky(np);
+    int* cells = reinterpret_cast<int*>(ctx->vin2);
+    CPR_TRY(hipMemcpyAsync(cells, perf_cell.data(), np * sizeof(int), hipMemcpyHostToDevice, s));
+    perf_perm_kernel<<<div_up((long)np, 256), 256, 0, s>>>((int)np, cells, perm3, N, ctx->vin, ctx->vout);
+    if ((rc = launch_check(ctx, "cpr_create perforations")) != CPR_OK) return rc;
+    CPR_TRY(hipMemcpyAsync(kx.data(), ctx->vin, np * sizeof(double), hipMemcpyDeviceToHost, s));
+    CPR_TRY(hipMemcpyAsync(ky.data(), ctx->vout, np * sizeof(double), hipMemcpyDeviceToHost, s));
+    CPR_TRY(hipStreamSynchronize(s));
+    for (size_t q = 0; q < np; ++q)
+      ctx->perfs[q].wi = peaceman(kx[q], ky[q], g->dx, g->dy, g->dz, perf_well[q]->rw, perf_well[q]->skin);
     if ((rc = dalloc(ctx, &ctx->perfs_d, ctx->perfs.size())) != CPR_OK) return rc;
     CPR_TRY(hipMemcpyAsync(ctx->perfs_d, ctx->perfs.data(), ctx->perfs.size() * sizeof(Perf),
                            hipMemcpyHostToDevice, s));
