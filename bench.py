@@ -95,22 +95,28 @@ def network_timing(nx, ny, nz, reps=20):
             "frac_of_bf16_peak": tflops / BF16_PEAK_TFLOPS, "grid": [nx, ny, nz], "batch": 1}
 
 
-def algorithmic_bytes(kclass, b, n, iterations_per_cycle, precision, levels=None, orth="dcgs2", pre=1, post=1):
+def algorithmic_bytes(kclass, b, n, iterations_per_cycle, precision, levels=None, orth="dcgs2", pre=1, post=1,
+                      black=False):
     """Bytes the launches of one kernel class in one Newton step must move at
     minimum (every array element touched once per launch, FP64), and the
     number of those launches.  iterations_per_cycle: Arnoldi steps of each
     restart cycle; levels: cell counts of the multigrid levels; orth: the
     FGMRES orthogonalisation (delayed CGS2 or CGS2); pre / post: sweeps of
-    the V(pre, post) cycle."""
+    the V(pre, post) cycle; black: cycles over the black rows (FP64 red-black
+    ILU, delayed CGS2, no rate wells), whose products and basis vectors are
+    half as long and whose last fine red half-sweep rides with stage 2."""
     s = 8
     its = sum(iterations_per_cycle)
     if kclass == "spmv":
         # 7 b x b blocks + x + y per cell; once per cycle also the true
         # residual, which reads the right-hand side as well
         per = (7 * b * b + 2 * b) * s * n
-        return its * per + len(iterations_per_cycle) * (per + b * s * n), its + len(iterations_per_cycle)
+        # black rows: half of the blocks, all of x, half of y
+        step = (7 * b * b + 3 * b) * s * n // 2 if black else per
+        return its * step + len(iterations_per_cycle) * (per + b * s * n), its + len(iterations_per_cycle)
     if kclass == "orth":
         tot, launches = 0, 0
+        n = n // 2 if black else n
         for k in iterations_per_cycle:
             for j in range(k):
                 if orth == "cgs2":
@@ -127,7 +133,8 @@ def algorithmic_bytes(kclass, b, n, iterations_per_cycle, precision, levels=None
         return tot, launches
     if kclass == "smooth":
         # red-black Gauss-Seidel half-sweeps on the levels smoothed by
-        # multi-block kernels (those above the first level of <= 4096 cells):
+        # multi-block kernels (those above the first level of <= 4096 cells,
+        # or all above a coarsest level of more than 128):
         # black pre-sweep 11 values per black cell (7 stencil, r, x, res, red x),
         # black post-sweep 10 + coarse correction n/8, red sweep 10 (the
         # zero-guess red sweep of the first pre-sweep rides with the
@@ -135,11 +142,16 @@ def algorithmic_bytes(kclass, b, n, iterations_per_cycle, precision, levels=None
         # others); each further pre-sweep is red + black pre, each further
         # post-sweep black pre + red
         down = next((l for l, nl in enumerate(levels) if nl <= 4096), len(levels) - 1)
+        if levels[-1] > 128:
+            down = len(levels) - 1
         per, launches = 0, 0
         for l in range(down):
             nl = levels[l]
             per += (44 + 41 + 40 + (pre - 1 + post - 1) * (40 + 44)) * nl
             launches += 3 + 2 * (pre - 1 + post - 1)
+        if black and down:
+            per -= 40 * levels[0]
+            launches -= 1
         return its * per, its * launches
     if kclass == "ilu":
         # stage-2 residual and red-black block ILU(0) sweeps, per cell of a
@@ -507,26 +519,30 @@ def main():
     while solver.mg_level_shape(len(levels)) is not None:
         levels.append(int(np.prod(solver.mg_level_shape(len(levels)))))
     ks = min(2, args.steps)
+    black = not any(w.get("control") == "rate" for w in case["wells"])
     classes = {}
     for cls in ("spmv", "orth", "smooth", "ilu"):
         _, _, _, _, (nl, ms) = run.timed(fp64, ks, 0, kclass=cls)
-        ab, al = algorithmic_bytes(cls, b, n, per_cycle, "fp64", levels, pre=CYCLE["mg_pre"], post=CYCLE["mg_post"])
+        ab, al = algorithmic_bytes(cls, b, n, per_cycle, "fp64", levels, pre=CYCLE["mg_pre"], post=CYCLE["mg_post"],
+                                   black=black)
         gbs = ab * ks / (ms * 1e-3) / 1e9 if ms > 0 else None
         classes[cls] = {"launches_per_step": nl / ks, "expected_launches_per_step": al,
                         "ms_per_step": ms / ks, "avg_launch_us": 1e3 * ms / max(nl, 1),
                         "algorithmic_bytes_per_step": ab, "GBps": gbs,
                         "frac": gbs / HBM_PEAK_GBS if gbs else None}
     sp = classes["spmv"]
-    ab, al = algorithmic_bytes("spmv", b, n, per_cycle, "fp64")
+    ab, al = algorithmic_bytes("spmv", b, n, per_cycle, "fp64", black=black)
     avg_ms = sp["ms_per_step"] / max(sp["launches_per_step"], 1)
     achieved = (ab / al) / (avg_ms * 1e-3) / 1e9
+    kernel = f"spmv_black_kernel<{b}>" if black else f"spmv_kernel<{b}>"
     traffic = None
     tfile = os.path.join(ROOT, "profiles", "spmv_traffic.json")
     if os.path.exists(tfile):
         info = json.load(open(tfile))
-        if info.get("workload_cells") == n and info.get("source_sha") == _kernel_sha("spmv"):
+        if info.get("workload_cells") == n and info.get("kernel") == kernel \
+                and info.get("source_sha") == _kernel_sha("spmv"):
             traffic = info.get("bytes_per_launch")
-    roofline = {"bound": "hbm", "kernel": "spmv_kernel<3>" if (b == 3 and n > (1 << 20)) else "spmv",
+    roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": traffic, "launches_sampled": int(sp["launches_per_step"] * ks),
                 "avg_launch_us": avg_ms * 1e3, "algorithmic_bytes_per_launch": ab / al,
@@ -545,7 +561,10 @@ def main():
     network = network_timing(nx, ny, nz) if (b == 3 and nx % 8 == 0 and ny % 8 == 0 and nz % 8 == 0) else None
     configs = other_configs() if not (args.no_variants or args.no_other_configs) else {}
 
-    cpu = cpu_baseline_value(sample, n, st["iterations"], class_bytes) if sample else None
+    # the oracle works on whole vectors and products
+    whole_bytes = sum(algorithmic_bytes(cls, b, n, per_cycle, "fp64", levels, pre=CYCLE["mg_pre"],
+                                        post=CYCLE["mg_post"])[0] for cls in classes)
+    cpu = cpu_baseline_value(sample, n, st["iterations"], whole_bytes) if sample else None
     out = {
         "metric": METRIC, "value": sec, "unit": "s/Newton step", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": sec * 1e3,
