@@ -764,6 +764,7 @@ int cpr_precond_apply(cpr_ctx_t* ctx, const double* v, double* z) {
   if (check_ctx(ctx)) return CPR_EINVAL;
   if (!v || !z) return set_err(ctx, CPR_EINVAL, "null argument");
   if (!ctx->setup_done) return set_err(ctx, CPR_EINVAL, "cpr_setup has not been called for this Jacobian");
+  if (precond_apply_nat(ctx, v, z)) return launch_check(ctx, "cpr_precond_apply");
   CPR_TRY(vec_nat_to_cs(ctx, v, ctx->vin));
   precond_apply(ctx, ctx->vin, ctx->vin, nullptr, ctx->vout);
   CPR_TRY(vec_cs_to_nat(ctx, ctx->vout, z));

@@ -482,6 +482,8 @@ int setup_cpr(cpr_ctx* ctx);
 // equal v).  Otherwise v must equal vin.  With redc (device scalar, nrm2
 // given too) only the black half of vin is read; the red half of v is
 // *redc / sqrt(*nrm2) times that of v0.
+// Natural-order input and output in the passes at either end; false: not for this context.
+bool precond_apply_nat(cpr_ctx* ctx, const double* v, double* z);
 void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z,
                    const double* v0 = nullptr, const double* redc = nullptr);
 
