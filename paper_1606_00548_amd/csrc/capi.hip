@@ -50,9 +50,9 @@ void free_all(cpr_ctx* ctx) {
   ctx->hhost = nullptr;
   for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
   phase_timing_release(ctx);
-  for (hipEvent_t e : {ctx->ev_q, ctx->ev_rap, ctx->ev_gj, ctx->ev_iter[0], ctx->ev_iter[1]})
+  for (hipEvent_t e : {ctx->ev_rap, ctx->ev_ilu, ctx->ev_iter[0], ctx->ev_iter[1]})
     if (e) (void)hipEventDestroy(e);
-  ctx->ev_q = ctx->ev_rap = ctx->ev_gj = ctx->ev_iter[0] = ctx->ev_iter[1] = nullptr;
+  ctx->ev_rap = ctx->ev_ilu = ctx->ev_iter[0] = ctx->ev_iter[1] = nullptr;
   if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
   ctx->aux = nullptr;
   if (ctx->nn) cpr_nn_destroy(ctx->nn);
@@ -98,9 +98,8 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
     return set_err(ctx, CPR_EINVAL, "black oil needs a PVT table with 2..16 nodes");
   ctx->stream = (hipStream_t)stream;
   CPR_TRY(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking));
-  CPR_TRY(hipEventCreateWithFlags(&ctx->ev_q, hipEventDisableTiming));
   CPR_TRY(hipEventCreateWithFlags(&ctx->ev_rap, hipEventDisableTiming));
-  CPR_TRY(hipEventCreateWithFlags(&ctx->ev_gj, hipEventDisableTiming));
+  CPR_TRY(hipEventCreateWithFlags(&ctx->ev_ilu, hipEventDisableTiming));
   CPR_TRY(hipEventCreateWithFlags(&ctx->ev_iter[0], hipEventDisableTiming));
   CPR_TRY(hipEventCreateWithFlags(&ctx->ev_iter[1], hipEventDisableTiming));
   ctx->grid = *g;

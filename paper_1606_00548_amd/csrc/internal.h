@@ -273,7 +273,7 @@ struct cpr_ctx {
   // setup runs the Galerkin chain and the coarsest inverse on a second
   // stream (default priority) while the ILU factorisation runs on `stream`
   hipStream_t aux = nullptr;
-  hipEvent_t ev_q = nullptr, ev_rap = nullptr, ev_gj = nullptr;
+  hipEvent_t ev_rap = nullptr, ev_ilu = nullptr;
   hipEvent_t ev_iter[2] = {nullptr, nullptr};   // completion of Arnoldi steps (even, odd)
   // set by FGMRES when a restart cycle with the FP32 preconditioner or the
   // learned stage stalls: the rest of that solve applies plain FP64 CPR

@@ -912,19 +912,17 @@ int setup_cpr(cpr_ctx* ctx) {
     mixed ? launch_decoupling<3, true>(ctx) : launch_decoupling<3, false>(ctx);
   // rows >= 1 of the decoupled blocks: the Jacobian's own (quasi-IMPES) or D^-1 A (ABF)
   const double* Jdec = abf ? ctx->Jt : ctx->J;
-  // Galerkin chain and coarsest inverse on the auxiliary stream.  The ILU
-  // factorisation on the caller's stream overlaps the inverse only, a serial
-  // chain in one workgroup: its kernels flood the chip, so that the Galerkin
-  // kernels beside them took as long as it did and the inverse's workgroup got
-  // its place when they had drained (192x192x48: 288 against 26 us and the
-  // inverse done 970 against 450 us after the decoupling).
-  hipStream_t a = ctx->aux;
-  CPR_TRY(hipEventRecord(ctx->ev_q, s));
-  CPR_TRY(hipStreamWaitEvent(a, ctx->ev_q, 0));
+  // Galerkin chain and coarsest inverse, the longer chain for small systems,
+  // on the caller's stream, where nothing waits for an event (Newton step of 32x32x8: 852 -> 833 us).
+  // The ILU factorisation on the auxiliary stream overlaps the inverse only, a
+  // serial chain in one workgroup: its kernels flood the chip, so that the
+  // Galerkin kernels beside them took as long as it did and the inverse's
+  // workgroup got its place when they had drained (192x192x48: 288 against 26
+  // us and the inverse done 970 against 450 us after the decoupling).
   for (size_t l = 0; l + 1 < ctx->levels.size(); ++l) {
     const MGLevel& F = ctx->levels[l];
     MGLevel& C = ctx->levels[l + 1];
-    rap_kernel<<<div_up(C.lay.n, 64), 256, 0, a>>>(F.lay, C.lay, F.A, C.A, mixed ? C.Af : nullptr);
+    rap_kernel<<<div_up(C.lay.n, 64), 256, 0, s>>>(F.lay, C.lay, F.A, C.A, mixed ? C.Af : nullptr);
   }
   // dense inverse of the coarsest level
   const MGLevel& last = ctx->levels.back();
@@ -933,58 +931,59 @@ int setup_cpr(cpr_ctx* ctx) {
     const int nb = last.lay.cs ? last.lay.nh : nc / 2;
     double* sb = ctx->gj_work;
     double* si = ctx->gj_work + (size_t)nb * nb;
-    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, a>>>(last.lay, last.A, sb, ctx->flag);
-    CPR_TRY(hipEventRecord(ctx->ev_rap, a));
+    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, s>>>(last.lay, last.A, sb, ctx->flag);
+    CPR_TRY(hipEventRecord(ctx->ev_rap, s));
     if (nb <= 64) {
-      schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 128) {
-      schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 192) {
-      schur_lanes_kernel<3, 12, 16><<<1, 1024, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<3, 12, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 224) {
-      schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, a>>>(nb, sb, si, ctx->flag);
+      schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, s>>>(nb, sb, si, ctx->flag);
     } else {
       constexpr int lds = 4 * 8 * 512 * sizeof(double);   // a quarter of the 256 x 256 matrix
       CPR_TRY(hipFuncSetAttribute((const void*)schur_invert_kernel<256, 32, 16, 12>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-      schur_invert_kernel<256, 32, 16, 12><<<1, 512, lds, a>>>(nb, sb, si, ctx->flag);
+      schur_invert_kernel<256, 32, 16, 12><<<1, 512, lds, s>>>(nb, sb, si, ctx->flag);
     }
-    schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, a>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
+    schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
   } else {
-    CPR_TRY(hipEventRecord(ctx->ev_rap, a));
+    CPR_TRY(hipEventRecord(ctx->ev_rap, s));
     double* bufA = ctx->gj_work;
     double* bufB = ctx->gj_work + (size_t)nc * 2 * nc;
-    dense_build_kernel<<<div_up(nc, 256), 256, 0, a>>>(last.lay, last.A, bufA);
+    dense_build_kernel<<<div_up(nc, 256), 256, 0, s>>>(last.lay, last.A, bufA);
     int gblocks = div_up((long)nc * 2 * nc, 256);
     if (gblocks > 512) gblocks = 512;
     for (int p = 0; p < nc; ++p) {
-      gj_step_kernel<<<gblocks, 256, 0, a>>>(nc, p, bufA, bufB, ctx->flag);
+      gj_step_kernel<<<gblocks, 256, 0, s>>>(nc, p, bufA, bufB, ctx->flag);
       double* t = bufA; bufA = bufB; bufB = t;
     }
-    gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, a>>>(nc, bufA, ctx->cinv, ctx->cinvf);
+    gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(nc, bufA, ctx->cinv, ctx->cinvf);
   }
-  CPR_TRY(hipEventRecord(ctx->ev_gj, a));
-  CPR_TRY(hipStreamWaitEvent(s, ctx->ev_rap, 0));
+  hipStream_t a = ctx->aux;
+  CPR_TRY(hipStreamWaitEvent(a, ctx->ev_rap, 0));
   // block ILU(0): red diagonals (cells or tiles) first, black ones use them
   const bool tiles = ctx->opt.ilu_order == CPR_ILU_TILES;
   const int nh = tiles ? (int)div_up(tile_threads(L), 64) : div_up(L.nh, 64);
   for (int colour = 0; colour < 2; ++colour) {
     if (tiles) {
       if (ctx->b == 1)
-        ilu_tiles_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+        ilu_tiles_kernel<1><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
       else if (ctx->b == 2)
-        ilu_tiles_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+        ilu_tiles_kernel<2><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
       else
-        ilu_tiles_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+        ilu_tiles_kernel<3><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else if (ctx->b == 1) {
-      ilu_kernel<1><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+      ilu_kernel<1><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else if (ctx->b == 2) {
-      ilu_kernel<2><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+      ilu_kernel<2><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     } else {
-      ilu_kernel<3><<<nh, 64, 0, s>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
+      ilu_kernel<3><<<nh, 64, 0, a>>>(L, colour, Jdec, ctx->R0, ctx->Dinv, ctx->flag, df);
     }
   }
-  CPR_TRY(hipStreamWaitEvent(s, ctx->ev_gj, 0));
+  CPR_TRY(hipEventRecord(ctx->ev_ilu, a));
+  CPR_TRY(hipStreamWaitEvent(s, ctx->ev_ilu, 0));
   rc = launch_check(ctx, "cpr_setup kernels");
   if (rc != CPR_OK) return rc;
   int* hflag = reinterpret_cast<int*>(ctx->hhost + 8);
