@@ -529,7 +529,11 @@ inline bool red_rows_exact(const cpr_ctx* c) {
   return !precond_fp32(c) && c->opt.ilu_order == CPR_ILU_RED_BLACK && c->nrate == 0;
 }
 
-int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st);
+// ||x||^2, its red cells' share, ||x - y||^2
+struct Norms {
+  double all = 0.0, red = 0.0, diff = 0.0;
+};
+int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known = nullptr);
 // Basis vector j of the last FGMRES cycle, whole, into dst (colour-split).
 void krylov_vector(cpr_ctx* ctx, int j, double* dst);
 int bicgstab_solve(cpr_ctx* ctx, cpr_stats_t* st);
@@ -537,5 +541,4 @@ void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, con
 // Bubble-point floor of the black-oil update: the first PVT pressure node.
 inline double pb_floor(const FluidDev& f) { return f.model == 3 ? f.pvt[0][0] : 0.0; }
 int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out);
-int reduce_dots(cpr_ctx* ctx, const double* a, const double* b, const double* c, const double* d, long len,
-                double* ab, double* cd);
+int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, Norms* n);

@@ -431,9 +431,11 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int 
 }
 
 // part rows 0 and 1: this block's share of the squares of x's black and red
-// cells (b planes of n = 2 nh cells).
+// cells (b planes of n = 2 nh cells; nh = 0: all in row 0), row 2: of x - y
+// when y is given.
 __global__ __launch_bounds__(KB) void colour_norms_kernel(long len, long nh, const double* __restrict__ x,
-                                                          double* __restrict__ part, int nblk) {
+                                                          const double* __restrict__ y, double* __restrict__ part,
+                                                          int nblk) {
   __shared__ double sh[CHUNK * (KB / 64)];
   __shared__ double tot[CHUNK];
   long per = (len + nblk - 1) / nblk;
@@ -444,11 +446,17 @@ __global__ __launch_bounds__(KB) void colour_norms_kernel(long len, long nh, con
   for (int q = 0; q < CHUNK; ++q) acc[q] = 0.0;
   for (long e = beg + threadIdx.x; e < end; e += KB) {
     const long c = e - 2 * nh * ((e >= 2 * nh ? 1 : 0) + (e >= 4 * nh ? 1 : 0));
-    const double v = x[e] * x[e];
-    acc[c < nh ? 1 : 0] += v;
+    const double a = x[e], v = a * a;
+    const bool red = c < nh;
+    acc[0] += red ? 0.0 : v;
+    acc[1] += red ? v : 0.0;
+    if (y) {
+      const double d = a - y[e];
+      acc[2] += d * d;
+    }
   }
-  block_sum_chunk(acc, 2, sh, tot);
-  if (threadIdx.x < 2) part[(size_t)threadIdx.x * nblk + blockIdx.x] = tot[threadIdx.x];
+  block_sum_chunk(acc, 3, sh, tot);
+  if (threadIdx.x < 3) part[(size_t)threadIdx.x * nblk + blockIdx.x] = tot[threadIdx.x];
 }
 
 // dst = the whole basis vector j of a black-row cycle: black half as stored,
@@ -665,47 +673,30 @@ void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, con
   newton_update_kernel<<<div_up(n > nrate ? n : nrate, 256), 256, 0, s>>>(b, n, nrate, pb_min, x, dx);
 }
 
-// Dot product of two device vectors of length len into host slot `slot` of
-// ctx->hhost (0..7), read after the stream is synchronised.
-static void queue_dot(cpr_ctx* ctx, const double* a, const double* b, long len, int slot) {
+// a . b into *out (host); synchronises.
+int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out) {
   hipStream_t s = ctx->stream;
   // reuse the orthogonalisation kernel with V = a (one vector), w = b
-  orth_kernel<<<ctx->nblk, KB, 0, s>>>(len, 1, a, 0, const_cast<double*>(b), nullptr, 1, 0, ctx->part,
-                                       ctx->nblk);
-  reduce_kernel<<<1, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev + slot);
-}
-
-// The same into *out; synchronises.
-int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out) {
-  queue_dot(ctx, a, b, len, 0);
+  orth_kernel<<<ctx->nblk, KB, 0, s>>>(len, 1, a, 0, const_cast<double*>(b), nullptr, 1, 0, ctx->part, ctx->nblk);
+  reduce_kernel<<<1, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev);
   CPR_TRY(hipGetLastError());
-  CPR_TRY(hipStreamSynchronize(ctx->stream));
+  CPR_TRY(hipStreamSynchronize(s));
   *out = ctx->hhost[0];
   return CPR_OK;
 }
 
-// Two dot products with one wait.
-int reduce_dots(cpr_ctx* ctx, const double* a, const double* b, const double* c, const double* d, long len,
-                double* ab, double* cd) {
-  queue_dot(ctx, a, b, len, 0);
-  queue_dot(ctx, c, d, len, 1);
-  CPR_TRY(hipGetLastError());
-  CPR_TRY(hipStreamSynchronize(ctx->stream));
-  *ab = ctx->hhost[0];
-  *cd = ctx->hhost[1];
-  return CPR_OK;
-}
-
-// ||x||^2 and its red cells' share (host).  Syncs.
-static int reduce_colour_norms(cpr_ctx* ctx, const double* x, double* all, double* red) {
+// ||x||^2, its red cells' share (0 with rate wells, whose vectors are longer)
+// and, when y is given, ||x - y||^2 (host), in one pass.  Syncs.
+int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, Norms* n) {
   hipStream_t s = ctx->stream;
-  const long bn = (long)ctx->b * ctx->lay.n;
-  colour_norms_kernel<<<ctx->nblk, KB, 0, s>>>(bn, ctx->lay.nh, x, ctx->part, ctx->nblk);
-  reduce_kernel<<<2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev);
+  const long nh = ctx->nrate ? 0 : ctx->lay.nh;
+  colour_norms_kernel<<<ctx->nblk, KB, 0, s>>>(vec_len(ctx), nh, x, y, ctx->part, ctx->nblk);
+  reduce_kernel<<<y ? 3 : 2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev);
   CPR_TRY(hipGetLastError());
   CPR_TRY(hipStreamSynchronize(s));
-  *red = ctx->hhost[1];
-  *all = ctx->hhost[0] + ctx->hhost[1];
+  n->red = ctx->hhost[1];
+  n->all = ctx->hhost[0] + ctx->hhost[1];
+  n->diff = y ? ctx->hhost[2] : 0.0;
   return CPR_OK;
 }
 
@@ -914,8 +905,9 @@ void krylov_vector(cpr_ctx* ctx, int j, double* dst) {
 
 // ctx->rs holds the right-hand side, ctx->xs receives the solution
 // (colour-split); with options.x0 it also holds the initial guess.
+// known: the right-hand side's norms, where the caller has them already.
 // Mirrors the oracle's FGMRES step for step.
-int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
+int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
   hipStream_t s = ctx->stream;
   const int b = ctx->b;
   const long len = vec_len(ctx);
@@ -946,10 +938,16 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
   // residual is the right-hand side, so one reduction gives both norms.
   const bool from_x0 = ctx->opt.x0 != 0;
   const bool colours = dcgs && ctx->nrate == 0;
-  double bb, bb_red = 0.0;
-  int rc = colours && !from_x0 ? reduce_colour_norms(ctx, ctx->rs, &bb, &bb_red)
-                               : reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb);
+  Norms nb;
+  int rc = CPR_OK;
+  if (known)
+    nb = *known;
+  else if (colours && !from_x0)
+    rc = reduce_norms(ctx, ctx->rs, nullptr, &nb);
+  else
+    rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &nb.all);
   if (rc) return rc;
+  const double bb = nb.all, bb_red = nb.red;
   double bnorm = std::sqrt(bb);
   S.bnorm = bnorm;
   if (!std::isfinite(bnorm)) {
@@ -977,8 +975,11 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st) {
     const bool first = S.cycles == 0 && !from_x0;   // r = b, x = 0
     double rr = bb, rr_red = bb_red;
     if (!first) {
-      rc = colours ? reduce_colour_norms(ctx, r, &rr, &rr_red) : reduce_dot(ctx, r, r, len, &rr);
+      Norms nr;
+      rc = colours ? reduce_norms(ctx, r, nullptr, &nr) : reduce_dot(ctx, r, r, len, &nr.all);
       if (rc) return rc;
+      rr = nr.all;
+      rr_red = nr.red;
     }
     double beta = std::sqrt(rr);
     S.true_rel = beta / bnorm;

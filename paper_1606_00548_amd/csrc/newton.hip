@@ -12,13 +12,6 @@
 
 namespace {
 
-// d = a - b (for ||b^l - r^(l-1)||)
-__global__ void diff_kernel(long len, const double* __restrict__ a, const double* __restrict__ b,
-                            double* __restrict__ d) {
-  long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < len) d[t] = a[t] - b[t];
-}
-
 double forcing(const cpr_newton_options_t& no, double rtol, int l, double bn, double bn_prev,
                double rn_prev, double diff_prev) {
   if (no.forcing == CPR_FORCING_FIXED) return rtol;
@@ -55,9 +48,9 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
     if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
     ctx->assembled = 1;
     ctx->setup_done = 0;
-    double bb;
-    if ((rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb)) != CPR_OK) return rc;
-    double bn = std::sqrt(bb);
+    Norms nb;   // of the residual, which the linear solve takes over
+    if ((rc = reduce_norms(ctx, ctx->rs, nullptr, &nb)) != CPR_OK) return rc;
+    double bn = std::sqrt(nb.all);
     const double b0 = bn;
     double bn_prev = 0.0, rn_prev = 0.0, diff_prev = 0.0;
     int l = 0, lin_total = 0;
@@ -74,27 +67,22 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
       if (rc != CPR_OK) return rc;
       if (ctx->opt.learned) CPR_TRY(hipMemsetAsync(ctx->nncount, 0, 2 * sizeof(int), s));
       cpr_stats_t ls = {};
-      rc = bicg ? bicgstab_solve(ctx, &ls) : fgmres_solve(ctx, &ls);
+      rc = bicg ? bicgstab_solve(ctx, &ls) : fgmres_solve(ctx, &ls, &nb);
       if (attempt_failure(rc)) break;
       if (rc < 0) return rc;
       const double* r = bicg ? ctx->V : ctx->tmp;   // b - A dx
       // what the forcing term needs: EW2 ||r||, EW1 ||b^l - r||
-      double rr = 0.0, dd = 0.0;
+      double rr = 0.0;
       if (no.forcing == CPR_FORCING_EW2 && (rc = reduce_dot(ctx, r, r, len, &rr)) != CPR_OK) return rc;
       launch_newton_update(b, ctx->lay.n, ctx->nrate, pb_floor(ctx->fl), x_cs, ctx->xs, s);
       if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
       ctx->setup_done = 0;
-      if (no.forcing == CPR_FORCING_EW1) {
-        diff_kernel<<<div_up(len, 256), 256, 0, s>>>(len, ctx->rs, r, ctx->vout);
-        rc = reduce_dots(ctx, ctx->vout, ctx->vout, ctx->rs, ctx->rs, len, &dd, &bb);
-      } else {
-        rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &bb);
-      }
+      rc = reduce_norms(ctx, ctx->rs, no.forcing == CPR_FORCING_EW1 ? r : nullptr, &nb);
       if (rc != CPR_OK) return rc;
       bn_prev = bn;
       rn_prev = std::sqrt(rr);
-      diff_prev = std::sqrt(dd);
-      bn = std::sqrt(bb);
+      diff_prev = std::sqrt(nb.diff);
+      bn = std::sqrt(nb.all);
       if (l < CPR_NEWTON_HIST) {
         S.theta[l] = o.rtol;
         S.lin_its[l] = ls.iterations;
