@@ -914,11 +914,12 @@ int setup_cpr(cpr_ctx* ctx) {
   const double* Jdec = abf ? ctx->Jt : ctx->J;
   // Galerkin chain and coarsest inverse, the longer chain for small systems,
   // on the caller's stream, where nothing waits for an event (Newton step of
-  // 32x32x8: 852 -> 833 us).  The ILU factorisation on the auxiliary stream overlaps the inverse only, a
-  // serial chain in one workgroup: its kernels flood the chip, so that the
-  // Galerkin kernels beside them took as long as it did and the inverse's
-  // workgroup got its place when they had drained (192x192x48: 288 against 26
-  // us and the inverse done 970 against 450 us after the decoupling).
+  // 32x32x8: 852 -> 833 us).  The ILU factorisation on the auxiliary stream
+  // overlaps the inverse only, a serial chain in one workgroup: its kernels
+  // flood the chip, so that the Galerkin kernels beside them took as long as
+  // it did and the inverse's workgroup got its place when they had drained
+  // (192x192x48: 288 against 26 us and the inverse done 970 against 450 us
+  // after the decoupling).
   for (size_t l = 0; l + 1 < ctx->levels.size(); ++l) {
     const MGLevel& F = ctx->levels[l];
     MGLevel& C = ctx->levels[l + 1];
