@@ -524,12 +524,19 @@ inline bool learned_on(const cpr_ctx* c) { return c->opt.learned && !c->fp64_now
 // against the stencil product the two differ by its own rounding, eps |A| |z|.
 // Not so with the FP32 preconditioner (FP32 rounding), with tiles as colours
 // (fill inside a tile) and with rate-controlled wells (their columns are
-// outside the ILU).
-inline bool red_rows_exact(const cpr_ctx* c) {
-  return !precond_fp32(c) && c->opt.ilu_order == CPR_ILU_RED_BLACK && c->nrate == 0;
+// outside the ILU).  A mixed solve is not counted after its FP64 fallback
+// either: it works on whole vectors from end to end.
+inline bool red_rows_exact(const cpr_options_t& o, int nrate) {
+  return o.precision != CPR_PREC_MIXED && o.ilu_order == CPR_ILU_RED_BLACK && nrate == 0;
 }
+inline bool red_rows_exact(const cpr_ctx* c) { return red_rows_exact(c->opt, c->nrate); }
+// Whether FGMRES keeps its basis as black halves.  Delayed CGS2 holds up to 32
+// vectors' coefficients in registers; longer restarts use CGS2, as the oracle
+// does, on whole vectors.
+inline bool dcgs2_cycles(const cpr_options_t& o) { return o.orth == CPR_ORTH_DCGS2 && o.restart <= 32; }
+inline bool black_row_cycles(const cpr_options_t& o, int nrate) { return dcgs2_cycles(o) && red_rows_exact(o, nrate); }
 
-// ||x||^2, its red cells' share, ||x - y||^2
+// ||x||^2, its red cells' share (0 unless asked for by colour), ||x - y||^2
 struct Norms {
   double all = 0.0, red = 0.0, diff = 0.0;
 };
@@ -541,4 +548,4 @@ void launch_newton_update(int b, int n, int nrate, double pb_min, double* x, con
 // Bubble-point floor of the black-oil update: the first PVT pressure node.
 inline double pb_floor(const FluidDev& f) { return f.model == 3 ? f.pvt[0][0] : 0.0; }
 int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double* out);
-int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, Norms* n);
+int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, bool by_colour, Norms* n);

@@ -56,6 +56,12 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// Lane k's value (k the same in all lanes).
+__device__ inline double lane_value(double v, int k) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                          __builtin_amdgcn_readlane(__double2loint(v), k));
+}
+
 // Values that the last workgroup of a kernel reads from the others.  Stored
 // and loaded at agent scope (past the XCDs' own L2s); a workgroup's thread 0
 // stores its values, waits for them and only then counts itself as arrived
@@ -305,7 +311,10 @@ enum { D_RED = 704, R_V = 0, R_U = 64, R_ADD = 65 };
 
 // The totals of step j's dots (one workgroup per row, fixed order), and by
 // the last workgroup to finish the step's scalars (lane i = basis vector i <
-// j <= 32; sums by a fixed butterfly): beta = sqrt(e - |a|^2) (1 at step 0,
+// j <= 32; sums by a fixed butterfly, or, of whole vectors, one after the
+// other: the FP32 preconditioner turns a last bit of a vector's norm into
+// other roundings of its entries, so that route keeps its order of summation
+// for good): beta = sqrt(e - |a|^2) (1 at step 0,
 // which has no vector to reorthogonalise) and g = (d - a.c) / beta; flag = 1
 // when beta^2 <= 0.  red (black-row cycles): the dots lack the red halves'
 // share, multiple * multiple * s0 with s0 = |v_0,red|^2; uh's multiple is
@@ -339,7 +348,18 @@ __global__ __launch_bounds__(KB) void dcgs_coef_kernel(int j, const double* __re
     host[S_A + i] = a;
     host[S_C + i] = c;
   }
-  const double aa = wave_sum(a * a), ac = wave_sum(a * c);
+  double aa, ac;
+  if (red) {
+    aa = wave_sum(a * a);
+    ac = wave_sum(a * c);
+  } else {
+    aa = ac = 0.0;
+    for (int k = 0; k < j; ++k) {
+      const double ak = lane_value(a, k);
+      aa = __builtin_fma(ak, ak, aa);
+      ac = __builtin_fma(ak, lane_value(c, k), ac);
+    }
+  }
   const double ra = wave_sum(a * rv), rcv = wave_sum(c * rv);
   if (i != 0) return;
   const double own = red ? uh * uh * s0 : 0.0;
@@ -431,8 +451,9 @@ __global__ __launch_bounds__(KB) void dcgs_update_kernel(long len, long nh, int 
 }
 
 // part rows 0 and 1: this block's share of the squares of x's black and red
-// cells (b planes of n = 2 nh cells; nh = 0: all in row 0), row 2: of x - y
-// when y is given.
+// cells (b planes of n = 2 nh cells; nh = 0: all in row 0, in the order and
+// with the fused multiply-adds of orth_kernel, so that the norm of a whole
+// vector is reduce_dot's to the bit), row 2: of x - y when y is given.
 __global__ __launch_bounds__(KB) void colour_norms_kernel(long len, long nh, const double* __restrict__ x,
                                                           const double* __restrict__ y, double* __restrict__ part,
                                                           int nblk) {
@@ -446,13 +467,13 @@ __global__ __launch_bounds__(KB) void colour_norms_kernel(long len, long nh, con
   for (int q = 0; q < CHUNK; ++q) acc[q] = 0.0;
   for (long e = beg + threadIdx.x; e < end; e += KB) {
     const long c = e - 2 * nh * ((e >= 2 * nh ? 1 : 0) + (e >= 4 * nh ? 1 : 0));
-    const double a = x[e], v = a * a;
+    const double a = x[e];
     const bool red = c < nh;
-    acc[0] += red ? 0.0 : v;
-    acc[1] += red ? v : 0.0;
+    acc[0] = red ? acc[0] : __builtin_fma(a, a, acc[0]);
+    acc[1] = red ? __builtin_fma(a, a, acc[1]) : acc[1];
     if (y) {
       const double d = a - y[e];
-      acc[2] += d * d;
+      acc[2] = __builtin_fma(d, d, acc[2]);
     }
   }
   block_sum_chunk(acc, 3, sh, tot);
@@ -685,11 +706,11 @@ int reduce_dot(cpr_ctx* ctx, const double* a, const double* b, long len, double*
   return CPR_OK;
 }
 
-// ||x||^2, its red cells' share (0 with rate wells, whose vectors are longer)
-// and, when y is given, ||x - y||^2 (host), in one pass.  Syncs.
-int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, Norms* n) {
+// ||x||^2, with by_colour (no rate wells, whose vectors are longer) its red
+// cells' share, and, when y is given, ||x - y||^2 (host), in one pass.  Syncs.
+int reduce_norms(cpr_ctx* ctx, const double* x, const double* y, bool by_colour, Norms* n) {
   hipStream_t s = ctx->stream;
-  const long nh = ctx->nrate ? 0 : ctx->lay.nh;
+  const long nh = by_colour ? ctx->lay.nh : 0;
   colour_norms_kernel<<<ctx->nblk, KB, 0, s>>>(vec_len(ctx), nh, x, y, ctx->part, ctx->nblk);
   reduce_kernel<<<y ? 3 : 2, KB, 0, s>>>(ctx->part, ctx->nblk, ctx->hdev, nullptr, ctx->hhost_dev);
   CPR_TRY(hipGetLastError());
@@ -917,9 +938,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
   const int max_iter = ctx->opt.max_iter;
   const int nblk = ctx->nblk;
   const int eb = div_up(len, 256);
-  // delayed CGS2 keeps up to 32 vectors' coefficients in registers; longer
-  // restarts use CGS2 (as the oracle does)
-  const bool dcgs = ctx->opt.orth == CPR_ORTH_DCGS2 && m <= 32;
+  const bool dcgs = dcgs2_cycles(ctx->opt), black = black_row_cycles(ctx->opt, ctx->nrate);
   double* x = ctx->xs;
   double* r = ctx->tmp;
   cpr_stats_t S = {};
@@ -937,15 +956,12 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
   // From zero: x is written by the first cycle's update, and the first
   // residual is the right-hand side, so one reduction gives both norms.
   const bool from_x0 = ctx->opt.x0 != 0;
-  const bool colours = dcgs && ctx->nrate == 0;
   Norms nb;
   int rc = CPR_OK;
   if (known)
     nb = *known;
-  else if (colours && !from_x0)
-    rc = reduce_norms(ctx, ctx->rs, nullptr, &nb);
   else
-    rc = reduce_dot(ctx, ctx->rs, ctx->rs, len, &nb.all);
+    rc = reduce_norms(ctx, ctx->rs, nullptr, black, &nb);
   if (rc) return rc;
   const double bb = nb.all, bb_red = nb.red;
   double bnorm = std::sqrt(bb);
@@ -976,7 +992,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
     double rr = bb, rr_red = bb_red;
     if (!first) {
       Norms nr;
-      rc = colours ? reduce_norms(ctx, r, nullptr, &nr) : reduce_dot(ctx, r, r, len, &nr.all);
+      rc = reduce_norms(ctx, r, nullptr, black, &nr);
       if (rc) return rc;
       rr = nr.all;
       rr_red = nr.red;
@@ -1014,7 +1030,7 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
     int k = 0;
     if (dcgs) {
       ctx->kry_half = 0;
-      const double s0 = red_rows_exact(ctx) ? rr_red / rr : -1.0;   // |v_0,red|^2, v_0 = r / beta
+      const double s0 = black ? rr_red / rr : -1.0;   // |v_0,red|^2, v_0 = r / beta
       if ((rc = dcgs2_cycle(ctx, beta, bnorm, s0, its, k, H, g)) != CPR_OK) {
         if (st) *st = S;
         return rc;

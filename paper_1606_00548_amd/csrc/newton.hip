@@ -39,6 +39,7 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
   const int b = ctx->b;
   const long len = vec_len(ctx);
   const bool bicg = no.krylov == CPR_KRYLOV_BICGSTAB;
+  const bool by_colour = !bicg && black_row_cycles(lin, ctx->nrate);   // what the linear solve takes over
   cpr_newton_stats_t S = {};
   double dt = dt_days;
   int rc;
@@ -49,7 +50,7 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
     ctx->assembled = 1;
     ctx->setup_done = 0;
     Norms nb;   // of the residual, which the linear solve takes over
-    if ((rc = reduce_norms(ctx, ctx->rs, nullptr, &nb)) != CPR_OK) return rc;
+    if ((rc = reduce_norms(ctx, ctx->rs, nullptr, by_colour, &nb)) != CPR_OK) return rc;
     double bn = std::sqrt(nb.all);
     const double b0 = bn;
     double bn_prev = 0.0, rn_prev = 0.0, diff_prev = 0.0;
@@ -77,7 +78,7 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
       launch_newton_update(b, ctx->lay.n, ctx->nrate, pb_floor(ctx->fl), x_cs, ctx->xs, s);
       if ((rc = launch_assemble(ctx, xold_cs, x_cs, dt, ctx->rs, false)) != CPR_OK) return rc;
       ctx->setup_done = 0;
-      rc = reduce_norms(ctx, ctx->rs, no.forcing == CPR_FORCING_EW1 ? r : nullptr, &nb);
+      rc = reduce_norms(ctx, ctx->rs, no.forcing == CPR_FORCING_EW1 ? r : nullptr, by_colour, &nb);
       if (rc != CPR_OK) return rc;
       bn_prev = bn;
       rn_prev = std::sqrt(rr);
