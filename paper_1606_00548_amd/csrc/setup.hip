@@ -934,7 +934,9 @@ int setup_cpr(cpr_ctx* ctx) {
     double* si = ctx->gj_work + (size_t)nb * nb;
     schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, s>>>(last.lay, last.A, sb, ctx->flag);
     CPR_TRY(hipEventRecord(ctx->ev_rap, s));
-    if (nb <= 64) {
+    if (nb == 0) {
+      // a single, red cell: nothing to invert, schur_expand_kernel forms 1 / A
+    } else if (nb <= 64) {
       schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
     } else if (nb <= 128) {
       schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
