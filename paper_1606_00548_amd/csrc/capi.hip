@@ -151,7 +151,7 @@ int create_impl(const cpr_grid_t* g, const cpr_fluid_t* f, const double* perm3, 
   ALLOC(ctx->xs, NV);
   ALLOC(ctx->rs, NV);
   ALLOC(ctx->tmp, NV);
-  ALLOC(ctx->flag, 4);
+  ALLOC(ctx->flag, FLAGS);
   ALLOC(ctx->lnk, N);
   ALLOC(ctx->rprime, N);
   ALLOC(ctx->qbuf, N);

@@ -266,6 +266,11 @@ struct PhaseTimer {
   double inner_ms[PH_INNER] = {};
 };
 
+// cpr_ctx::flag: setup's findings (a singular block or operator, cells without
+// quasi-IMPES weights, a coarsest level to be inverted with full pivoting) and
+// the counters of the Krylov kernels' last workgroups
+enum { FLAG_SINGULAR = 0, FLAG_QIMPES, FLAG_LAST_DOTS, FLAG_LAST_UPDATE, FLAG_PIVOT, FLAGS };
+
 struct cpr_ctx {
   std::string err;
   DevAlloc mem;                // device allocator taken at creation
@@ -324,7 +329,7 @@ struct cpr_ctx {
   double* cinv = nullptr;      // dense inverse of the coarsest level (column major)
   float* cinvf = nullptr;
   double* gj_work = nullptr;   // Gauss-Jordan workspace
-  int* flag = nullptr;         // device: singular, quasi-IMPES fallbacks, two last-workgroup counters
+  int* flag = nullptr;         // device, see FLAG_SINGULAR
   int qimpes_bad = 0;
 
   // Krylov workspace (colour-split)

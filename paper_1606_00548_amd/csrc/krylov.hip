@@ -758,7 +758,7 @@ void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const doub
   // of them that is less than the reduction's launch (3.5 to 5 us), for 768
   // (128x128x32) it was 11 us.
   constexpr int UPDATE_LAST = 128;
-  int* counter = nblk <= UPDATE_LAST ? ctx->flag + 3 : nullptr;
+  int* counter = nblk <= UPDATE_LAST ? ctx->flag + FLAG_LAST_UPDATE : nullptr;
   if (j <= 8)
     dcgs_update_kernel<8><<<nblk, KB, 0, s>>>(len, nh, j, ctx->V, stride, uh, w, coef, ctx->part, nblk, add, nrm,
                                               host, counter);
@@ -860,7 +860,7 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, double s0, int& its, in
       PhaseScope ps(ctx, PH_ORTH);
       dcgs_dots(ctx, nh, j, uj, w);
       dcgs_coef_kernel<<<2 * j + 2, KB, 0, s>>>(j, ctx->part, nblk, hd + D_DOTS, hd + D_COEF, slot, red, s0, hd + D_NRM,
-                                                ctx->flag + 2);
+                                                ctx->flag + FLAG_LAST_DOTS);
       dcgs_update(ctx, nh, j, uj, w, hd + D_COEF, black ? red + R_ADD : nullptr, hd + D_NRM, slot + S_NRM);
     }
     CPR_TRY(hipGetLastError());

@@ -299,6 +299,10 @@ __global__ void gj_step_kernel(int nc, int p, const double* __restrict__ src, do
 }
 
 constexpr int SCHUR_MAX = 512;   // coarsest levels up to this size are inverted through the Schur complement
+// ... of those above this size, the ones whose red diagonals are no pivots by
+// Gauss-Jordan over all rows (below); up to it a red diagonal of zero is an error
+constexpr int SCHUR_ONLY_MAX = 128;
+constexpr double PIVOT_GROWTH = 64.0;
 
 // Coarsest inverse through the red-black Schur complement (nc <= 512).  A
 // 7-point operator couples red cells only to black ones, so with the cells
@@ -308,8 +312,13 @@ constexpr int SCHUR_MAX = 512;   // coarsest levels up to this size are inverted
 // Only S (at most 256 x 256) goes through Gauss-Jordan with partial
 // pivoting, in one workgroup (schur_invert_kernel); B and C have at most six
 // entries per row and column, so S and the other blocks are short sums, one
-// thread per entry (schur_build_kernel, schur_expand_kernel).  A zero or non-finite red
-// diagonal or S pivot sets the singular flag.
+// thread per entry (schur_build_kernel, schur_expand_kernel).  The red cells are
+// eliminated by their diagonals, without pivoting.  A pressure operator's
+// diagonal is at least about the size of its cell's couplings, but decoupled or
+// imported systems need not be like that: where a multiplier (a black row's
+// coupling to a red cell over that cell's diagonal) exceeds PIVOT_GROWTH, two
+// decimal digits, or a red diagonal or S pivot is zero or not finite, the flag
+// is set.
 //
 // Position of coarsest cell t among the cells of its colour: its place in
 // the colour's half, or t / 2 in natural order (nx is odd there, so colours
@@ -346,10 +355,21 @@ __device__ inline unsigned wave_max(unsigned k) {
 // S = Db - C Dr^-1 B (row major), one thread per entry: black cells couple
 // through the red cells adjacent to both.
 __global__ __launch_bounds__(256) void schur_build_kernel(Lay L, const double* __restrict__ A, double* __restrict__ S,
-                                                          int* __restrict__ flag) {
+                                                          double growth, int* __restrict__ flag) {
   const int nc = L.n, nb = L.cs ? L.nh : nc / 2;
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < nc && colour_of(L, g) == 0 && (!(fabs(A[g]) > TINY) || !isfinite(A[g]))) atomicExch(flag, 1);
+  if (g < nc && colour_of(L, g) == 0) {
+    const double d = fabs(A[g]);
+    double most = 0.0;   // of the black rows' couplings to this cell
+    int i, j, k;
+    lay_coords(L, g, i, j, k);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      const int n = lay_nbr(L, i, j, k, e + 1);
+      if (n >= 0) most = fmax(most, fabs(A[(size_t)((e ^ 1) + 1) * nc + n]));
+    }
+    if (!(d > TINY) || !isfinite(d) || most > growth * d) atomicExch(flag, 1);
+  }
   if (g >= nb * nb) return;
   const int t1 = black_cell(L, g / nb), t2 = black_cell(L, g % nb);
   int i, j, k, i2, j2, k2;
@@ -803,7 +823,7 @@ __global__ void ilu_tiles_kernel(Lay L, int colour, const double* __restrict__ J
 // setup's flags to pinned memory (a copy to pageable memory would be staged
 // by the runtime and waited for there)
 __global__ void report_flags_kernel(const int* __restrict__ flag, int* __restrict__ host) {
-  if (threadIdx.x < 2) host[threadIdx.x] = flag[threadIdx.x];
+  if (threadIdx.x < FLAGS) host[threadIdx.x] = flag[threadIdx.x];
 }
 
 __global__ void zero_int_kernel(int* p, int n) {
@@ -886,8 +906,35 @@ static void launch_decoupling(cpr_ctx* ctx) {
     abf_kernel<B, MIXED><<<nb, 64, 0, ctx->stream>>>(n, ctx->J, ctx->Wabf, ctx->R0, ctx->Jt, L0.A, ctx->flag, ctx->Jf,
                                                      L0.Af);
   else
-    qimpes_kernel<B, MIXED><<<nb, 64, 0, ctx->stream>>>(n, ctx->J, ctx->w, ctx->R0, L0.A, ctx->flag + 1, ctx->Jf,
-                                                        L0.Af);
+    qimpes_kernel<B, MIXED><<<nb, 64, 0, ctx->stream>>>(n, ctx->J, ctx->w, ctx->R0, L0.A, ctx->flag + FLAG_QIMPES,
+                                                        ctx->Jf, L0.Af);
+}
+
+// Coarsest inverse by Gauss-Jordan with partial pivoting over all rows, one
+// launch a column.
+static void launch_pivoted_inverse(cpr_ctx* ctx) {
+  hipStream_t s = ctx->stream;
+  const MGLevel& last = ctx->levels.back();
+  const int nc = last.lay.n;
+  double* bufA = ctx->gj_work;
+  double* bufB = ctx->gj_work + (size_t)nc * 2 * nc;
+  dense_build_kernel<<<div_up(nc, 256), 256, 0, s>>>(last.lay, last.A, bufA);
+  int gblocks = div_up((long)nc * 2 * nc, 256);
+  if (gblocks > 512) gblocks = 512;
+  for (int p = 0; p < nc; ++p) {
+    gj_step_kernel<<<gblocks, 256, 0, s>>>(nc, p, bufA, bufB, ctx->flag);
+    double* t = bufA; bufA = bufB; bufB = t;
+  }
+  gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(nc, bufA, ctx->cinv, ctx->cinvf);
+}
+
+// setup's flags, once its kernels have run.  Syncs.
+static int read_flags(cpr_ctx* ctx, int (&flag)[FLAGS]) {
+  report_flags_kernel<<<1, 64, 0, ctx->stream>>>(ctx->flag, reinterpret_cast<int*>(ctx->hhost_dev + 8));
+  CPR_TRY(hipGetLastError());
+  CPR_TRY(hipStreamSynchronize(ctx->stream));
+  for (int q = 0; q < FLAGS; ++q) flag[q] = reinterpret_cast<const int*>(ctx->hhost + 8)[q];
+  return CPR_OK;
 }
 
 int setup_cpr(cpr_ctx* ctx) {
@@ -896,7 +943,7 @@ int setup_cpr(cpr_ctx* ctx) {
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   const int n = L.n;
-  zero_int_kernel<<<1, 64, 0, s>>>(ctx->flag, 4);   // and the counters of the Krylov kernels' last workgroups
+  zero_int_kernel<<<1, 64, 0, s>>>(ctx->flag, FLAGS);   // and the counters of the Krylov kernels' last workgroups
   // The FP32 copies of a mixed preconditioner (decoupled blocks, levels, ILU
   // diagonals) are stored by the kernels that form the values: passes of their
   // own read them again (256x256x64 black oil: 625 us of the decoupling and
@@ -932,37 +979,31 @@ int setup_cpr(cpr_ctx* ctx) {
     const int nb = last.lay.cs ? last.lay.nh : nc / 2;
     double* sb = ctx->gj_work;
     double* si = ctx->gj_work + (size_t)nb * nb;
-    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, s>>>(last.lay, last.A, sb, ctx->flag);
+    const bool only = nc <= SCHUR_ONLY_MAX;
+    int* bad = ctx->flag + (only ? FLAG_SINGULAR : FLAG_PIVOT);
+    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, s>>>(last.lay, last.A, sb,
+                                                                         only ? HUGE_VAL : PIVOT_GROWTH, bad);
     CPR_TRY(hipEventRecord(ctx->ev_rap, s));
     if (nb == 0) {
       // a single, red cell: nothing to invert, schur_expand_kernel forms 1 / A
     } else if (nb <= 64) {
-      schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<1, 4, 16><<<1, 1024, 0, s>>>(nb, sb, si, bad);
     } else if (nb <= 128) {
-      schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<2, 8, 16><<<1, 1024, 0, s>>>(nb, sb, si, bad);
     } else if (nb <= 192) {
-      schur_lanes_kernel<3, 12, 16><<<1, 1024, 0, s>>>(nb, sb, si, ctx->flag);
+      schur_lanes_kernel<3, 12, 16><<<1, 1024, 0, s>>>(nb, sb, si, bad);
     } else if (nb <= 224) {
-      schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, s>>>(nb, sb, si, ctx->flag);
+      schur_invert_kernel<224, 32, 16, 14><<<1, 512, 0, s>>>(nb, sb, si, bad);
     } else {
       constexpr int lds = 4 * 8 * 512 * sizeof(double);   // a quarter of the 256 x 256 matrix
       CPR_TRY(hipFuncSetAttribute((const void*)schur_invert_kernel<256, 32, 16, 12>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-      schur_invert_kernel<256, 32, 16, 12><<<1, 512, lds, s>>>(nb, sb, si, ctx->flag);
+      schur_invert_kernel<256, 32, 16, 12><<<1, 512, lds, s>>>(nb, sb, si, bad);
     }
     schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
   } else {
     CPR_TRY(hipEventRecord(ctx->ev_rap, s));
-    double* bufA = ctx->gj_work;
-    double* bufB = ctx->gj_work + (size_t)nc * 2 * nc;
-    dense_build_kernel<<<div_up(nc, 256), 256, 0, s>>>(last.lay, last.A, bufA);
-    int gblocks = div_up((long)nc * 2 * nc, 256);
-    if (gblocks > 512) gblocks = 512;
-    for (int p = 0; p < nc; ++p) {
-      gj_step_kernel<<<gblocks, 256, 0, s>>>(nc, p, bufA, bufB, ctx->flag);
-      double* t = bufA; bufA = bufB; bufB = t;
-    }
-    gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(nc, bufA, ctx->cinv, ctx->cinvf);
+    launch_pivoted_inverse(ctx);
   }
   hipStream_t a = ctx->aux;
   CPR_TRY(hipStreamWaitEvent(a, ctx->ev_rap, 0));
@@ -989,12 +1030,15 @@ int setup_cpr(cpr_ctx* ctx) {
   CPR_TRY(hipStreamWaitEvent(s, ctx->ev_ilu, 0));
   rc = launch_check(ctx, "cpr_setup kernels");
   if (rc != CPR_OK) return rc;
-  int* hflag = reinterpret_cast<int*>(ctx->hhost + 8);
-  report_flags_kernel<<<1, 64, 0, s>>>(ctx->flag, reinterpret_cast<int*>(ctx->hhost_dev + 8));
-  CPR_TRY(hipGetLastError());
-  CPR_TRY(hipStreamSynchronize(s));
-  ctx->qimpes_bad = hflag[1];
-  if (hflag[0]) return set_err(ctx, CPR_ESINGULAR, "singular ILU diagonal block or coarsest operator");
+  int flag[FLAGS];
+  if ((rc = read_flags(ctx, flag)) != CPR_OK) return rc;
+  if (flag[FLAG_PIVOT] && !flag[FLAG_SINGULAR]) {
+    launch_pivoted_inverse(ctx);
+    if ((rc = launch_check(ctx, "cpr_setup kernels")) != CPR_OK) return rc;
+    if ((rc = read_flags(ctx, flag)) != CPR_OK) return rc;
+  }
+  ctx->qimpes_bad = flag[FLAG_QIMPES];
+  if (flag[FLAG_SINGULAR]) return set_err(ctx, CPR_ESINGULAR, "singular ILU diagonal block or coarsest operator");
   ctx->setup_done = 1;
   return CPR_OK;
 }
