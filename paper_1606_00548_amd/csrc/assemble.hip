@@ -74,12 +74,15 @@ double pvt_eval(const FluidDev& f, int row, double p) {
 
 // x / s given rs = RN(1 / s): two residual corrections of x rs, the second
 // of which rounds correctly (Markstein, IBM J. Res. Dev. 34, 1990) for every
-// quotient in the normal range; five operations instead of the dozen of a
-// division, for the many quotients by the same few denominators.
+// quotient in the normal range, and the hardware's fix-up of the special ones
+// (zeros, infinities: a residual would be inf - inf or 0 inf); six operations
+// instead of the dozen of a division, for the many quotients by the same few
+// denominators.
 __device__ inline double div_by(double x, double s, double rs) {
   double q = x * rs;
   q = __builtin_fma(__builtin_fma(-q, s, x), rs, q);
-  return __builtin_fma(__builtin_fma(-q, s, x), rs, q);
+  q = __builtin_fma(__builtin_fma(-q, s, x), rs, q);
+  return __builtin_amdgcn_div_fixup(q, s, x);
 }
 
 // The PVT table in LDS: nodes, then value and slope of each row's segments
