@@ -350,8 +350,9 @@ struct cpr_ctx {
   double* hhost = nullptr;     // pinned host mirror
   double* hhost_dev = nullptr; // its device address (kernels write the Hessenberg column there)
   int nblk = 0;
-  // black-row Krylov cycle (krylov.hip): basis vectors of the last FGMRES
-  // cycle whose red halves are kept as scalars (0: stored whole)
+  // black-row Krylov cycle (krylov.hip): slots of the last FGMRES cycle that
+  // hold final basis vectors, whose red halves are kept as scalars like that
+  // of the vector behind them (0: stored whole)
   int kry_half = 0;
 
   // kernel-duration sampling (one kernel class at a time)

@@ -865,6 +865,7 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, double s0, int& its, in
     }
     CPR_TRY(hipGetLastError());
     CPR_TRY(hipEventRecord(ctx->ev_iter[j & 1], s));
+    if (black) ctx->kry_half = j + 1;
     return CPR_OK;
   };
   double nu_prev = 0.0, est = beta;
@@ -910,16 +911,16 @@ int dcgs2_cycle(cpr_ctx* ctx, double beta, double bnorm, double s0, int& its, in
     if (learned_on(ctx)) learned_discard_last(ctx);
   }
   givens_qr(Hh, m, k, beta, R, g);
-  if (black) ctx->kry_half = k;
   return CPR_OK;
 }
 
 void krylov_vector(cpr_ctx* ctx, int j, double* dst) {
   const long len = vec_len(ctx);
   const double* vj = ctx->V + (size_t)j * len;
-  if (j > 0 && j < ctx->kry_half)
-    whole_vector_kernel<<<div_up(len, 256), 256, 0, ctx->stream>>>(len, ctx->lay.nh, ctx->V, vj,
-                                                                   ctx->hdev + D_RED + R_V + j, dst);
+  // behind the final vectors lies the unnormalised u of the last step
+  if (j > 0 && j <= ctx->kry_half)
+    whole_vector_kernel<<<div_up(len, 256), 256, 0, ctx->stream>>>(
+        len, ctx->lay.nh, ctx->V, vj, ctx->hdev + D_RED + (j < ctx->kry_half ? R_V + j : R_U), dst);
   else
     (void)hipMemcpyAsync(dst, vj, len * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream);
 }
