@@ -62,12 +62,12 @@ __device__ inline double lane_value(double v, int k) {
                           __builtin_amdgcn_readlane(__double2loint(v), k));
 }
 
-// Values that the last workgroup of a kernel reads from the others.  Stored
-// and loaded at agent scope (past the XCDs' own L2s); a workgroup's thread 0
-// stores its values, waits for them and only then counts itself as arrived
-// (last_block), so the last to arrive sees them all.  No fence is needed for
-// them, and none of the kernel's other stores is read.  The last workgroup
-// leaves the counter at zero for the next kernel.
+// Values that the last workgroup of a kernel reads from the others, stored and
+// loaded at agent scope (past the XCDs' own L2s).  A workgroup's thread 0
+// stores its values and then counts itself as arrived with release and acquire
+// (last_block); a barrier hands what it acquired to its workgroup, so the last
+// to arrive sees them all.  The last workgroup leaves the counter at zero for
+// the next kernel.
 __device__ inline void put_agent(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -76,8 +76,7 @@ __device__ inline double get_agent(const double* p) {
 }
 __device__ inline bool last_block(int* counter, int* sh) {
   if (threadIdx.x == 0) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     *sh = old == (int)gridDim.x - 1;
     if (*sh) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
