@@ -26,6 +26,8 @@
 // down to the dense coarsest solve run in one single-workgroup kernel where
 // they fit its LDS (cycle_fused_level), which removes a dozen latency-bound
 // launches per cycle.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace {
@@ -405,6 +407,29 @@ __global__ __launch_bounds__(GV_ROWS * GV_PARTS) void coarse_gemv_kernel(int nc,
   if (part == 0 && row < nc) {
     double t = 0.0;
     for (int q = 0; q < GV_PARTS; ++q) t += sh[q][lr];
+    x[row] = (T)t;
+  }
+}
+
+// The same for a mixed solve's FP64 fallback, which keeps one order of its
+// sums for good (fallback_inverse): `parts` interleaved partial sums a row (as
+// many as 1,024 threads hold of nc rows), added up in turn.
+template <typename T>
+__global__ __launch_bounds__(1024) void coarse_parts_kernel(int nc, int parts, const double* __restrict__ inv,
+                                                            const T* __restrict__ r, T* __restrict__ x) {
+  __shared__ double sh[1024];
+  const int rows = nc < GV_ROWS ? nc : GV_ROWS;   // a workgroup's; rows * parts <= 1,024
+  const int lr = threadIdx.x % rows, part = threadIdx.x / rows;
+  const int row = blockIdx.x * rows + lr;
+  if (part < parts && row < nc) {
+    double s = 0.0;
+    for (int c = part; c < nc; c += parts) s += inv[(size_t)c * nc + row] * (double)r[c];
+    sh[part * rows + lr] = s;
+  }
+  __syncthreads();
+  if (part == 0 && row < nc) {
+    double t = 0.0;
+    for (int p = 0; p < parts; ++p) t += sh[p * rows + lr];
     x[row] = (T)t;
   }
 }
@@ -1268,6 +1293,10 @@ int fused_level(const cpr_ctx* ctx) {
   return fuse;
 }
 
+const double* coarsest_inverse(const cpr_ctx* ctx) {
+  return mixed_fallback(ctx) && ctx->cinv64 ? ctx->cinv64 : ctx->cinv;
+}
+
 template <typename T>
 CoarseArgs<T> coarse_args(cpr_ctx* ctx, int first) {
   CoarseArgs<T> a;
@@ -1279,7 +1308,7 @@ CoarseArgs<T> coarse_args(cpr_ctx* ctx, int first) {
     a.x[q] = Pre<T>::x(L);
     a.r[q] = Pre<T>::r(L);
   }
-  a.inv = ctx->cinv;
+  a.inv = coarsest_inverse(ctx);
   a.alpha = (T)ctx->opt.mg_alpha;
   a.pre = ctx->opt.mg_pre;
   a.post = ctx->opt.mg_post;
@@ -1358,8 +1387,12 @@ void vcycle(cpr_ctx* ctx, bool skip_last_red) {
     if (e != hipSuccess) set_hip_err(ctx, e, "coarse_cycle_kernel");
   } else {
     MGLevel& L = ctx->levels.back();
-    coarse_gemv_kernel<T><<<div_up(nc, GV_ROWS), GV_ROWS * GV_PARTS, 0, s>>>(nc, ctx->cinv, Pre<T>::r(L),
-                                                                             Pre<T>::x(L));
+    if (mixed_fallback(ctx))
+      coarse_parts_kernel<T><<<div_up(nc, std::min(nc, GV_ROWS)), 1024, 0, s>>>(
+          nc, nc <= DENSE_FUSED_MAX && nl <= MAXLV ? 1024 / nc : 1, coarsest_inverse(ctx), Pre<T>::r(L), Pre<T>::x(L));
+    else
+      coarse_gemv_kernel<T><<<div_up(nc, GV_ROWS), GV_ROWS * GV_PARTS, 0, s>>>(nc, ctx->cinv, Pre<T>::r(L),
+                                                                               Pre<T>::x(L));
   }
   for (int l = down - 1; l >= 0; --l) {
     MGLevel& L = ctx->levels[l];

@@ -328,6 +328,8 @@ struct cpr_ctx {
   std::vector<MGLevel> levels;
   double* cinv = nullptr;      // dense inverse of the coarsest level (column major)
   float* cinvf = nullptr;
+  double* cinv64 = nullptr;    // that of a mixed solve's FP64 fallback (fallback_inverse; up to 512 cells)
+  bool cinv64_done = false;
   double* gj_work = nullptr;   // Gauss-Jordan workspace
   int* flag = nullptr;         // device, see FLAG_SINGULAR
   int qimpes_bad = 0;
@@ -481,6 +483,7 @@ hipError_t vec_cs_to_nat(cpr_ctx* ctx, const double* src, double* dst);
 
 // setup.hip
 int setup_cpr(cpr_ctx* ctx);
+int fallback_inverse(cpr_ctx* ctx);
 
 // apply.hip
 // z = M^-1 v.  If nrm2 (device) is given, vin holds an unnormalised Krylov
@@ -519,6 +522,8 @@ int time_step(cpr_ctx* ctx, const double* xold_cs, double* x_cs, double dt_days,
 // krylov.hip
 // The preconditioner runs in FP32: MIXED precision and no FP64 fallback.
 inline bool precond_fp32(const cpr_ctx* c) { return c->opt.precision == CPR_PREC_MIXED && !c->fp64_now; }
+// A mixed solve applies plain FP64 CPR after a stalled cycle.
+inline bool mixed_fallback(const cpr_ctx* c) { return c->opt.precision == CPR_PREC_MIXED && c->fp64_now; }
 // The learned stage runs: requested, and no stalled cycle has handed the
 // solve to plain FP64 CPR.
 inline bool learned_on(const cpr_ctx* c) { return c->opt.learned && !c->fp64_now; }

@@ -1021,6 +1021,10 @@ int fgmres_solve(cpr_ctx* ctx, cpr_stats_t* st, const Norms* known) {
         ctx->opt.stall_ratio > 0 && beta > ctx->opt.stall_ratio * beta_start) {
       ctx->fp64_now = true;
       S.fp64_fallback = S.cycles;
+      if (mixed_fallback(ctx) && (rc = fallback_inverse(ctx)) != CPR_OK) {
+        if (st) *st = S;
+        return rc;
+      }
     }
     beta_start = beta;
     scale_kernel<<<eb, 256, 0, s>>>(len, beta, first ? ctx->rs : r, ctx->V);

@@ -403,10 +403,10 @@ __global__ __launch_bounds__(256) void schur_build_kernel(Lay L, const double* _
 // remembered, and the exchange form leaves M[q_p][p'] = S^-1[p][q_p'].  The
 // pivot's magnitude is compared in its leading 23 bits (exponent and 12 bits
 // of the mantissa, the row index below them: the lowest row of nearly equal
-// ones), which bounds the multipliers by 1 + 2^-12.
+// ones), which bounds the multipliers by 1 + 2^-12; with EXACT in full.
 // A 432-cell coarsest level (192x192x48) takes 403 us with the kernels around
 // it (383 here), where one launch per column of the whole operator took 2680.
-template <int NB, int TR, int TC, int CR>
+template <int NB, int TR, int TC, int CR, bool EXACT = false>
 __global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const double* __restrict__ S,
                                                                double* __restrict__ out, int* __restrict__ flag) {
   constexpr int NT = TR * TC, RR = NB / TR, CC = NB / TC, NS = (NB + 63) / 64;
@@ -436,14 +436,30 @@ __global__ __launch_bounds__(TR * TC) void schur_invert_kernel(int nb, const dou
   __syncthreads();
   for (int p = 0; p < nb; ++p) {
     const double* cp = col[p & 1];
-    unsigned key = 0;
+    int q;
+    if constexpr (EXACT) {
+      static_assert(NS == 1, "a row a lane");
+      double best = used ? -1.0 : fabs(cp[lane]);
+      q = lane;
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(best, o);
+        const int oq = __shfl_xor(q, o);
+        if (ov > best || (ov == best && oq < q)) {
+          best = ov;
+          q = oq;
+        }
+      }
+      q = __builtin_amdgcn_readfirstlane(q);
+    } else {
+      unsigned key = 0;
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-      const int r = lane + 64 * i;
-      const unsigned k = (((unsigned)__double2hiint(cp[r]) & 0x7fffff00u) | (255u - (unsigned)r)) + 1u;
-      if (!((used >> i) & 1u) && k > key) key = k;
+      for (int i = 0; i < NS; ++i) {
+        const int r = lane + 64 * i;
+        const unsigned k = (((unsigned)__double2hiint(cp[r]) & 0x7fffff00u) | (255u - (unsigned)r)) + 1u;
+        if (!((used >> i) & 1u) && k > key) key = k;
+      }
+      q = (int)(255u - ((wave_max(key) - 1u) & 255u));
     }
-    const int q = (int)(255u - ((wave_max(key) - 1u) & 255u));
     const double pv = cp[q];
     if ((q & 63) == lane) used |= 1u << (q >> 6);
     if (tid == 0) {
@@ -843,6 +859,7 @@ static void free_levels(cpr_ctx* ctx) {
   ctx->levels.clear();
   dev_free(ctx->mem, ctx->cinv); ctx->cinv = nullptr;
   dev_free(ctx->mem, ctx->cinvf); ctx->cinvf = nullptr;
+  dev_free(ctx->mem, ctx->cinv64); ctx->cinv64 = nullptr;
   dev_free(ctx->mem, ctx->gj_work); ctx->gj_work = nullptr;
 }
 
@@ -890,6 +907,7 @@ static int build_hierarchy(cpr_ctx* ctx) {
   size_t nc = shapes.back().n;
   CPR_TRY(dev_malloc(ctx->mem, (void**)&ctx->cinv, nc * nc * sizeof(double)));
   CPR_TRY(dev_malloc(ctx->mem, (void**)&ctx->cinvf, nc * nc * sizeof(float)));
+  if (nc <= SCHUR_MAX) CPR_TRY(dev_malloc(ctx->mem, (void**)&ctx->cinv64, nc * nc * sizeof(double)));
   CPR_TRY(dev_malloc(ctx->mem, (void**)&ctx->gj_work, 2 * nc * 2 * nc * sizeof(double)));
   return CPR_OK;
 }
@@ -912,7 +930,7 @@ static void launch_decoupling(cpr_ctx* ctx) {
 
 // Coarsest inverse by Gauss-Jordan with partial pivoting over all rows, one
 // launch a column.
-static void launch_pivoted_inverse(cpr_ctx* ctx) {
+static void launch_pivoted_inverse(cpr_ctx* ctx, double* inv, float* invf) {
   hipStream_t s = ctx->stream;
   const MGLevel& last = ctx->levels.back();
   const int nc = last.lay.n;
@@ -925,7 +943,35 @@ static void launch_pivoted_inverse(cpr_ctx* ctx) {
     gj_step_kernel<<<gblocks, 256, 0, s>>>(nc, p, bufA, bufB, ctx->flag);
     double* t = bufA; bufA = bufB; bufB = t;
   }
-  gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(nc, bufA, ctx->cinv, ctx->cinvf);
+  gj_extract_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(nc, bufA, inv, invf);
+}
+
+// The inverse that a mixed solve's FP64 fallback applies.  A system on which
+// the FP32 preconditioner stalls amplifies last bits (a digit in the last place
+// of the coarsest solve became 1e-5 of dx after 75 iterations), so from there
+// on the solve keeps the arithmetic of one elimination for good, whichever is
+// the fastest: partial pivoting over all rows, for levels of up to 128 cells
+// over those of the Schur complement.  Formed by the first fallback after a
+// setup.
+int fallback_inverse(cpr_ctx* ctx) {
+  const MGLevel& last = ctx->levels.back();
+  const int nc = last.lay.n;
+  if (nc > SCHUR_MAX || ctx->cinv64_done) return CPR_OK;   // setup's own is that one
+  hipStream_t s = ctx->stream;
+  if (nc <= SCHUR_ONLY_MAX) {
+    const int nb = last.lay.cs ? last.lay.nh : nc / 2;
+    double* sb = ctx->gj_work;
+    double* si = ctx->gj_work + (size_t)nb * nb;
+    schur_build_kernel<<<div_up(std::max(nc, nb * nb), 256), 256, 0, s>>>(last.lay, last.A, sb, HUGE_VAL,
+                                                                         ctx->flag + FLAG_SINGULAR);
+    if (nb > 0)
+      schur_invert_kernel<64, 32, 16, 4, true><<<1, 512, 0, s>>>(nb, sb, si, ctx->flag + FLAG_SINGULAR);
+    schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(last.lay, last.A, si, ctx->cinv64, nullptr);
+  } else {
+    launch_pivoted_inverse(ctx, ctx->cinv64, nullptr);
+  }
+  ctx->cinv64_done = true;
+  return launch_check(ctx, "coarsest inverse of the FP64 fallback");
 }
 
 // setup's flags, once its kernels have run.  Syncs.
@@ -940,6 +986,7 @@ static int read_flags(cpr_ctx* ctx, int (&flag)[FLAGS]) {
 int setup_cpr(cpr_ctx* ctx) {
   int rc = build_hierarchy(ctx);
   if (rc != CPR_OK) return rc;
+  ctx->cinv64_done = false;
   hipStream_t s = ctx->stream;
   const Lay& L = ctx->lay;
   const int n = L.n;
@@ -1003,7 +1050,7 @@ int setup_cpr(cpr_ctx* ctx) {
     schur_expand_kernel<<<div_up((long)nc * nc, 256), 256, 0, s>>>(last.lay, last.A, si, ctx->cinv, ctx->cinvf);
   } else {
     CPR_TRY(hipEventRecord(ctx->ev_rap, s));
-    launch_pivoted_inverse(ctx);
+    launch_pivoted_inverse(ctx, ctx->cinv, ctx->cinvf);
   }
   hipStream_t a = ctx->aux;
   CPR_TRY(hipStreamWaitEvent(a, ctx->ev_rap, 0));
@@ -1033,7 +1080,7 @@ int setup_cpr(cpr_ctx* ctx) {
   int flag[FLAGS];
   if ((rc = read_flags(ctx, flag)) != CPR_OK) return rc;
   if (flag[FLAG_PIVOT] && !flag[FLAG_SINGULAR]) {
-    launch_pivoted_inverse(ctx);
+    launch_pivoted_inverse(ctx, ctx->cinv, ctx->cinvf);
     if ((rc = launch_check(ctx, "cpr_setup kernels")) != CPR_OK) return rc;
     if ((rc = read_flags(ctx, flag)) != CPR_OK) return rc;
   }
