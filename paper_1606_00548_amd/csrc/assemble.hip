@@ -350,7 +350,7 @@ __device__ inline void face_flow(const FaceState<MODEL>& lo, const FaceState<MOD
 // and never goes to memory; with the states in planes of their own, the
 // kernel read them 1,380 bytes a cell beyond the caches (five rows of
 // neighbours, none of them still in an XCD's L2) and was bound by that.  Now
-// 530 bytes are written and about 85 read per cell, and what bounds it is the
+// 536 bytes are written and about 85 read per cell, and what bounds it is the
 // latency of FP64 chains between the barriers with two workgroups per CU (256
 // registers a thread, 60 KB of LDS): VALU issue in a third of the wave cycles.
 // The loops over axes and evaluations stay rolled, so that the code fits the
@@ -358,8 +358,8 @@ __device__ inline void face_flow(const FaceState<MODEL>& lo, const FaceState<MOD
 // of either colour, so each store covers whole cache lines.  NAT: x_old, x
 // and rhs in natural order, else colour-split; the sums run in direction
 // order, one term after the other, whichever side of a face forms its flow.
-// The call at MODEL 3: 1615 to 896 us at 256x256x64, 225 to 146 at
-// 128x128x32; MODEL 2: 227 to 121 at 60x220x85.
+// The call at MODEL 3: 1592 to 911 us at 256x256x64, 234 to 155 at
+// 128x128x32; MODEL 2: 233 to 129 at 60x220x85.
 template <int MODEL, int TX, int TY, bool NAT>
 __global__ __launch_bounds__(TX * TY) void cell_kernel(FluidDev f, Lay L, int kz, double dz, double top, double vol,
                                                        double dt, double s0, double s1, double s2,

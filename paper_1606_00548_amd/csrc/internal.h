@@ -275,8 +275,9 @@ struct cpr_ctx {
   std::string err;
   DevAlloc mem;                // device allocator taken at creation
   hipStream_t stream = nullptr;
-  // setup runs the Galerkin chain and the coarsest inverse on a second
-  // stream (default priority) while the ILU factorisation runs on `stream`
+  // setup runs the ILU factorisation (which writes Dinv and Dinvf) on a second
+  // stream of default priority, from ev_rap (the Galerkin chain is done) on,
+  // beside the coarsest inverse on `stream`, which waits for ev_ilu at the end
   hipStream_t aux = nullptr;
   hipEvent_t ev_rap = nullptr, ev_ilu = nullptr;
   hipEvent_t ev_iter[2] = {nullptr, nullptr};   // completion of Arnoldi steps (even, odd)
@@ -491,11 +492,11 @@ int fallback_inverse(cpr_ctx* ctx);
 // equal v).  Otherwise v must equal vin.  With redc (device scalar, nrm2
 // given too) only the black half of vin is read; the red half of v is
 // *redc / sqrt(*nrm2) times that of v0.
-// Natural-order input and output in the passes at either end; false: not for this context.
-bool precond_apply_nat(cpr_ctx* ctx, const double* v, double* z);
 void precond_apply(cpr_ctx* ctx, const double* vin, double* v, const double* nrm2, double* z,
                    const double* v0 = nullptr, const double* redc = nullptr);
-
+// The same for natural-order v and z (which may overlap), permuted by its own
+// first and last kernels; false: not for this context.
+bool precond_apply_nat(cpr_ctx* ctx, const double* v, double* z);
 void precond_pressure_stage(cpr_ctx* ctx, const double* v);
 
 // learned.hip

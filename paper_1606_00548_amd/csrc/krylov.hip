@@ -753,9 +753,11 @@ void dcgs_update(cpr_ctx* ctx, long nh, int j, double* uh, double* w, const doub
   const size_t stride = (size_t)vec_len(ctx);
   const long len = nh ? ctx->b * nh : vec_len(ctx);
   prof_begin(ctx, CPR_KCLASS_ORTH);
-  // Arriving at one counter costs about 10 ns a workgroup: up to UPDATE_LAST
-  // of them that is less than the reduction's launch (3.5 to 5 us), for 768
-  // (128x128x32) it was 11 us.
+  // Arriving at one counter costs 25 to 40 ns a workgroup, the reduction a
+  // launch and the gap before it.  Update with its own sum against update +
+  // reduction (us, without the gap of 1 to 3): 6.0 against 4.2 + 2.8 for 47
+  // workgroups, 7.5 against 4.5 + 2.3 for 115, 9.8 against 4.5 + 2.4 for 192,
+  // 48 against 10 + 4 for 1,024 (128x128x32, b = 3).
   constexpr int UPDATE_LAST = 128;
   int* counter = nblk <= UPDATE_LAST ? ctx->flag + FLAG_LAST_UPDATE : nullptr;
   if (j <= 8)

@@ -10,16 +10,16 @@
 // with 3x3x3 zero-padded correlations, 2x2x2 average pooling, nearest
 // upsampling (read on the fly by the convolution that consumes it), and a
 // normalised mean-squared-error loss.  Parameters: FP32 master copy, Adam
-// moments, BF16 copies laid out as MFMA B-fragments.
+// moments, BF16 copies laid out as MFMA fragments.
 //
 // Convolutions are implicit GEMMs on the CDNA matrix cores
-// (v_mfma_f32_16x16x16_bf16, FP32 accumulation): one wavefront computes 16
-// output voxels x all output channels, looping over 27 taps x input
-// channels in K-steps of 16; activations are converted to BF16 as they are
-// loaded.  The data gradient is the same kernel with mirrored taps and
-// transposed channel blocks; the weight gradient is a GEMM over voxels
-// (M = input channels, N = output channels) whose per-workgroup partial sums
-// are reduced in a fixed order, so training is deterministic.
+// (v_mfma_f32_16x16x32_bf16, FP32 accumulation): M = output channels, N =
+// voxels, K = 27 taps x input channels in steps of 32; activations are
+// converted to BF16 as they are staged in LDS.  The data gradient is the same
+// kernel with mirrored taps and transposed channel blocks; the weight gradient
+// is a GEMM over voxels (M = input channels, N = output channels) whose
+// per-workgroup partial sums are reduced in a fixed order, so training is
+// deterministic.
 #include <cmath>
 #include <cstring>
 
@@ -96,7 +96,7 @@ __device__ inline unsigned pack_bf16x2(float a, float b) {
 struct ConvArgs {
   Geo g;
   const float* X;        // input [batch][voxel][CSRC] (half-resolution grid when UP)
-  const bf16x8* W;       // all B-fragments [NK][CO/16][64]
+  const bf16x8* W;       // all weight fragments [NK][CO/16][64]
   const float* bias;     // [CO] (EPI 1)
   const float* skip;     // [batch][voxel][CO] or null
   float* outA;           // EPI 1: relu(acc + bias) (null: not stored); EPI 0: acc
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(256, (conv_per_cu<CI, CO, UP, KS, NS>())) void conv
 // a wave reads dZ once and X~ once per dy, and the dx = -1, +1 operands are
 // funnel shifts of the dx = 0 one and a neighbour on either side.  The 27 /
 // 3 * CIB / 16 accumulators stay in registers over all of the workgroup's
-// tiles; its partial sums are added up in workgroup order by
-// wgrad_reduce_kernel.  The bias gradient sums dZ in FP32 as it is staged.
+// tiles; its partial sums are added up in a fixed order by
+// partial_sum_kernel.  The bias gradient sums dZ in FP32 as it is staged.
 // The K loop is bound by LDS reads and MFMA issue alike (per K-step, CIB =
 // 32: 80 LDS against 288 MFMA cycles a wave, three waves a workgroup on four
 // SIMDs).  Four samples of 64x64x32: 50 us for 32 to 16 channels and 24 for 3
@@ -906,11 +906,11 @@ __device__ inline void k_index(int ck, int ks, int kk, int& t, int& c) {
   }
 }
 
-// BF16 B-fragments of conv weights W[27][ci][co] (FP32 master) for
+// BF16 fragments of conv weights W[27][ci][co] (FP32 master) for
 // v_mfma_f32_16x16x32_bf16: frag[ks][nt][lane][e] is the weight at K-index
-// kk = 8*(lane/16) + e of step ks and output column nt*16 + lane%16.
-// Forward: K = (tap, ci) with ck = 4 for the 3-channel input, N = co.
-// Backward (data gradient): taps mirrored (26 - t), K = (tap, co), N = ci.
+// kk = 8*(lane/16) + e of step ks and result channel nt*16 + lane%16.
+// Forward: K = (tap, ci) with ck = 4 for the 3-channel input, M = co.
+// Backward (data gradient): taps mirrored (26 - t), K = (tap, co), M = ci.
 __global__ void frag_kernel(int ci, int ck, int co, int backward, const float* __restrict__ W,
                             bf16x8* __restrict__ frag) {
   const int nt_n = backward ? ci / 16 : co / 16;

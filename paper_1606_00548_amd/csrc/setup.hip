@@ -912,7 +912,6 @@ static int build_hierarchy(cpr_ctx* ctx) {
   return CPR_OK;
 }
 
-// FP32 copies used by the mixed-precision preconditioner.
 // Decoupling; MIXED: with FP32 copies of the decoupled blocks and the fine
 // level.  The per-cell kernels stream the Jacobian's planes in one-wave
 // workgroups.
