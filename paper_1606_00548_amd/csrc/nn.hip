@@ -381,15 +381,21 @@ __global__ __launch_bounds__(256, (conv_per_cu<CI, CO, UP, KS, NS>())) void conv
         const long o = o0 + (long)m * g.nx;
         if constexpr (EPI == 1 && CO == 16) {
           if (p.head) {
-            // y = sum_c head[c] (relu(acc + bias) + skip)[c] + head[CO]
+            // y = sum_c head[c] (relu(acc + bias) + skip)[c] + head[CO], by a
+            // tree over the channels: c and c + 8, then 4, 2 and 1 apart, the
+            // first of each pair fused
             const f32x4 a = acc[m][0];
             const float4 k = skv[m][0];
-            float h = (fmaxf(a[0] + bias[0].x, 0.f) + k.x) * p.head[c0];
-            h += (fmaxf(a[1] + bias[0].y, 0.f) + k.y) * p.head[c0 + 1];
-            h += (fmaxf(a[2] + bias[0].z, 0.f) + k.z) * p.head[c0 + 2];
-            h += (fmaxf(a[3] + bias[0].w, 0.f) + k.w) * p.head[c0 + 3];
-            h += __shfl_xor(h, 32);
-            h += __shfl_xor(h, 16);
+            const float v[4] = {fmaxf(a[0] + bias[0].x, 0.f) + k.x, fmaxf(a[1] + bias[0].y, 0.f) + k.y,
+                                fmaxf(a[2] + bias[0].z, 0.f) + k.z, fmaxf(a[3] + bias[0].w, 0.f) + k.w};
+            float t[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float w = p.head[c0 + e];
+              t[e] = __builtin_fmaf(v[e], w, __shfl_xor(__fmul_rn(v[e], w), 32));
+              t[e] += __shfl_xor(t[e], 16);
+            }
+            const float h = (t[0] + t[2]) + (t[1] + t[3]);
             if (ok && kq == 0) p.y[o] = h + p.head[CO];
             continue;
           }
