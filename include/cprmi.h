@@ -287,9 +287,12 @@ int cpr_export_jacobian(cpr_ctx_t* ctx, double* blocks);
  * the pressure multigrid hierarchy on A_p = (A~)_pp (2x2x2 aggregation,
  * Galerkin coarse operators, dense inverse of the coarsest level; a level
  * above the coarsest with odd nx is stored with a ghost column) and the
- * red-black block ILU(0) diagonals of A~.  Synchronises the stream (to report singular blocks).  Returns
- * CPR_ESINGULAR if a diagonal block or the coarsest operator cannot be
- * inverted, CPR_EINVAL for an unknown decoupling or composition. */
+ * red-black block ILU(0) diagonals of A~.  Synchronises the stream (to report
+ * singular blocks; twice where a coarsest level of 129 to 512 cells has red
+ * diagonals that are no pivots and is inverted with pivoting over all rows).
+ * Returns CPR_ESINGULAR if a diagonal block or the coarsest operator cannot
+ * be inverted (a coarsest level of up to 128 cells: also if a red diagonal is
+ * zero), CPR_EINVAL for an unknown decoupling or composition. */
 int cpr_setup(cpr_ctx_t* ctx, const cpr_options_t* o);
 
 /* Solve A dx = rhs (both device, [b][n]) from dx = 0 (or from the dx passed
